@@ -219,7 +219,7 @@ int max_nodes() {
 // and kv [nrhs] for the refinement levels.
 struct InnerScratch {
   double2* mult = nullptr;
-  unsigned char* swp = nullptr;
+  unsigned long long* swp = nullptr;
   double2* part = nullptr;
   double2* ys = nullptr;
   double2* acc = nullptr;
@@ -1076,7 +1076,7 @@ static ovs_status sign_apply_impl(ovs_lattice l, ovs_deflation defl, int32_t n_d
     double *beta, *sv, *tnorm2, *qerr, *red, *apart, *red_n, *red_tn, *scl, *dnorm;
     int *kstop, *status, *rhs_map, *ints, *kused, *pidx, *kv;
     QuadNodes* rules;
-    unsigned char* swp;
+    unsigned long long* swp;
     double2 *probes, *yp;
     unsigned* bar;
   } B{};
@@ -1130,7 +1130,7 @@ static ovs_status sign_apply_impl(ovs_lattice l, ovs_deflation defl, int32_t n_d
     if (!arn) {
       const int wchunk = std::min(kIsignWaveChunk, nwave_max);
       B.mult = a.take<double2>((size_t)nr * wchunk * K * 64);
-      B.swp = a.take<unsigned char>((size_t)nr * wchunk * K * 64);
+      B.swp = a.take<unsigned long long>((size_t)nr * wchunk * isign_swp_words(K) * 64);
       B.part = a.take<double2>((size_t)nr * nwave_max * 2 * K);
       B.dnorm = a.take<double>((size_t)nr * K);
       if (monitor) {
@@ -2087,7 +2087,7 @@ static ovs_status inner_sign_entry(ovs_lattice l, bool tri, int batch, int k, co
       be = a.take<double>((size_t)batch * k);
       ga = a.take<double2>((size_t)batch * k);
       sc.mult = a.take<double2>((size_t)batch * wchunk * k * 64);
-      sc.swp = a.take<unsigned char>((size_t)batch * wchunk * k * 64);
+      sc.swp = a.take<unsigned long long>((size_t)batch * wchunk * isign_swp_words(k) * 64);
       sc.part = a.take<double2>((size_t)batch * nwave * 2 * k);
     } else {
       H = a.take<double2>((size_t)batch * k * k);

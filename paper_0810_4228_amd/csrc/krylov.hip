@@ -489,14 +489,54 @@ __global__ void k_scale_copy(const T2* __restrict__ T, T2* __restrict__ out, lon
 // multiplier and one swap bit per column.
 // ===========================================================================
 
+// 1 / d to within an ulp by two Newton steps, and n / d from it with one
+// residual correction: the quotient an IEEE division returns (whose expansion
+// is these steps between scalings by powers of two) while no intermediate
+// leaves the normal range.
+__device__ __forceinline__ double newton_rcp(double d) {
+  double y = __builtin_amdgcn_rcp(d);
+  y = fma(y, fma(-d, y, 1.0), y);
+  return fma(y, fma(-d, y, 1.0), y);
+}
+__device__ __forceinline__ double quotient(double n, double d, double y) {
+  const double q = n * y;
+  return fma(fma(-d, q, n), y, q);
+}
+
+// c ? a : b by components (a select of whole structures can go through scratch)
+__device__ __forceinline__ Cx<double> csel(bool c, Cx<double> a, Cx<double> b) {
+  return {c ? a.re : b.re, c ? a.im : b.im};
+}
+
+// The value that lane l (uniform) of the wave holds.
+__device__ __forceinline__ double lane_value(double v, int l) {
+  const int lo = __builtin_amdgcn_readlane(__double2loint(v), l);
+  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), l);
+  return __hiloint2double(hi, lo);
+}
+
 // One thread per (source r, shifted solve q): q = 2*node + (0: +tau, 1: -tau).
 // Tridiagonal T_r = tridiag(beta, alpha, gamma) of size k_r, with the rule of
 // source r (rules[r]: each source may be at its own step).  Wave results are
 // reduced over lanes: part[r][wave][2][kmax] complex (fine rule, coarse rule),
 // wave = wave0 + blockIdx.x of nwave in all; waves beyond a source's nodes
 // write zero rows.  A launch covers one chunk of waves; the multipliers of a
-// chunk live in mult/swp [r][blockIdx.x][kmax][64], which the next chunk
+// chunk live in mult [r][blockIdx.x][kmax][64] and swp, which the next chunk
 // (ordered on the stream) reuses.
+//
+// swp holds the swaps as bits: word w of a wave and lane is steps 64 w to
+// 64 w + 63 from the bottom, isign_swp_words(kmax) words.
+//
+// Bound by the latency of one wave's serial chain, k elimination steps and k
+// rows back, whatever the number of waves.  A step is two dependent quotients
+// and a complex multiply-add: the pivot test compares squares (hypot only for
+// near ties and extreme values), both pivot cases share one quotient by
+// selects (the subdiagonal is real, so Smith's quotient by it is two plain
+// ones), and the coefficients of 64 steps sit in the lanes of the wave, loaded
+// a block ahead and read by readlane.  The rows back load their multipliers a
+// block of 16 ahead.  One source, k = 375 on average (the checks of an 8^4
+// solve): 217 us a launch with hypot, three divergent divisions and one
+// scalar load per step, 130 us so.
 __global__ void __launch_bounds__(64) k_isign_tri(const double2* __restrict__ alpha,
                                                   const double* __restrict__ beta,
                                                   const double2* __restrict__ gamma, int kmax,
@@ -504,7 +544,7 @@ __global__ void __launch_bounds__(64) k_isign_tri(const double2* __restrict__ al
                                                   const QuadNodes* __restrict__ rules,
                                                   int wave0, int nwave,
                                                   double2* __restrict__ mult,
-                                                  unsigned char* __restrict__ swp,
+                                                  unsigned long long* __restrict__ swp,
                                                   double2* __restrict__ part) {
   const int r = blockIdx.y;
   const QuadNodes qn = rules[r];
@@ -523,6 +563,8 @@ __global__ void __launch_bounds__(64) k_isign_tri(const double2* __restrict__ al
   const double* be = beta + (long)r * kmax;
   const double2* ga = gamma + (long)r * kmax;
   const long mbase = ((long)(r * gridDim.x + blockIdx.x) * kmax) * 64 + lane;
+  unsigned long long* swap_w =
+      swp + (long)(r * gridDim.x + blockIdx.x) * isign_swp_words(kmax) * 64 + lane;
   double2* part_r = part + ((long)r * nwave + wave) * 2 * kmax;
   if (k <= 0) return;
   if (wave * 64 >= nq) {
@@ -537,26 +579,65 @@ __global__ void __launch_bounds__(64) k_isign_tri(const double2* __restrict__ al
   // elimination from the bottom: current column j holds (cu: row j-1, cd: row j)
   Cx<double> cu = (k >= 2) ? c64(ga[k - 2]) : Cx<double>{0, 0};
   Cx<double> cd = c64(al[k - 1]) + Cx<double>{0.0, sig};
-  for (int j = k - 1; j >= 1; --j) {
-    const Cx<double> du = (j >= 2) ? c64(ga[j - 2]) : Cx<double>{0, 0};
-    const Cx<double> dm = c64(al[j - 1]) + Cx<double>{0.0, sig};
-    const Cx<double> dd = {be[j - 1], 0.0};
-    const bool sw = cabs1(dd) > cabs1(cd);
-    Cx<double> m;
-    if (sw) {
-      m = cdiv(cd, dd);
+  // lane l of a block starting at column j0 holds the entries of column
+  // j0 - l (below column 1: clamped loads, never used)
+  struct Block {
+    double2 a, g;
+    double b;
+  };
+  auto load_block = [&](int j0) {
+    const int j = j0 - lane;
+    Block o;
+    o.a = al[max(j - 1, 0)];
+    o.b = be[max(j - 1, 0)];
+    o.g = ga[max(j - 2, 0)];
+    if (j < 2) o.g = make_double2(0.0, 0.0);
+    return o;
+  };
+  Block nxt = load_block(k - 1);
+  for (int j0 = k - 1; j0 >= 1; j0 -= 64) {
+    const Block cur = nxt;
+    nxt = load_block(j0 - 64);
+    const int n = min(64, j0);
+    unsigned long long swaps = 0;
+#pragma unroll 2
+    for (int l = 0; l < n; ++l) {
+      const int j = j0 - l;
+      const Cx<double> du = {lane_value(cur.g.x, l), lane_value(cur.g.y, l)};
+      const Cx<double> dm = Cx<double>{lane_value(cur.a.x, l), lane_value(cur.a.y, l)} +
+                            Cx<double>{0.0, sig};
+      const double dd = lane_value(cur.b, l);
+      // sw: |dd| > |cd| as hypot compares them; m = sw ? cd / dd : dd / cd, the
+      // latter by Smith's algorithm
+      const double b2 = dd * dd, c2 = fma(cd.re, cd.re, cd.im * cd.im);
+      const double top = fmax(b2, c2), low = fmin(b2, c2);
+      bool sw = b2 > c2;
+      const bool big = fabs(cd.re) >= fabs(cd.im);
+      const double hi = big ? cd.re : cd.im, lo = big ? cd.im : cd.re;
+      double rr = quotient(lo, hi, newton_rcp(hi));
+      // squares apart by more than their rounding, and every quotient in the
+      // normal range
+      const bool plain = (top > low * 1.0000000001) & (top < 1e280) & (c2 > 1e-280);
+      if (!plain) {
+        sw = fabs(dd) > cabs1(cd);
+        rr = lo / hi;
+      }
+      const double den = sw ? dd : hi + lo * rr;
+      const double br = dd * rr;
+      const double nre = sw ? cd.re : (big ? dd : br);
+      const double nim = sw ? cd.im : (big ? -br : -dd);
+      const double y = newton_rcp(den);
+      Cx<double> m = {quotient(nre, den, y), quotient(nim, den, y)};
+      if (!plain) m = {nre / den, nim / den};
+      // sw: column = (-m du, cu - m dm), else (du, dm - m cu)
+      const Cx<double> t = cmul(m, csel(sw, dm, cu));
       const Cx<double> nu_ = -cmul(m, du);
-      const Cx<double> nd = cu - cmul(m, dm);
-      cu = nu_;
-      cd = nd;
-    } else {
-      m = cdiv(dd, cd);
-      const Cx<double> nd = dm - cmul(m, cu);
-      cu = du;
-      cd = nd;
+      cd = csel(sw, cu, dm) - t;
+      cu = csel(sw, nu_, du);
+      mult[mbase + (long)j * 64] = d2(m);
+      swaps |= (unsigned long long)sw << l;
     }
-    mult[mbase + (long)j * 64] = d2(m);
-    swp[mbase + (long)j * 64] = sw ? 1 : 0;
+    swap_w[(long)((k - 1 - j0) >> 6) * 64] = swaps;
   }
   const Cx<double> inv_r00 = cdiv(Cx<double>{1.0, 0.0}, cd);
   // z = P E e_1 streamed out top-down; row j-1 is final after column j.  The
@@ -565,46 +646,47 @@ __global__ void __launch_bounds__(64) k_isign_tri(const double2* __restrict__ al
   constexpr int kRows = 16;
   __shared__ double rows[kRows][4][65];  // [row][fine re, fine im, coarse re, coarse im][lane]
   Cx<double> cur = inv_r00;
+  // a block's multipliers and swaps, loaded together and one block ahead of
+  // their use (rows from k on clamped to row k-1, never used)
+  double2 mb[kRows], mn[kRows];
+  unsigned long long sb[2], sn[2];  // words of the block's first and last row
+  auto word = [&](int j) { return max(k - 1 - j, 0) >> 6; };
+  auto load_rows = [&](int j0) {
+#pragma unroll
+    for (int t = 0; t < kRows; ++t) mn[t] = mult[mbase + (long)min(j0 + t, k - 1) * 64];
+    sn[0] = swap_w[(long)word(j0) * 64];
+    sn[1] = swap_w[(long)word(j0 + kRows - 1) * 64];
+  };
+  if (k > 1) load_rows(1);
   for (int j0 = 1; j0 <= k; j0 += kRows) {
     const int nrow = min(kRows, k - j0 + 1);
-    // the block's multipliers and swaps, loaded together rather than one row
-    // per dependent step (rows from k on clamped to row k-1, never used)
-    double2 mb[kRows];
-    unsigned char sb[kRows];
+#pragma unroll
+    for (int t = 0; t < kRows; ++t) mb[t] = mn[t];
+    sb[0] = sn[0];
+    sb[1] = sn[1];
+    if (j0 + kRows <= k) load_rows(j0 + kRows);
+    // rows beyond k (the last block's tail) are formed from clamped entries and
+    // not read
 #pragma unroll
     for (int t = 0; t < kRows; ++t) {
-      const long jc = min(j0 + t, k - 1);
-      mb[t] = mult[mbase + jc * 64];
-      sb[t] = swp[mbase + jc * 64];
-    }
-#pragma unroll
-    for (int t = 0; t < kRows; ++t) {
-      if (t < nrow) {
-        const int j = j0 + t;
-        Cx<double> fin;
-        if (j < k) {
-          const Cx<double> m = c64(mb[t]);
-          const Cx<double> nw = -cmul(m, cur);
-          if (sb[t]) {
-            fin = nw;
-          } else {
-            fin = cur;
-            cur = nw;
-          }
-        } else {
-          fin = cur;
-        }
-        rows[t][0][lane] = wfine * fin.re;
-        rows[t][1][lane] = wfine * fin.im;
-        rows[t][2][lane] = wcoarse * fin.re;
-        rows[t][3][lane] = wcoarse * fin.im;
-      }
+      const Cx<double> nw = -cmul(c64(mb[t]), cur);
+      const int j = j0 + t;
+      const unsigned long long w = word(j) == word(j0) ? sb[0] : sb[1];
+      const bool swapped = (w >> ((k - 1 - j) & 63)) & 1;
+      const bool take = swapped & (j < k);  // row k-1: the current value
+      const Cx<double> fin = csel(take, nw, cur);
+      cur = csel(swapped, cur, nw);
+      rows[t][0][lane] = wfine * fin.re;
+      rows[t][1][lane] = wfine * fin.im;
+      rows[t][2][lane] = wcoarse * fin.re;
+      rows[t][3][lane] = wcoarse * fin.im;
     }
     __syncthreads();
     {
       const int t = lane & (kRows - 1), c = lane / kRows;  // 16 rows x 4 parts = 64 lanes
       if (t < nrow) {
         double acc = 0.0;
+#pragma unroll 16
         for (int l = 0; l < 64; ++l) acc += rows[t][c][l];
         double* out = reinterpret_cast<double*>(part_r + (c < 2 ? 0 : kmax) + (j0 - 1 + t));
         out[c & 1] = acc;
@@ -614,7 +696,10 @@ __global__ void __launch_bounds__(64) k_isign_tri(const double2* __restrict__ al
   }
 }
 
-// x[r][j] = sum over waves (fixed order); err[r] = |x_fine - x_coarse| / |x_fine|
+// x[r][j] = sum over waves (fixed order); err[r] = |x_fine - x_coarse| / |x_fine|.
+// One workgroup per source, bound by memory latency: the loads of eight waves
+// are issued before their additions (22 waves, k = 375: 21 us one at a time,
+// 10.6 us so).
 __global__ void __launch_bounds__(256) k_isign_final(const double2* __restrict__ part, int nwave,
                                                      int kmax, const int* __restrict__ kvec,
                                                      double2* __restrict__ x,
@@ -626,10 +711,24 @@ __global__ void __launch_bounds__(256) k_isign_final(const double2* __restrict__
   for (int j = threadIdx.x; j < kmax; j += blockDim.x) {
     Cx<double> f = {0, 0}, c = {0, 0};
     if (j < k) {
-      for (int w = 0; w < nwave; ++w) {
-        const double2* p = part + ((long)r * nwave + w) * 2 * kmax;
-        f = f + c64(p[j]);
-        c = c + c64(p[kmax + j]);
+      const double2* p = part + (long)r * nwave * 2 * kmax + j;
+      int w = 0;
+      for (; w + 8 <= nwave; w += 8) {
+        double2 a[8], b[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          a[u] = p[(long)(w + u) * 2 * kmax];
+          b[u] = p[(long)(w + u) * 2 * kmax + kmax];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          f = f + c64(a[u]);
+          c = c + c64(b[u]);
+        }
+      }
+      for (; w < nwave; ++w) {
+        f = f + c64(p[(long)w * 2 * kmax]);
+        c = c + c64(p[(long)w * 2 * kmax + kmax]);
       }
     }
     x[(long)r * kmax + j] = d2(f);
@@ -998,7 +1097,7 @@ int isign_tri_nwave(int nnode) { return cdiv_i(2L * nnode, 64); }
 
 void launch_isign_tri(const double2* alpha, const double* beta, const double2* gamma, int kmax,
                       const int* kvec, int nrhs, const QuadNodes* rules, int nwave, double2* mult,
-                      unsigned char* swp, double2* part, double2* x, double* err, hipStream_t s) {
+                      unsigned long long* swp, double2* part, double2* x, double* err, hipStream_t s) {
   const int nw = std::max(nwave, 1);
   for (int w0 = 0; w0 < nw; w0 += kIsignWaveChunk)
     hipLaunchKernelGGL(k_isign_tri, dim3(std::min(kIsignWaveChunk, nw - w0), nrhs), dim3(64), 0,

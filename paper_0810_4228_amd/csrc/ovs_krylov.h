@@ -80,8 +80,8 @@ void launch_scale_copy(bool f32, const void* T, void* out, long N, const double*
 
 // Inner sign by the tau = e^u trapezoid rule.  The tridiagonal form runs its
 // shifted solves in launches of at most kIsignWaveChunk waves of 64 solves
-// per source (mult, swp: [nrhs][kIsignWaveChunk][kmax][64]; part: [nrhs][all
-// waves][2][kmax]); the Hessenberg form kIsignHessChunk solves per source
+// per source (mult: [nrhs][kIsignWaveChunk][kmax][64]; swp: [nrhs]
+// [kIsignWaveChunk][isign_swp_words(kmax)][64]; part: [nrhs][all waves][2][kmax]); the Hessenberg form kIsignHessChunk solves per source
 // (ys: [nrhs][kIsignHessChunk][kmax]; acc: [nrhs][2][kmax]).  A launch takes
 // about k sequential elimination steps whatever its number of waves, so the
 // chunk holds every solve of the rules down to step 1/16 (43 waves): one
@@ -95,11 +95,13 @@ struct QuadNodes {
   int nnode;  // number of nodes
 };
 int isign_tri_nwave(int nnode);
+// 64-bit words that hold one swap bit for each of kmax elimination steps
+__host__ __device__ inline int isign_swp_words(int kmax) { return (kmax + 63) / 64; }
 // rules: device array [nrhs], the rule of each source; nwave: the largest
 // isign_tri_nwave over the sources with kvec[r] > 0 (the part stride).
 void launch_isign_tri(const double2* alpha, const double* beta, const double2* gamma, int kmax,
                       const int* kvec, int nrhs, const QuadNodes* rules, int nwave, double2* mult,
-                      unsigned char* swp, double2* part, double2* x, double* err, hipStream_t s);
+                      unsigned long long* swp, double2* part, double2* x, double* err, hipStream_t s);
 void launch_isign_hess(const double2* H, int kmax, const int* kvec, int nrhs, double h, int n0,
                        int nnode, double2* ys, double2* acc, double2* x, double* err,
                        hipStream_t s);

@@ -1,0 +1,42 @@
+"""Kernel variants at the sizes where they can go wrong: edges of their blocks and
+tiles, remainders, degenerate entries (GPU)."""
+import numpy as np
+import pytest
+
+import synth
+from gpu_util import rel, say
+from oracle import krylov, sign
+
+pytestmark = pytest.mark.gpu
+
+MW = -1.5
+
+
+@pytest.mark.parametrize("kind", ["random", "ties"])
+@pytest.mark.parametrize("k", [1, 2, 15, 16, 17, 18, 63, 64, 65, 66, 80, 128, 129, 130, 193])
+def test_inner_sign_tridiag_block_edges(kind, k):
+    """sgn(G) e_1 (eq. 1.3) at sizes around the 64-step blocks of the elimination
+    and the 16-row blocks of the way back, against the oracle's spectral sign.
+    ties: zero diagonal with alternating couplings 1 and 0.4 (even sizes; an odd
+    one has a zero eigenvalue), so that the pivot test compares equal moduli at
+    the node tau = 1 and meets exact zeros.  The accepted coarse/fine difference
+    (3e-7) bounds the coarse rule's error, hence 6e-7."""
+    import paper_0810_4228_amd as ovs
+    rng = np.random.default_rng(100 + k)
+    if kind == "ties":
+        if k % 2:
+            pytest.skip("odd chains have a zero eigenvalue")
+        diag = np.zeros(k, complex)
+        c = np.where(np.arange(k) % 2 == 0, 1.0, 0.4)
+        sub, sup = c.astype(complex), c.astype(complex)
+    else:
+        diag = rng.choice([-1.0, 1.0], k) * (1 + 0.3 * rng.random(k)) + 0.2j * rng.standard_normal(k)
+        sub = (0.05 + 0.1 * rng.random(k)).astype(complex)
+        sup = 0.1 * (rng.standard_normal(k) + 1j * rng.standard_normal(k))
+    G = krylov.tridiag(diag, sub[:k - 1].real, sup[:k - 1])
+    lat = ovs.Lattice((2, 2, 2, 2))
+    x, err, st = lat.inner_sign_tridiag(diag[None], sub[None], sup[None], return_status=True)
+    e = rel(x[0], sign.sign_e1(G))
+    say(f"inner sign {kind} k={k}: {e:.2e}, estimate {err[0]:.1e}, status {st}")
+    assert st == 0
+    assert e <= 6e-7
