@@ -67,24 +67,18 @@ bool valid_op(int op) { return op >= 0 && op <= 3; }
 size_t elem_bytes(const ovs_lattice_s* l) { return l->prec == OVS_F32_STORE ? 8 : 16; }
 
 
-Tuning get_tuning(const ovs_lattice_s* l, int nrhs) {
+// The configuration set for batches of nrhs sources, or the default of a launch
+// of `launch` of them (0: all).
+Tuning get_tuning(const ovs_lattice_s* l, int nrhs, int launch) {
   for (auto& p : l->tuning)
     if (p.first == nrhs) return p.second;
-  Tuning t;
-  const bool f32 = l->prec == OVS_F32_STORE;
-  t.rhs_block = f32 ? (nrhs >= 4 ? 4 : (nrhs >= 2 ? 2 : 1)) : 1;
-  // smaller workgroups while the grid is small: more CUs take part (8^4 with
-  // one source: 64 workgroups of 64 rather than 16 of 256)
-  const long blocks = (nrhs + t.rhs_block - 1) / t.rhs_block;
-  t.wg = 256;
-  while (t.wg > 64 && (long)l->g.V / t.wg * blocks < 1024) t.wg /= 2;
-  return t;
+  return default_tuning(l->prec == OVS_F32_STORE, l->g, launch > 0 ? launch : nrhs);
 }
 
-Tuning get_dual_tuning(const ovs_lattice_s* l, int nrhs) {
+Tuning get_dual_tuning(const ovs_lattice_s* l, int nrhs, int launch = 0) {
   for (auto& p : l->dual_tuning)
     if (p.first == nrhs) return p.second;
-  return Tuning{};
+  return default_dual_tuning(l->prec == OVS_F32_STORE, l->g, launch > 0 ? launch : nrhs);
 }
 
 void set_tuning(ovs_lattice_s* l, int nrhs, const Tuning& t) {
@@ -96,6 +90,10 @@ void set_dual_tuning(ovs_lattice_s* l, int nrhs, const Tuning& t) {
   for (auto& p : l->dual_tuning)
     if (p.first == nrhs) { p.second = t; return; }
   l->dual_tuning.push_back({nrhs, t});
+}
+
+void clear_tuning(std::vector<std::pair<int, Tuning>>& v, int nrhs) {
+  v.erase(std::remove_if(v.begin(), v.end(), [&](auto& p) { return p.first == nrhs; }), v.end());
 }
 
 // Occupancy caps tried by the autotuner: dynamic LDS per workgroup in KiB
@@ -624,14 +622,14 @@ ovs_status ovs_dual_apply_timed(ovs_lattice l, ovs_field v, int32_t iters, doubl
   const int nwg = dual_num_wg(l->g);
   Arena a{nullptr};
   a.take<char>(fb); a.take<char>(fb); a.take<char>(fb);
-  a.take<double>((size_t)nrhs * nwg * 3); a.take<int>(nrhs); a.take<int>(2);
+  a.take<double>((size_t)nrhs * nwg * 12); a.take<int>(nrhs); a.take<int>(2);
   ovs_status st = ensure_ws(l, a.off + 4096);
   if (st != OVS_OK) return st;
   Arena b{(char*)l->ws};
   void* T = b.take<char>(fb);
   void* S = b.take<char>(fb);
   void* Wt = b.take<char>(fb);  // w~: a copy of v in its own memory, as in the solve
-  double* part = b.take<double>((size_t)nrhs * nwg * 3);
+  double* part = b.take<double>((size_t)nrhs * nwg * 12);
   int* map = b.take<int>(nrhs);
   int* ints = b.take<int>(2);
   std::vector<int> hmap(nrhs);
@@ -645,7 +643,7 @@ ovs_status ovs_dual_apply_timed(ovs_lattice l, ovs_field v, int32_t iters, doubl
   // V~ = the field, W~ = its copy: distinct memory, so the A and A^dag
   // workgroups of a tile do not share spinor fetches (iteration 0 reads slot 0)
   const DualArgs da{l->links, v->data, Wt, (long)nrhs * N, false, ints, T, S, part, map,
-                    ints + 1, nrhs, dt.lds_kb, dt.order, dt.nt & 1, dt.g - 1};
+                    ints + 1, nrhs, dt.lds_kb, dt.order, dt.nt & 1, dual_pair_of(dt)};
   const Hop hA = make_hop(l->m_w, l->mu), hAd = make_hop(l->m_w, -l->mu);
   hipEvent_t e0, e1;
   OVS_HIP(hipEventCreate(&e0));
@@ -744,7 +742,7 @@ ovs_status ovs_autotune(ovs_lattice l, int32_t nrhs) {
     const int blocks_f32[] = {1, 2, 3, 4, 6};
     const int blocks_f64[] = {1, 2, 3};
     const int wgs[] = {64, 128, 256};
-    Tuning best = get_tuning(l, nrhs);
+    Tuning best;
     double best_ms = 1e300;
     const int* bl = f32 ? blocks_f32 : blocks_f64;
     const int nb = f32 ? 5 : 3;
@@ -782,7 +780,17 @@ ovs_status ovs_autotune(ovs_lattice l, int32_t nrhs) {
           }
     }
     best.tuned = true;
-    if (st == OVS_OK) set_tuning(l, nrhs, best);
+    // a default that none of the candidates beats (one wave per hop is not among
+    // them) stays the batch's configuration
+    double def_ms = 1e300;
+    const Tuning def = default_tuning(f32, l->g, nrhs);
+    if (timed_loop(l, OVS_OP_A, fi, fo, 2, def, &def_ms) != OVS_OK ||
+        timed_loop(l, OVS_OP_A, fi, fo, 8, def, &def_ms) != OVS_OK)
+      def_ms = 1e300;
+    if (st == OVS_OK) {
+      if (def.hops && def_ms <= best_ms) clear_tuning(l->tuning, nrhs);
+      else set_tuning(l, nrhs, best);
+    }
     // dual-stencil source block for the Lanczos step
     if (st == OVS_OK) {
       const long N = 12L * l->g.Vs;
@@ -790,7 +798,7 @@ ovs_status ovs_autotune(ovs_lattice l, int32_t nrhs) {
       const int nwg = dual_num_wg(l->g);
       Arena a{nullptr};
       a.take<char>(fb); a.take<char>(3 * fb); a.take<char>(fb); a.take<char>(fb);
-      a.take<double>((size_t)nrhs * nwg * 3); a.take<int>(nrhs); a.take<int>(4);
+      a.take<double>((size_t)nrhs * nwg * 12); a.take<int>(nrhs); a.take<int>(4);
       st = ensure_ws(l, a.off + 4096);
       if (st == OVS_OK) {
         Arena b{(char*)l->ws};
@@ -798,7 +806,7 @@ ovs_status ovs_autotune(ovs_lattice l, int32_t nrhs) {
         void* wbuf = b.take<char>(3 * fb);
         void* T = b.take<char>(fb);
         void* S = b.take<char>(fb);
-        double* part = b.take<double>((size_t)nrhs * nwg * 3);
+        double* part = b.take<double>((size_t)nrhs * nwg * 12);
         int* map = b.take<int>(nrhs);
         int* ints = b.take<int>(4);
         std::vector<int> hmap(nrhs);
@@ -821,19 +829,22 @@ ovs_status ovs_autotune(ovs_lattice l, int32_t nrhs) {
         const Hop hA = make_hop(l->m_w, l->mu), hAd = make_hop(l->m_w, -l->mu);
         Tuning dbest;
         double bms = 1e300;
-        for (int pair = 0; pair < 6; ++pair)
+        const bool with_hops = default_dual_tuning(f32, l->g, n1).hops;
+        for (int pair = 0; pair <= (with_hops ? kDualHops : 5); ++pair)
         for (int bb = 1; bb <= (f32 ? 4 : 2); ++bb) {
           if (bb > nrhs && bb != 1) continue;
           if (pair == 5 && (bb != 1 || !f32)) continue;  // the t march: FP32, one source per thread
+          if (pair == kDualHops && bb != 1) continue;    // one configuration, the default
           for (int kb : lds_candidates(l))
             for (int order = 0; order < (pair == 5 ? 2 : 8); ++order)
               for (int nt = 0; nt < 2; ++nt) {
+              if (pair == kDualHops && (kb || order || nt)) continue;
               const size_t eb = elem_bytes(l);
               DualArgs da{l->links, basis, wbuf, (long)nrhs * N, false, ints, T, S, part, map,
                           halves ? ints + 2 : ints + 1, n1, kb, order, nt, pair};
               DualArgs db{l->links, (char*)basis + n1 * N * eb, (char*)wbuf + n1 * N * eb,
                           (long)nrhs * N, false, ints, (char*)T + n1 * N * eb,
-                          (char*)S + n1 * N * eb, part + (size_t)n1 * nwg * 3, map, ints + 3,
+                          (char*)S + n1 * N * eb, part + (size_t)n1 * nwg * 12, map, ints + 3,
                           n2, kb, order, nt, pair};
               auto launch = [&]() {
                 if (launch_dual(f32, da, l->g, hA, hAd, bb, l->stream) != hipSuccess) return false;
@@ -876,7 +887,10 @@ ovs_status ovs_autotune(ovs_lattice l, int32_t nrhs) {
         // streaming stores measured ~1% faster over whole solves at 16^3 x 32
         dbest.nt |= 2;
         dbest.tuned = true;
-        if (st == OVS_OK) set_dual_tuning(l, nrhs, dbest);
+        if (st == OVS_OK) {
+          if (dbest.g == kDualHops + 1) clear_tuning(l->dual_tuning, nrhs);  // the default
+          else set_dual_tuning(l, nrhs, dbest);
+        }
         if (s2) (void)hipStreamSynchronize(s2);
         if (fork) (void)hipEventDestroy(fork);
         if (join) (void)hipEventDestroy(join);
@@ -1098,7 +1112,7 @@ static ovs_status sign_apply_impl(ovs_lattice l, ovs_deflation defl, int32_t n_d
     if (!arn) B.wbuf = a.take<char>(3ul * nr * N * es);
     B.T = a.take<char>((size_t)nr * N * es);
     if (!arn) B.S = a.take<char>((size_t)nr * N * es);
-    B.part1 = a.take<double>((size_t)nr * nwg_d * 3);
+    B.part1 = a.take<double>((size_t)nr * nwg_d * 12);  // sums of tiles or of their quarters
     B.part2 = a.take<double>((size_t)nr * nwg_u * 4);
     B.spart = a.take<double>((size_t)nr * nch_start * 3);
     B.sums = a.take<double>((size_t)nr * 3);
@@ -1414,10 +1428,11 @@ static ovs_status sign_apply_impl(ovs_lattice l, ovs_deflation defl, int32_t n_d
                           B.rhs_map, B.ints + 1, nr, B.probes, s);
       OVS_HIP(hipStreamSynchronize(s));  // pidx_h lifetime
     }
-    const Tuning dt = get_dual_tuning(l, tune_key);
+    const Tuning dt = get_dual_tuning(l, tune_key, nr);
     const int dual_b = std::min(dt.rhs_block, f32 ? 4 : 2);
+    const bool quad = dt.hops;
     DualArgs da{l->links, B.basis, B.wbuf, bstride, two_pass, B.ints, B.T, B.S, B.part1,
-                B.rhs_map, B.ints + 1, nr, dt.lds_kb, dt.order, dt.nt & 1, dt.g - 1};
+                B.rhs_map, B.ints + 1, nr, dt.lds_kb, dt.order, dt.nt & 1, dual_pair_of(dt)};
     // one full iteration is three launches: dual stencil; update (forming
     // alpha); beta with the probe gather and the iteration advance.  The last
     // iteration only forms alpha.
@@ -1425,12 +1440,12 @@ static ovs_status sign_apply_impl(ovs_lattice l, ovs_deflation defl, int32_t n_d
       OVS_HIP(launch_dual(f32, da, l->g, hA, hAd, dual_b, s));
       if (full) {
         launch_update(f32, B.T, B.S, B.basis, bstride, B.wbuf, N, co, B.ints, B.rhs_map,
-                      B.ints + 1, nr, B.part2, two_pass, B.part1, nwg_d, (dt.nt >> 1) & 1, s);
+                      B.ints + 1, nr, B.part2, two_pass, B.part1, nwg_d, quad, (dt.nt >> 1) & 1, s);
         launch_beta_tail(f32, B.part2, nwg_u, co, B.ints, B.rhs_map, B.ints + 1, nr, B.ints + 2,
                          B.basis, bstride, N, two_pass, B.pidx, P, probing ? B.probes : nullptr,
                          s);
       } else {
-        launch_alpha(B.part1, nwg_d, co, B.ints, B.rhs_map, B.ints + 1, nr, s);
+        launch_alpha(B.part1, nwg_d, quad, co, B.ints, B.rhs_map, B.ints + 1, nr, s);
         launch_advance(B.ints, s);
       }
       OVS_HIP(hipGetLastError());
@@ -1472,7 +1487,7 @@ static ovs_status sign_apply_impl(ovs_lattice l, ovs_deflation defl, int32_t n_d
         const int n = std::min(chunk, nfull - done_it);
         PersistArgs pa{l->links, B.basis, B.wbuf, bstride, two_pass, B.ints, B.T, B.S, B.part1,
                        B.part2, B.rhs_map, B.ints + 1, nr, std::min(dual_b, f32 ? 2 : 1),
-                       dt.g == 5, dt.order, dt.nt & 1, (dt.nt >> 1) & 1, co, B.pidx, P,
+                       dt.tuned && dt.g == 5, dt.order, dt.nt & 1, (dt.nt >> 1) & 1, co, B.pidx, P,
                        probing ? B.probes : nullptr, n, B.bar};
         OVS_HIP(launch_persistent(f32, pa, l->g, hA, hAd, s));
         done_it += n;
@@ -1608,7 +1623,7 @@ static ovs_status sign_apply_impl(ovs_lattice l, ovs_deflation defl, int32_t n_d
       else
         OVS_HIP(hipMemsetAsync(B.Y, 0, sizeof(double2) * nr * N, s));
       const int kmx = *std::max_element(kused.begin(), kused.end());
-      Tuning tn = get_tuning(l, tune_key);
+      Tuning tn = get_tuning(l, tune_key, nr);
       for (int it = 0; it < kmx; ++it) {
         if (it + 1 < kmx)
           OVS_HIP(launch_wilson(f32, l->links, B.basis + (size_t)(it % 3) * bstride * es, B.T, nr,
@@ -1630,7 +1645,7 @@ static ovs_status sign_apply_impl(ovs_lattice l, ovs_deflation defl, int32_t n_d
     OVS_HIP(hipMemcpyAsync(l->last_x.data(), B.x, sizeof(double2) * nr * K, hipMemcpyDeviceToHost, s));
   } else {
     // ---- Arnoldi with classical Gram-Schmidt applied twice (Section 2) ----
-    Tuning tn = get_tuning(l, tune_key);
+    Tuning tn = get_tuning(l, tune_key, nr);
     // convergence checks as for 2sL: every kCheckEvery steps, x_j = sgn(H_j) e_1
     // and y on the sampled entries; a converged source keeps its k (its later
     // columns are computed but not used)

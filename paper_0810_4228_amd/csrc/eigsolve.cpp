@@ -101,7 +101,6 @@ ovs_status compute_eigentriples(ovs_lattice_s* l, int m, double tol, int max_ite
   if (Np > 0x7fffffffL) return OVS_ERR_ARG;
   const void* links64 = (l->prec == OVS_F64) ? l->links : l->links64;
   if (!links64) return OVS_ERR_STATE;
-  Tuning t64;  // FP64 stencil, one source per thread
   const Hop hA = hop_of(l->m_w, l->mu), hAd = hop_of(l->m_w, -l->mu);
   const bool progress = (l->debug_flags & OVS_DEBUG_PROGRESS) != 0;
   Ranges rg(l, "ovs_deflation_compute");
@@ -147,7 +146,8 @@ ovs_status compute_eigentriples(ovs_lattice_s* l, int m, double tol, int max_ite
     return hipGetLastError() == hipSuccess;
   };
   auto apply = [&](const double2* X, double2* Y, int n, const Hop& h) -> bool {
-    return launch_wilson(false, links64, X, Y, n, g, h, false, true, t64, s) == hipSuccess;
+    return launch_wilson(false, links64, X, Y, n, g, h, false, true,
+                         default_tuning(false, g, n), s) == hipSuccess;
   };
   auto norms2 = [&](const double2* X, int n, std::vector<double>& out) -> bool {
     launch_norm2(false, X, Np, n, part, red, s);

@@ -152,16 +152,13 @@ static ovs_status vjp_impl(ovs_lattice l, ovs_deflation defl, int32_t n_defl, co
     double2 *kappa, *coefQ, *coefL;
     int* kused;
     // paired stencil (T = A x, S = A^dagger y in one launch): iteration 0,
-    // active count, identity source map; per-tile partials (not used)
+    // active count, identity source map; per-tile partials (written by some forms, not used)
     int* dints;
     double* dpart2;
     // the projected tbar_i and sbar_i of the steps of one force group
     double2 *GT, *GS;
   } P_{};
   GradScalars S{}, S2{};
-  // tile of the paired stencil: 64 sites on small lattices, where 256-site
-  // tiles would leave most CUs idle
-  const int dual_tile = (g.V / 256 < 128) ? 64 : 256;
   // force groups: the link force of cg consecutive reverse steps is summed in
   // one pass (steps i with i / cg equal; the recomputation segments, in both
   // modes, so the sums are the same)
@@ -203,7 +200,7 @@ static ovs_status vjp_impl(ovs_lattice l, ovs_deflation defl, int32_t n_defl, co
     P_.GT = a.take<double2>((size_t)cg * NF);
     P_.GS = a.take<double2>((size_t)cg * NF);
     P_.dints = a.take<int>(2 + (size_t)nrhs);
-    P_.dpart2 = a.take<double>((size_t)nrhs * ((g.V + dual_tile - 1) / dual_tile) * 3);
+    P_.dpart2 = a.take<double>((size_t)nrhs * dual_num_wg(g) * 3);
     P_.vjp = a.take<char>(isign_vjp_scratch_bytes(k, nnmax));
     for (int lv = 0; lv < 2; ++lv) {
       P_.vo[lv].x = a.take<double2>(k);
@@ -299,14 +296,15 @@ static ovs_status vjp_impl(ovs_lattice l, ovs_deflation defl, int32_t n_defl, co
   auto applyAd = [&](const double2* in, double2* out) {
     return launch_wilson(false, l->links, in, out, nrhs, g, hAd, false, true, tn, l->stream);
   };
-  // ta = A x and tb = A^dagger y in one launch (the dual stencil of the solve,
-  // one thread per site for both operators): half the launches of a pair of
-  // applications, and the links read once.  Every step of the forward pass,
+  // ta = A x and tb = A^dagger y in one launch (the dual stencil of the solve):
+  // half the launches of a pair of applications, and the links read once.  Every step of the forward pass,
   // its replay and the reverse sweep uses it, so replayed vectors stay
   // bitwise equal to the forward ones.
+  const int pair = dual_pair_of(default_dual_tuning(false, g, nrhs));
   auto applyBoth = [&](const double2* x, const double2* y, double2* ta, double2* tb) {
-    DualArgs da{l->links, x, y, 0, false, P_.dints, ta, tb, P_.dpart2, P_.dints + 2,
-                P_.dints + 1, nrhs, 0, 0, 0, 0, dual_tile};
+    DualArgs da{l->links, x, y, 0, false, P_.dints, ta, tb,
+                pair == kDualHops ? nullptr : P_.dpart2, P_.dints + 2, P_.dints + 1, nrhs, 0, 0, 0,
+                pair};
     return launch_dual(false, da, g, hA, hAd, 1, l->stream);
   };
   auto mks = [&](const GradScalars& Sx, std::initializer_list<const double2*> xs, int tab,

@@ -170,10 +170,10 @@ __global__ void k_start_vectors(const double2* __restrict__ bR, const double2* _
 // ---- per-step kernels (bodies in ovs_lanczos.h) ----------------------------
 
 __global__ void __launch_bounds__(256) k_alpha(const double* __restrict__ partials, int nparts,
-                                               CoefArrays co, const int* __restrict__ it,
+                                               int quad, CoefArrays co, const int* __restrict__ it,
                                                const int* __restrict__ rhs_map,
                                                const int* __restrict__ n_active) {
-  alpha_body(blockIdx.x, *it, partials, nparts, co, rhs_map, *n_active);
+  alpha_body(blockIdx.x, *it, partials, nparts, quad, co, rhs_map, *n_active);
 }
 
 template <typename T2>
@@ -185,10 +185,10 @@ __global__ void __launch_bounds__(256) k_update(const T2* __restrict__ T, const 
                                                 const int* __restrict__ n_active,
                                                 double* __restrict__ partials, int two_pass_ring,
                                                 const double* __restrict__ apart, int anparts,
-                                                int nt) {
+                                                int quad, int nt) {
   update_body<T2>(blockIdx.x, blockIdx.y, gridDim.x, *it, T, S, basis, basis_stride, wbuf,
                   slot_stride, N, co, rhs_map, *n_active, partials, two_pass_ring, apart, anparts,
-                  nt);
+                  quad, nt);
 }
 
 // beta_body for one source slot per workgroup, then the iteration advance:
@@ -929,25 +929,25 @@ void launch_start(const double2* bR, const double2* bL, int nrhs, long N, double
 // first, so fewer and longer-running workgroups keep that head cheap.
 int update_nwg(long N) { return chunks_for(N, 256); }
 
-void launch_alpha(const double* partials, int nparts, const CoefArrays& co, const int* it,
+void launch_alpha(const double* partials, int nparts, bool quad, const CoefArrays& co, const int* it,
                   const int* rhs_map, const int* n_active, int nslots, hipStream_t s) {
-  hipLaunchKernelGGL(k_alpha, dim3(nslots), dim3(256), 0, s, partials, nparts, co, it, rhs_map,
-                     n_active);
+  hipLaunchKernelGGL(k_alpha, dim3(nslots), dim3(256), 0, s, partials, nparts, (int)quad, co, it,
+                     rhs_map, n_active);
 }
 
 void launch_update(bool f32, const void* T, const void* S, void* basis, long basis_stride,
                    void* wbuf, long N, const CoefArrays& co, const int* it, const int* rhs_map,
                    const int* n_active, int nslots, double* partials, bool ring,
-                   const double* apart, int anparts, int nt, hipStream_t s) {
+                   const double* apart, int anparts, bool quad, int nt, hipStream_t s) {
   dim3 grid(update_nwg(N), nslots);
   if (f32)
     hipLaunchKernelGGL(k_update<float2>, grid, dim3(256), 0, s, (const float2*)T, (const float2*)S,
                        (float2*)basis, basis_stride, (float2*)wbuf, N, N, co, it, rhs_map, n_active,
-                       partials, (int)ring, apart, anparts, nt);
+                       partials, (int)ring, apart, anparts, (int)quad, nt);
   else
     hipLaunchKernelGGL(k_update<double2>, grid, dim3(256), 0, s, (const double2*)T,
                        (const double2*)S, (double2*)basis, basis_stride, (double2*)wbuf, N, N, co,
-                       it, rhs_map, n_active, partials, (int)ring, apart, anparts, nt);
+                       it, rhs_map, n_active, partials, (int)ring, apart, anparts, (int)quad, nt);
 }
 
 void launch_beta_tail(bool f32, const double* partials, int nparts, const CoefArrays& co, int* it,

@@ -58,6 +58,7 @@ struct Tuning {
   int g = 1;             // lanes sharing one site (each lane one source); 1 = source blocking
   int nt = 0;            // streaming (non-temporal) stores of the output
   int stage = 0;         // 1: the tile's input spinors staged in LDS (g = 1 only)
+  bool hops = false;     // one wave per hop (small untuned launches; the rest unused)
   bool tuned = false;
 };
 
@@ -154,6 +155,7 @@ void launch_pack_links(const double2* canon, void* links, bool f32, const Geomet
                        const int bc[4], hipStream_t s);
 
 // out = op in on fields of nrhs sources; g5in/g5out select gamma5 factors.
+// tn.hops: the form with one wave per hop.
 hipError_t launch_wilson(bool f32, const void* links, const void* in, void* out, int nrhs,
                          const Geometry& g, const Hop& hop, bool g5in, bool g5out,
                          const Tuning& tn, hipStream_t s);
@@ -174,7 +176,8 @@ struct DualArgs {
   const int* it;
   void* out_t;
   void* out_s;
-  double* partials;    // [slot][dual_num_wg][3]
+  double* partials;    // [slot][dual_num_wg][3], with pair 6 [slot][dual_num_wg][4][3];
+                       // null (pair 6 only): no sums
   const int* rhs_map;
   const int* n_active;
   int nrhs_slots;
@@ -186,14 +189,18 @@ struct DualArgs {
                        // 3: one operator per workgroup (k_dual_op); 4: the
                        // same with the tile's spinors staged in LDS; 5: one
                        // operator and source per workgroup marching along t
-                       // (k_dual_march; order 0 or 1)
-  int tile = 256;      // sites per tile of k_dual (pair 0): 256, or 64 for small
-                       // lattices (more workgroups); the other variants need 256;
-                       // partials are [slot][ceil(V / tile)][3]
+                       // (k_dual_march; order 0 or 1); 6: one wave per hop
+                       // (k_hops_dual), with the sums of each 64-site quarter
+                       // of a tile apart
 };
 hipError_t launch_dual(bool f32, const DualArgs& a, const Geometry& g, const Hop& hA,
                        const Hop& hAd, int rhs_block, hipStream_t s);
 int dual_num_wg(const Geometry& g);
+constexpr int kDualHops = 6;   // DualArgs::pair of the one-wave-per-hop form
+// Kernel configurations of launches of nsrc sources that none was set for.
+Tuning default_tuning(bool f32, const Geometry& g, int nsrc);
+Tuning default_dual_tuning(bool f32, const Geometry& g, int nsrc);
+int dual_pair_of(const Tuning& t);
 
 // Persistent two-sided Lanczos: nit full iterations (dual stencil of the
 // operator-per-workgroup form, alpha, update, beta with probe gather) in one

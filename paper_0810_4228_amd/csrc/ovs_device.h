@@ -197,6 +197,18 @@ struct TileMap {
 // lattices with Lt a multiple of 8; otherwise as order 0).
 TileMap make_tile_map(const Geometry& g, int wg, int nrb, int order);
 
+// First site of tile tq.
+__device__ __forceinline__ int tile_site(int tq, const TileMap& m) {
+  if (!m.planar) return tq * m.wg;
+  const int p = tq % m.ppt;
+  int r = tq / m.ppt;
+  const int tin = r % m.tchunk;
+  r /= m.tchunk;
+  const int z = r % m.lz;
+  const int tc = r / m.lz;
+  return p * m.wg + m.plane * (z + m.lz * (tc * m.tchunk + tin));
+}
+
 __device__ __forceinline__ bool map_tile(int bid, const TileMap& m, int& site0, int& rb, int& tile) {
   int tq;
   if (m.group > 0) {
@@ -217,17 +229,7 @@ __device__ __forceinline__ bool map_tile(int bid, const TileMap& m, int& site0, 
     tq = m.rb_slow ? q % m.ntiles : q / m.nrb;
   }
   tile = tq;
-  if (m.planar) {
-    const int p = tq % m.ppt;
-    int r = tq / m.ppt;
-    const int tin = r % m.tchunk;
-    r /= m.tchunk;
-    const int z = r % m.lz;
-    const int tc = r / m.lz;
-    site0 = p * m.wg + m.plane * (z + m.lz * (tc * m.tchunk + tin));
-  } else {
-    site0 = tq * m.wg;
-  }
+  site0 = tile_site(tq, m);
   return true;
 }
 

@@ -44,7 +44,7 @@ Hop make_hop(double m_w, double mu);
 void op_setup(const ovs_lattice_s* l, ovs_op op, Hop& h, bool& g5in, bool& g5out);
 size_t elem_bytes(const ovs_lattice_s* l);
 // Stencil configuration for nrhs sources (tuned, or the default).
-Tuning get_tuning(const ovs_lattice_s* l, int nrhs);
+Tuning get_tuning(const ovs_lattice_s* l, int nrhs, int launch = 0);
 // Grows the lattice's cached workspace to at least bytes.
 ovs_status ensure_ws(ovs_lattice_s* l, size_t bytes);
 // canonical complex128 <-> internal storage-precision fields

@@ -9,17 +9,26 @@
 
 namespace ovs {
 
+// Sum t of the dual stencil's tile p (of all slots): one value, or with `quad`
+// the four 64-site quarters of the one-wave-per-hop form added in order.
+__device__ __forceinline__ double tile_sum(const double* __restrict__ partials, long p, int t,
+                                           int quad) {
+  if (!quad) return partials[p * 3 + t];
+  const double* q = partials + p * 12 + t;
+  return ((q[0] + q[3]) + q[6]) + q[9];
+}
+
 // alpha_i = conj(sw_i) sv_i (W~^dag A V~),  |t|^2 = sv_i^2 |A V~|^2, from the
 // dual stencil's per-tile partials of source slot rhs_map[jj].
 __device__ __forceinline__ void alpha_body(int jj, int i, const double* __restrict__ partials,
-                                           int nparts, const CoefArrays& co,
+                                           int nparts, int quad, const CoefArrays& co,
                                            const int* __restrict__ rhs_map, int na) {
   __shared__ double lds[4 * 3];
   if (jj >= na) return;
   const int slot = rhs_map[jj];
   double v[3] = {0, 0, 0};
   for (int p = threadIdx.x; p < nparts; p += blockDim.x)
-    for (int t = 0; t < 3; ++t) v[t] += partials[((long)slot * nparts + p) * 3 + t];
+    for (int t = 0; t < 3; ++t) v[t] += tile_sum(partials, (long)slot * nparts + p, t, quad);
   block_sum<3>(v, lds);
   if (threadIdx.x == 0) {
     const double sv = co.sv[(long)slot * (co.kmax + 1) + i];
@@ -47,7 +56,7 @@ __device__ __forceinline__ void update_body(int bx, int by, int gx, int i,
                                             const CoefArrays& co, const int* __restrict__ rhs_map,
                                             int na, double* __restrict__ partials,
                                             int two_pass_ring, const double* __restrict__ apart,
-                                            int anparts, int nt) {
+                                            int anparts, int quad, int nt) {
   __shared__ double lds[4 * 4];
   __shared__ double abc[2];
   const int jj = by;
@@ -60,7 +69,7 @@ __device__ __forceinline__ void update_body(int bx, int by, int gx, int i,
   if (apart) {
     double av[3] = {0, 0, 0};
     for (int p = threadIdx.x; p < anparts; p += blockDim.x)
-      for (int t = 0; t < 3; ++t) av[t] += apart[((long)slot * anparts + p) * 3 + t];
+      for (int t = 0; t < 3; ++t) av[t] += tile_sum(apart, (long)slot * anparts + p, t, quad);
     block_sum<3>(av, lds);
     if (threadIdx.x == 0) {
       const Cx<double> aa = scale(svi, cmulc(swi, Cx<double>{av[0], av[1]}));

@@ -120,7 +120,7 @@ k_persistent_2sl(const typename Vec2<R>::T* __restrict__ links, typename Vec2<R>
     for (int v = blockIdx.x; v < nwg_u * nslots; v += gridDim.x) {
       __syncthreads();
       update_body<T2>(v % nwg_u, v / nwg_u, nwg_u, i, T, S, basis, basis_stride, wbuf, N, N, co,
-                      rhs_map, na, part2, ring, part1, nwg_d, nt_update);
+                      rhs_map, na, part2, ring, part1, nwg_d, 0, nt_update);
     }
     grid_barrier(bar, per_group);
   }

@@ -15,6 +15,7 @@
 #include "ovs_common.h"
 #include "ovs_device.h"
 #include "ovs_dual.h"
+#include "ovs_hops.h"
 #include "ovs_spin.h"
 
 namespace ovs {
@@ -321,6 +322,27 @@ k_wilson_g(const typename Vec2<R>::T* __restrict__ links, const typename Vec2<R>
   store_spinor(outr, Vs, s, nt, psi);
 }
 
+// One wave per hop (ovs_hops.h): 64 sites of one source per workgroup,
+// blockIdx.y the source.  Workgroups go round robin over the 8 XCDs: each XCD
+// takes a contiguous range of the lattice, so that most neighbours of its sites
+// are in its own L2.
+__device__ __forceinline__ int xcd_chunk(int local, int xcd, int n) {
+  return xcd * ((n + 7) / 8) + local;
+}
+template <typename R>
+__global__ void __launch_bounds__(512)
+k_hops(const typename Vec2<R>::T* __restrict__ links, const typename Vec2<R>::T* __restrict__ in,
+       typename Vec2<R>::T* __restrict__ out, Geometry g, HopR<R> hc, int g5in, int g5out) {
+  using T2 = typename Vec2<R>::T;
+  const long base = (long)blockIdx.y * 12 * g.Vs;
+  const int ntile = (g.V + 63) / 64;
+  const int tile = xcd_chunk(blockIdx.x >> 3, blockIdx.x & 7, ntile);
+  if (tile >= ntile) return;  // uniform over the workgroup
+  hops_body<R, false, false>(links, HopField<R, false>{const_cast<T2*>(in) + base},
+                             HopField<R, false>{out + base}, g, hc, tile * 64, g5in, g5out,
+                             nullptr, nullptr);
+}
+
 // Dynamic LDS requests above the default per-workgroup limit need a
 // per-kernel opt-in; the limit is set once per process from the device query.
 static std::atomic<int> g_lds_limit_kb{64};
@@ -421,6 +443,18 @@ hipError_t launch_wilson(bool f32, const void* links, const void* in, void* out,
                          const Tuning& tn, hipStream_t s) {
   const int wg = tn.wg;
   hipError_t e = hipSuccess;
+  if (tn.hops) {
+    const dim3 grid(8 * (((g.V + 63) / 64 + 7) / 8), nrhs);
+    if (f32)
+      hipLaunchKernelGGL(k_hops<float>, grid, dim3(512), 0, s, (const float2*)links,
+                         (const float2*)in, (float2*)out, g, HopR<float>::make(hop_c), (int)g5in,
+                         (int)g5out);
+    else
+      hipLaunchKernelGGL(k_hops<double>, grid, dim3(512), 0, s, (const double2*)links,
+                         (const double2*)in, (double2*)out, g, HopR<double>::make(hop_c),
+                         (int)g5in, (int)g5out);
+    return hipGetLastError();
+  }
   if (tn.g > 1) {
 #define OVS_WG(RT, GG) e = launch_wg<RT, GG>(links, in, out, nrhs, g, hop_c, g5in, g5out, wg, tn.lds_kb, tn.order, tn.nt, s)
     if (f32) {
@@ -908,14 +942,102 @@ k_dual_march(const typename Vec2<R>::T* __restrict__ links,
   }
 }
 
+// The dual stencil with one wave per hop: blockIdx.x an operator and a 64-site
+// quarter of a tile (tiles and their order as in the other forms; the two
+// operators of a quarter on one XCD, which reads their links once), blockIdx.y
+// the active source.  The A workgroups write the sums of their quarter; the
+// four quarters of a tile added in order are the tile's sum of the other forms,
+// bit for bit.
+template <typename R>
+__global__ void __launch_bounds__(512)
+k_hops_dual(const typename Vec2<R>::T* __restrict__ links,
+            const typename Vec2<R>::T* __restrict__ basis,
+            const typename Vec2<R>::T* __restrict__ wbuf, long basis_stride, int ring,
+            const int* __restrict__ it, typename Vec2<R>::T* __restrict__ out_t,
+            typename Vec2<R>::T* __restrict__ out_s, double* __restrict__ partials, Geometry g,
+            HopR<R> hA, HopR<R> hAd, const int* __restrict__ rhs_map,
+            const int* __restrict__ n_active, TileMap tm) {
+  using T2 = typename Vec2<R>::T;
+  if ((int)blockIdx.y >= *n_active) return;  // uniform over the workgroup
+  const int iter = *it;
+  const int slot = rhs_map[blockIdx.y];
+  const long base = (long)slot * 12 * g.Vs;
+  const T2* in_v = basis + (long)(ring ? iter % 3 : iter) * basis_stride + base;
+  const T2* in_w = wbuf + (long)(iter % 3) * basis_stride + base;
+  const int local = blockIdx.x >> 3;
+  const bool dag = local & 1;
+  const int quarter = xcd_chunk(local >> 1, blockIdx.x & 7, 4 * tm.ntiles);
+  if (quarter >= 4 * tm.ntiles) return;  // uniform over the workgroup
+  const int site0 = tile_site(quarter >> 2, tm) + 64 * (quarter & 3);
+  double* part =
+      partials && !dag ? partials + ((long)slot * tm.ntiles * 4 + quarter) * 3 : nullptr;
+  hops_body<R, false, true>(links, HopField<R, false>{const_cast<T2*>(dag ? in_w : in_v)},
+                            HopField<R, false>{(dag ? out_s : out_t) + base}, g, dag ? hAd : hA,
+                            site0, false, true, in_w, part);
+}
+
+// Configurations of launches that none was set for, by the number of sites
+// times sources of the launch (n).  All forms give the same bits; measured on
+// 4^4 to 16^3 x 32, 1 to 24 sources, in us a launch.
+//
+// One operator.  n <= 100000: one wave per hop (FP64 8^4 x 1 3.9 against 6.3 with
+// one thread per site, 12^4 x 4 16.7 against 17.7; FP32 8^4 x 12 5.1 against 6.7,
+// 16^4 x 1 7.2 against 8.6; FP64 16^4 x 4, n = 262144, 54 against 42).  Above:
+// one thread per site with the tile staged in LDS (FP64 16^4 x 12 123 against 146
+// unstaged, FP32 52 against 56; several sources per thread are slower at every
+// size: FP32 16^4 x 12 with four 107).
+Tuning default_tuning(bool f32, const Geometry& g, int nsrc) {
+  (void)f32;
+  Tuning t;
+  t.hops = (long)g.V * nsrc <= 100000;
+  t.wg = t.hops ? 64 : 256;
+  t.stage = t.hops ? 0 : 1;
+  return t;
+}
+
+// The operator pair.  One wave per hop up to n = 140000 in FP64 (8^4 x 1 5.1
+// against 9.8 for the best of the others, 16^4 x 1 25 against 29, 16^4 x 2 47
+// against 49; 12^4 x 12, n = 248832, 88 against 82) and 36000 in FP32 (8^4 x 1 4.5
+// against 8.0, 12^4 x 1 6.6 against 8.4; 8^4 x 12, n = 49152, 11.4 against 10.6).
+// Above: one operator per workgroup with the tile staged, streaming stores
+// (FP64 16^4 x 12 251 against 286 with both operators per thread, FP32 16^4 x 4
+// 40 against 50); FP32 from n = 400000: both operators per thread, three
+// workgroups per CU (16^3 x 32 x 6 98 against 107 and 129 without the cap).
+// The update's streaming stores pay once a batch's vectors pass through the
+// caches unread (16^3 x 32 FP32: from 3 sources on).
+Tuning default_dual_tuning(bool f32, const Geometry& g, int nsrc) {
+  const long n = (long)g.V * nsrc;
+  Tuning t;
+  t.hops = n <= (f32 ? 36000 : 140000);
+  if (!t.hops) {
+    const bool both = f32 && n >= 400000;
+    t.g = both ? 1 : 5;
+    t.lds_kb = both && g_lds_limit_kb > 53 ? 53 : 0;
+    t.nt = 1;
+  }
+  if (n * (f32 ? 8 : 16) >= 3000000) t.nt |= 2;
+  return t;
+}
+
+// DualArgs::pair of a dual-stencil configuration.
+int dual_pair_of(const Tuning& t) { return t.hops ? kDualHops : t.g - 1; }
+
 int dual_num_wg(const Geometry& g) { return (g.V + 255) / 256; }
 
 template <typename R, int B>
 static hipError_t launch_d(const DualArgs& a, const Geometry& g, const Hop& hA, const Hop& hAd,
                      hipStream_t s) {
   using T2 = typename Vec2<R>::T;
-  if (a.tile != 256 && (a.tile != 64 || a.pair != 0)) return hipErrorInvalidValue;
-  const TileMap tm = make_tile_map(g, a.tile, (a.nrhs_slots + B - 1) / B, a.order);
+  if (a.pair == kDualHops) {
+    const TileMap th = make_tile_map(g, 256, 1, 0);
+    hipLaunchKernelGGL(k_hops_dual<R>, dim3(16 * ((4 * th.ntiles + 7) / 8), a.nrhs_slots),
+                       dim3(512), 0, s,
+                       (const T2*)a.links, (const T2*)a.basis, (const T2*)a.wbuf, a.basis_stride,
+                       (int)a.ring, a.it, (T2*)a.out_t, (T2*)a.out_s, a.partials, g,
+                       HopR<R>::make(hA), HopR<R>::make(hAd), a.rhs_map, a.n_active, th);
+    return hipSuccess;
+  }
+  const TileMap tm = make_tile_map(g, 256, (a.nrhs_slots + B - 1) / B, a.order);
   // the staged planes take 2 B 12 256 complex values of LDS: one or two sources
   constexpr bool kStage = 2 * B * 12 * 256 * sizeof(T2) <= 100 * 1024;
   // the operator-per-workgroup variant stages one field: B 12 256 values
@@ -986,7 +1108,7 @@ static hipError_t launch_d(const DualArgs& a, const Geometry& g, const Hop& hA, 
                        (T2*)a.out_s, a.partials, g, HopR<R>::make(hA), HopR<R>::make(hAd),
                        a.rhs_map, a.n_active, a.nt, tm);
   else
-    hipLaunchKernelGGL((k_dual<R, B>), dim3(8 * tm.per_xcd), dim3(a.tile), a.lds_kb * 1024, s,
+    hipLaunchKernelGGL((k_dual<R, B>), dim3(8 * tm.per_xcd), dim3(256), a.lds_kb * 1024, s,
                        (const T2*)a.links, (const T2*)a.basis, (const T2*)a.wbuf, a.basis_stride,
                        (int)a.ring, a.it, (T2*)a.out_t, (T2*)a.out_s, a.partials, g,
                        HopR<R>::make(hA), HopR<R>::make(hAd), a.rhs_map, a.n_active, a.nt, tm);

@@ -40,3 +40,37 @@ def test_inner_sign_tridiag_block_edges(kind, k):
     say(f"inner sign {kind} k={k}: {e:.2e}, estimate {err[0]:.1e}, status {st}")
     assert st == 0
     assert e <= 6e-7
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (3, 2, 5, 4), (4, 4, 4, 4), (5, 3, 7, 3),
+                                  (16, 16, 2, 8), (12, 10, 9, 8)])
+@pytest.mark.parametrize("nrhs", [1, 3])
+def test_one_wave_per_hop_equals_thread_per_site(prec, dims, nrhs):
+    """Launches without a set configuration and few sites run one wave per hop;
+    the same calls with the one-thread-per-site forms set give the same bits:
+    all four operators, and a fixed-k two-sided Lanczos solve (its alpha sums
+    the quarters of each 256-site tile, its coefficients follow).  Sizes below,
+    at and beyond the 64-site workgroups and 256-site tiles, with remainders,
+    and planar tiles (Lx Ly = 256); (12, 10, 9, 8) x 3 exceeds the FP32 limit of
+    the operator pair, which then differs from the single operator's form."""
+    import torch
+    import paper_0810_4228_amd as ovs
+    from gpu_util import to_dev
+    U = to_dev(synth.random_links(dims, 0.5, seed=41))
+    b = to_dev(synth.gaussian_sources(dims, nrhs, seed=42))
+    k = min(30, 6 * int(np.prod(dims)))
+    out = []
+    for cfg in (None, [110, 256, 0, 0, 110, 256, 0, 0]):
+        lat = ovs.Lattice(dims, precision=prec)
+        lat.set_links(U)
+        lat.set_params(MW, 0.3)
+        if cfg:
+            lat.set_tuning_raw(nrhs, cfg)
+        res = [lat.apply(op, b).cpu() for op in ("Dw", "Dw_dag", "A", "A_dag")]
+        res.append(lat.sign_apply(b, k)[0].cpu())
+        res += [torch.from_numpy(c) for c in lat.last_coefficients(nrhs, k)]
+        out.append(res)
+        lat.close()
+    for x, y in zip(*out):
+        assert torch.equal(x, y)
