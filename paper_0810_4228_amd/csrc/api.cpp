@@ -1433,21 +1433,33 @@ static ovs_status sign_apply_impl(ovs_lattice l, ovs_deflation defl, int32_t n_d
     const bool quad = dt.hops;
     DualArgs da{l->links, B.basis, B.wbuf, bstride, two_pass, B.ints, B.T, B.S, B.part1,
                 B.rhs_map, B.ints + 1, nr, dt.lds_kb, dt.order, dt.nt & 1, dual_pair_of(dt)};
-    // one full iteration is three launches: dual stencil; update (forming
-    // alpha); beta with the probe gather and the iteration advance.  The last
-    // iteration only forms alpha.
-    auto enqueue_iter = [&](bool full) -> ovs_status {
+    da.beta.partials = B.part2;
+    da.beta.nparts = nwg_u;
+    da.beta.co = co;
+    da.beta.N = N;
+    da.beta.idx = B.pidx;
+    da.beta.P = P;
+    da.beta.probes = probing ? B.probes : nullptr;
+    // one full iteration is two launches: the dual stencil, with the beta step of
+    // the iteration before (and its probe gather) beside it; the update, which
+    // forms alpha.  The iteration index advances once per run of iterations
+    // (enqueue_tail, with the last beta step); c: position in the run.  The last
+    // iteration of a solve only forms alpha.
+    auto enqueue_iter = [&](int c, bool full) -> ovs_status {
+      da.off = c;
+      da.beta.on = c > 0;
       OVS_HIP(launch_dual(f32, da, l->g, hA, hAd, dual_b, s));
-      if (full) {
-        launch_update(f32, B.T, B.S, B.basis, bstride, B.wbuf, N, co, B.ints, B.rhs_map,
+      if (full)
+        launch_update(f32, B.T, B.S, B.basis, bstride, B.wbuf, N, co, B.ints, c, B.rhs_map,
                       B.ints + 1, nr, B.part2, two_pass, B.part1, nwg_d, quad, (dt.nt >> 1) & 1, s);
-        launch_beta_tail(f32, B.part2, nwg_u, co, B.ints, B.rhs_map, B.ints + 1, nr, B.ints + 2,
-                         B.basis, bstride, N, two_pass, B.pidx, P, probing ? B.probes : nullptr,
-                         s);
-      } else {
-        launch_alpha(B.part1, nwg_d, quad, co, B.ints, B.rhs_map, B.ints + 1, nr, s);
-        launch_advance(B.ints, s);
-      }
+      else
+        launch_alpha(B.part1, nwg_d, quad, co, B.ints, c, B.rhs_map, B.ints + 1, nr, s);
+      OVS_HIP(hipGetLastError());
+      return OVS_OK;
+    };
+    auto enqueue_tail = [&](int n) -> ovs_status {
+      launch_beta_tail(f32, B.part2, nwg_u, co, B.ints, n, B.rhs_map, B.ints + 1, nr, B.ints + 2,
+                       B.basis, bstride, N, two_pass, B.pidx, P, probing ? B.probes : nullptr, s);
       OVS_HIP(hipGetLastError());
       return OVS_OK;
     };
@@ -1496,10 +1508,8 @@ static ovs_status sign_apply_impl(ovs_lattice l, ovs_deflation defl, int32_t n_d
         if (!gexec) {
           std::lock_guard<std::mutex> lock(g_capture_mu);  // see ensure_ws
           OVS_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-          for (int c = 0; c < chunk; ++c) {
-            st = enqueue_iter(true);
-            if (st != OVS_OK) break;
-          }
+          for (int c = 0; c < chunk && st == OVS_OK; ++c) st = enqueue_iter(c, true);
+          if (st == OVS_OK) st = enqueue_tail(chunk);
           hipError_t ce = hipStreamEndCapture(s, &graph);
           if (st != OVS_OK) return st;
           OVS_HIP(ce);
@@ -1510,12 +1520,17 @@ static ovs_status sign_apply_impl(ovs_lattice l, ovs_deflation defl, int32_t n_d
           done_it += chunk;
         }
       }
-      for (; done_it < nfull; ++done_it) {
-        st = enqueue_iter(true);
+      if (done_it < nfull) {
+        const int n = nfull - done_it;
+        for (int c = 0; c < n; ++c) {
+          st = enqueue_iter(c, true);
+          if (st != OVS_OK) return st;
+        }
+        st = enqueue_tail(n);
         if (st != OVS_OK) return st;
       }
       if (iend == K) {
-        st = enqueue_iter(false);
+        st = enqueue_iter(0, false);
         if (st != OVS_OK) return st;
       }
       i = iend;

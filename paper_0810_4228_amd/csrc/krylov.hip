@@ -171,47 +171,50 @@ __global__ void k_start_vectors(const double2* __restrict__ bR, const double2* _
 
 __global__ void __launch_bounds__(256) k_alpha(const double* __restrict__ partials, int nparts,
                                                int quad, CoefArrays co, const int* __restrict__ it,
+                                               int off,
                                                const int* __restrict__ rhs_map,
                                                const int* __restrict__ n_active) {
-  alpha_body(blockIdx.x, *it, partials, nparts, quad, co, rhs_map, *n_active);
+  alpha_body(blockIdx.x, *it + off, partials, nparts, quad, co, rhs_map, *n_active);
 }
 
 template <typename T2>
 __global__ void __launch_bounds__(256) k_update(const T2* __restrict__ T, const T2* __restrict__ S,
                                                 T2* __restrict__ basis, long basis_stride,
                                                 T2* __restrict__ wbuf, long slot_stride, long N,
-                                                CoefArrays co, const int* __restrict__ it,
+                                                CoefArrays co, const int* __restrict__ it, int off,
                                                 const int* __restrict__ rhs_map,
                                                 const int* __restrict__ n_active,
                                                 double* __restrict__ partials, int two_pass_ring,
                                                 const double* __restrict__ apart, int anparts,
                                                 int quad, int nt) {
-  update_body<T2>(blockIdx.x, blockIdx.y, gridDim.x, *it, T, S, basis, basis_stride, wbuf,
+  update_body<T2>(blockIdx.x, blockIdx.y, gridDim.x, *it + off, T, S, basis, basis_stride, wbuf,
                   slot_stride, N, co, rhs_map, *n_active, partials, two_pass_ring, apart, anparts,
                   quad, nt);
 }
 
-// beta_body for one source slot per workgroup, then the iteration advance:
-// the last workgroup to finish (a ticket counter, reset by that workgroup, so
-// it is zero between launches) increments *it, after every workgroup has read it.
+// beta_body of iteration *it + adv - 1 for one source slot per workgroup, then
+// the iteration index advances by adv: the last workgroup to finish (a ticket
+// counter, reset by that workgroup, so it is zero between launches) adds it,
+// after every workgroup has read *it.  Ends a run of adv iterations; the beta
+// steps before run beside the next iteration's dual stencil (BetaArgs).
 template <typename T2>
 __global__ void __launch_bounds__(256) k_beta_tail(const double* __restrict__ partials, int nparts,
-                                                   CoefArrays co, int* __restrict__ it,
+                                                   CoefArrays co, int* __restrict__ it, int adv,
                                                    const int* __restrict__ rhs_map,
                                                    const int* __restrict__ n_active,
                                                    int* __restrict__ ticket,
                                                    const T2* __restrict__ basis, long basis_stride,
                                                    long N, int ring, const int* __restrict__ idx,
                                                    int P, double2* __restrict__ probes) {
-  const int i = *it;
-  beta_body<T2>(blockIdx.x, i, partials, nparts, co, rhs_map, *n_active, basis, basis_stride, N,
+  const int base = *it;
+  beta_body<T2>(blockIdx.x, base + adv - 1, partials, nparts, co, rhs_map, *n_active, basis, basis_stride, N,
                 ring, idx, P, probes);
   __syncthreads();
   if (threadIdx.x == 0) {
     __threadfence();
     if (atomicAdd(ticket, 1) == (int)gridDim.x - 1) {
       *ticket = 0;
-      *it = i + 1;
+      *it = base + adv;
     }
   }
 }
@@ -930,37 +933,37 @@ void launch_start(const double2* bR, const double2* bL, int nrhs, long N, double
 int update_nwg(long N) { return chunks_for(N, 256); }
 
 void launch_alpha(const double* partials, int nparts, bool quad, const CoefArrays& co, const int* it,
-                  const int* rhs_map, const int* n_active, int nslots, hipStream_t s) {
+                  int off, const int* rhs_map, const int* n_active, int nslots, hipStream_t s) {
   hipLaunchKernelGGL(k_alpha, dim3(nslots), dim3(256), 0, s, partials, nparts, (int)quad, co, it,
-                     rhs_map, n_active);
+                     off, rhs_map, n_active);
 }
 
 void launch_update(bool f32, const void* T, const void* S, void* basis, long basis_stride,
-                   void* wbuf, long N, const CoefArrays& co, const int* it, const int* rhs_map,
-                   const int* n_active, int nslots, double* partials, bool ring,
+                   void* wbuf, long N, const CoefArrays& co, const int* it, int off,
+                   const int* rhs_map, const int* n_active, int nslots, double* partials, bool ring,
                    const double* apart, int anparts, bool quad, int nt, hipStream_t s) {
   dim3 grid(update_nwg(N), nslots);
   if (f32)
     hipLaunchKernelGGL(k_update<float2>, grid, dim3(256), 0, s, (const float2*)T, (const float2*)S,
-                       (float2*)basis, basis_stride, (float2*)wbuf, N, N, co, it, rhs_map, n_active,
+                       (float2*)basis, basis_stride, (float2*)wbuf, N, N, co, it, off, rhs_map, n_active,
                        partials, (int)ring, apart, anparts, (int)quad, nt);
   else
     hipLaunchKernelGGL(k_update<double2>, grid, dim3(256), 0, s, (const double2*)T,
                        (const double2*)S, (double2*)basis, basis_stride, (double2*)wbuf, N, N, co,
-                       it, rhs_map, n_active, partials, (int)ring, apart, anparts, (int)quad, nt);
+                       it, off, rhs_map, n_active, partials, (int)ring, apart, anparts, (int)quad, nt);
 }
 
 void launch_beta_tail(bool f32, const double* partials, int nparts, const CoefArrays& co, int* it,
-                      const int* rhs_map, const int* n_active, int nslots, int* ticket,
+                      int adv, const int* rhs_map, const int* n_active, int nslots, int* ticket,
                       const void* basis, long basis_stride, long N, bool ring, const int* idx,
                       int P, double2* probes, hipStream_t s) {
   if (f32)
     hipLaunchKernelGGL(k_beta_tail<float2>, dim3(nslots), dim3(256), 0, s, partials, nparts, co, it,
-                       rhs_map, n_active, ticket, (const float2*)basis, basis_stride, N, (int)ring,
+                       adv, rhs_map, n_active, ticket, (const float2*)basis, basis_stride, N, (int)ring,
                        idx, P, probes);
   else
     hipLaunchKernelGGL(k_beta_tail<double2>, dim3(nslots), dim3(256), 0, s, partials, nparts, co, it,
-                       rhs_map, n_active, ticket, (const double2*)basis, basis_stride, N, (int)ring,
+                       adv, rhs_map, n_active, ticket, (const double2*)basis, basis_stride, N, (int)ring,
                        idx, P, probes);
 }
 

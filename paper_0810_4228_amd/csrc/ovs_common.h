@@ -162,7 +162,21 @@ hipError_t launch_wilson(bool f32, const void* links, const void* in, void* out,
 // Lets kernels request dynamic LDS above the default per-workgroup limit.
 void set_lds_limit(int kb);
 
-// Dual stencil of the two-sided Lanczos step: for iteration i = *it,
+// The beta step (with the probe gather) of the iteration before the dual
+// stencil's, run by workgroups of the same launch ahead of the stencil's: nothing
+// in the stencil reads its results, and the next update does.
+struct BetaArgs {
+  int on = 0;
+  const double* partials = nullptr;   // the update's
+  int nparts = 0;
+  CoefArrays co{};
+  long N = 0;                         // field length of one source
+  const int* idx = nullptr;
+  int P = 0;
+  double2* probes = nullptr;
+};
+
+// Dual stencil of the two-sided Lanczos step: for iteration i = *it + off,
 //   T = A V~_i, S = A^dagger W~_i (A = gamma5 Dw(mu)), plus per-workgroup
 //   partials of W~_i^dagger T (complex) and |T|^2 per source slot.
 // V~_i = basis[ring ? i%3 : i], W~_i = wbuf[i%3]; each holds nrhs_slots
@@ -192,6 +206,8 @@ struct DualArgs {
                        // (k_dual_march; order 0 or 1); 6: one wave per hop
                        // (k_hops_dual), with the sums of each 64-site quarter
                        // of a tile apart
+  int off = 0;
+  BetaArgs beta{};
 };
 hipError_t launch_dual(bool f32, const DualArgs& a, const Geometry& g, const Hop& hA,
                        const Hop& hAd, int rhs_block, hipStream_t s);

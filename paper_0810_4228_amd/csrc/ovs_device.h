@@ -241,14 +241,14 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
-// Sums `n` values per thread over the workgroup; result valid in thread 0.
-// lds must hold blockDim.x/64 * n doubles.
+// Sums `n` values per thread over the first nw waves of the workgroup (all its
+// threads call it); result valid in thread 0.  lds must hold nw * n doubles.
 template <int NV>
-__device__ __forceinline__ void block_sum(double (&v)[NV], double* lds) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+__device__ __forceinline__ void block_sum(double (&v)[NV], double* lds, int nw) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
   for (int j = 0; j < NV; ++j) v[j] = wave_sum(v[j]);
-  if (lane == 0) {
+  if (lane == 0 && wave < nw) {
 #pragma unroll
     for (int j = 0; j < NV; ++j) lds[wave * NV + j] = v[j];
   }
@@ -263,5 +263,28 @@ __device__ __forceinline__ void block_sum(double (&v)[NV], double* lds) {
   }
   __syncthreads();
 }
+template <int NV>
+__device__ __forceinline__ void block_sum(double (&v)[NV], double* lds) {
+  block_sum<NV>(v, lds, blockDim.x >> 6);
+}
+
+// Two adjacent stored values as they come from memory, for loads issued ahead of
+// their use (a conversion at the load would wait for it).
+template <typename T2> struct RawPair;
+template <> struct RawPair<float2> {
+  float4 v;
+  __device__ void load(const float2* p) { v = *reinterpret_cast<const float4*>(p); }
+  __device__ Cx<double> first() const { return {(double)v.x, (double)v.y}; }
+  __device__ Cx<double> second() const { return {(double)v.z, (double)v.w}; }
+};
+template <> struct RawPair<double2> {
+  double2 a, b;
+  __device__ void load(const double2* p) {
+    a = p[0];
+    b = p[1];
+  }
+  __device__ Cx<double> first() const { return {a.x, a.y}; }
+  __device__ Cx<double> second() const { return {b.x, b.y}; }
+};
 
 }  // namespace ovs

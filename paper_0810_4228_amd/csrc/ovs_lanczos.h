@@ -63,8 +63,46 @@ __device__ __forceinline__ void update_body(int bx, int by, int gx, int i,
   if (jj >= na) return;
   const int slot = rhs_map[jj];
   const long ks = co.kmax;
+  const bool prev = i > 0;
+  // basis slots: ring of 3 in two-pass mode, else the full basis
+  const long vi = two_pass_ring ? (i % 3) : i;
+  const long vm = two_pass_ring ? ((i + 2) % 3) : (i - 1);
+  const long vn = two_pass_ring ? ((i + 1) % 3) : (i + 1);
+  const T2* Vi = basis + vi * basis_stride + slot * slot_stride;
+  const T2* Vm = basis + (prev ? vm : vi) * basis_stride + slot * slot_stride;
+  T2* Vn = basis + vn * basis_stride + slot * slot_stride;
+  const T2* Wi = wbuf + (long)(i % 3) * basis_stride + slot * slot_stride;
+  const T2* Wm = wbuf + (long)((i + 2) % 3) * basis_stride + slot * slot_stride;
+  T2* Wn = wbuf + (long)((i + 1) % 3) * basis_stride + slot * slot_stride;
+  const T2* Ts = T + slot * slot_stride;
+  const T2* Ss = S + slot * slot_stride;
+  // two adjacent complex elements per thread (one 16-byte access per vector in
+  // FP32); N is even (12 Vs).  The loads of an element pair are issued one
+  // iteration ahead, the first before alpha is formed: one load after the other
+  // would be a chain of memory latencies on the small lattices.
+  struct Elem {
+    RawPair<T2> t, v, s, w, vm, wm;
+  };
+  Elem nxt;
+  auto fetch = [&](long e) {
+    nxt.t.load(Ts + e);
+    nxt.v.load(Vi + e);
+    nxt.s.load(Ss + e);
+    nxt.w.load(Wi + e);
+    if (prev) {
+      nxt.vm.load(Vm + e);
+      nxt.wm.load(Wm + e);
+    }
+  };
+  const long step = 2 * (long)gx * blockDim.x;
+  long e = 2 * (bx * (long)blockDim.x + threadIdx.x);
+  if (e < N) fetch(e);
   const double svi = co.sv[slot * (ks + 1) + i];
   const Cx<double> swi = c64(co.sw[slot * (ks + 1) + i]);
+  const double svm = prev ? co.sv[slot * (ks + 1) + i - 1] : 0.0;
+  const Cx<double> swm = prev ? c64(co.sw[slot * (ks + 1) + i - 1]) : Cx<double>{0, 0};
+  const Cx<double> gm = prev ? c64(co.gamma[slot * ks + i - 1]) : Cx<double>{0, 0};
+  const double bm = prev ? co.beta[slot * ks + i - 1] : 0.0;
   Cx<double> a;
   if (apart) {
     double av[3] = {0, 0, 0};
@@ -85,53 +123,26 @@ __device__ __forceinline__ void update_body(int bx, int by, int gx, int i,
   } else {
     a = c64(co.alpha[slot * ks + i]);
   }
-  const bool prev = i > 0;
-  const double svm = prev ? co.sv[slot * (ks + 1) + i - 1] : 0.0;
-  const Cx<double> swm = prev ? c64(co.sw[slot * (ks + 1) + i - 1]) : Cx<double>{0, 0};
-  const Cx<double> gm = prev ? c64(co.gamma[slot * ks + i - 1]) : Cx<double>{0, 0};
-  const double bm = prev ? co.beta[slot * ks + i - 1] : 0.0;
   const Cx<double> c1 = {svi, 0.0};
   const Cx<double> c2 = scale(-svi, a);
   const Cx<double> c3 = scale(-svm, gm);
   const Cx<double> d1 = swi;
   const Cx<double> d2_ = -cmulc(a, swi);           // -conj(alpha) sw_i
   const Cx<double> d3 = scale(-bm, swm);           // -conj(beta) sw_{i-1}, beta real
-  // basis slots: ring of 3 in two-pass mode, else the full basis
-  const long vi = two_pass_ring ? (i % 3) : i;
-  const long vm = two_pass_ring ? ((i + 2) % 3) : (i - 1);
-  const long vn = two_pass_ring ? ((i + 1) % 3) : (i + 1);
-  const T2* Vi = basis + vi * basis_stride + slot * slot_stride;
-  const T2* Vm = basis + (prev ? vm : vi) * basis_stride + slot * slot_stride;
-  T2* Vn = basis + vn * basis_stride + slot * slot_stride;
-  const T2* Wi = wbuf + (long)(i % 3) * basis_stride + slot * slot_stride;
-  const T2* Wm = wbuf + (long)((i + 2) % 3) * basis_stride + slot * slot_stride;
-  T2* Wn = wbuf + (long)((i + 1) % 3) * basis_stride + slot * slot_stride;
-  const T2* Ts = T + slot * slot_stride;
-  const T2* Ss = S + slot * slot_stride;
   double v[4] = {0, 0, 0, 0};
-  // two adjacent complex elements per thread (one 16-byte access per vector in
-  // FP32); N is even (12 Vs)
-  for (long e = 2 * (bx * (long)blockDim.x + threadIdx.x); e < N;
-       e += 2 * (long)gx * blockDim.x) {
+  for (; e < N; e += step) {
+    const Elem c = nxt;
+    if (e + step < N) fetch(e + step);
     Cx<double> vt[2], wt[2];
-    {
-      Cx<double> x0, x1, y0, y1;
-      ld_pair64(Ts + e, x0, x1);
-      ld_pair64(Vi + e, y0, y1);
-      vt[0] = cfma(c2, y0, cmul(c1, x0));
-      vt[1] = cfma(c2, y1, cmul(c1, x1));
-      ld_pair64(Ss + e, x0, x1);
-      ld_pair64(Wi + e, y0, y1);
-      wt[0] = cfma(d2_, y0, cmul(d1, x0));
-      wt[1] = cfma(d2_, y1, cmul(d1, x1));
-      if (prev) {
-        ld_pair64(Vm + e, x0, x1);
-        ld_pair64(Wm + e, y0, y1);
-        vt[0] = cfma(c3, x0, vt[0]);
-        vt[1] = cfma(c3, x1, vt[1]);
-        wt[0] = cfma(d3, y0, wt[0]);
-        wt[1] = cfma(d3, y1, wt[1]);
-      }
+    vt[0] = cfma(c2, c.v.first(), cmul(c1, c.t.first()));
+    vt[1] = cfma(c2, c.v.second(), cmul(c1, c.t.second()));
+    wt[0] = cfma(d2_, c.w.first(), cmul(d1, c.s.first()));
+    wt[1] = cfma(d2_, c.w.second(), cmul(d1, c.s.second()));
+    if (prev) {
+      vt[0] = cfma(c3, c.vm.first(), vt[0]);
+      vt[1] = cfma(c3, c.vm.second(), vt[1]);
+      wt[0] = cfma(d3, c.wm.first(), wt[0]);
+      wt[1] = cfma(d3, c.wm.second(), wt[1]);
     }
     if (nt) {
       st_pair64_nt(Vn + e, vt[0], vt[1]);
@@ -160,6 +171,7 @@ __device__ __forceinline__ void update_body(int bx, int by, int gx, int i,
 // |delta| <= 1e-13 |v~| |w~| (no biorthogonal continuation); either stops the
 // source at k = i + 1 with zero coefficients from there on.  With probes !=
 // nullptr the entries idx[0..P) of the new V~_{i+1} are gathered as well.
+// The work of the first 256 threads; larger workgroups may call it (all threads).
 template <typename T2>
 __device__ __forceinline__ void beta_body(int jj, int i, const double* __restrict__ partials,
                                           int nparts, const CoefArrays& co,
@@ -170,15 +182,18 @@ __device__ __forceinline__ void beta_body(int jj, int i, const double* __restric
   __shared__ double lds[4 * 4];
   if (jj >= na) return;
   const int slot = rhs_map[jj];
+  const bool in = threadIdx.x < 256;
+  const double tnorm2 = co.tnorm2[slot * (long)co.kmax + i];  // ahead of the sums
   double v[4] = {0, 0, 0, 0};
-  for (int p = threadIdx.x; p < nparts; p += blockDim.x)
-    for (int t = 0; t < 4; ++t) v[t] += partials[((long)slot * nparts + p) * 4 + t];
-  block_sum<4>(v, lds);
+  if (in)
+    for (int p = threadIdx.x; p < nparts; p += 256)
+      for (int t = 0; t < 4; ++t) v[t] += partials[((long)slot * nparts + p) * 4 + t];
+  block_sum<4>(v, lds, 4);
   if (threadIdx.x == 0) {
     const long ks = co.kmax;
     const double bn = sqrt(v[2]), wn = sqrt(v[3]);
     const Cx<double> delta = {v[0], v[1]};
-    const double tn = sqrt(co.tnorm2[slot * ks + i]);
+    const double tn = sqrt(tnorm2);
     int st_ = co.status[slot];
     if (st_ == 0) {
       const bool forced = co.inject_plus1 == i + 1;
@@ -204,10 +219,10 @@ __device__ __forceinline__ void beta_body(int jj, int i, const double* __restric
     }
   }
   const int j = i + 1;
-  if (probes && j < co.kmax) {
+  if (probes && j < co.kmax && in) {
     const long sl = ring ? (j % 3) : j;
     const T2* vb = basis + sl * basis_stride + (long)slot * N;
-    for (int p = threadIdx.x; p < P; p += blockDim.x)
+    for (int p = threadIdx.x; p < P; p += 256)
       probes[((long)slot * co.kmax + j) * P + p] = d2(ld64(vb + idx[p]));
   }
 }

@@ -16,6 +16,7 @@
 #include "ovs_device.h"
 #include "ovs_dual.h"
 #include "ovs_hops.h"
+#include "ovs_lanczos.h"
 #include "ovs_spin.h"
 
 namespace ovs {
@@ -497,6 +498,22 @@ hipError_t launch_wilson(bool f32, const void* links, const void* in, void* out,
   return hipGetLastError();
 }
 
+// Workgroups ahead of a dual stencil's own for the beta steps of nslots sources:
+// a multiple of 8, so that the others keep their XCDs.
+static int beta_blocks(const DualArgs& a) { return a.beta.on ? 8 * ((a.nrhs_slots + 7) / 8) : 0; }
+
+// Whether workgroup b of a dual stencil's launch is one of those (it then does
+// source b's step of iteration iter - 1); uniform over the workgroup.
+template <typename T2>
+__device__ __forceinline__ bool beta_part(const BetaArgs& ba, int b, int nblocks, int iter,
+                                          const T2* basis, long basis_stride, int ring,
+                                          const int* rhs_map, int na) {
+  if (b >= nblocks) return false;
+  beta_body<T2>(b, iter - 1, ba.partials, ba.nparts, ba.co, rhs_map, na, basis, basis_stride, ba.N,
+                ring, ba.idx, ba.P, ba.probes);
+  return true;
+}
+
 // ---- dual stencil for the two-sided Lanczos step ---------------------------
 // For each active source slot r: T_r = A V~_r, S_r = A^dag W~_r, and per
 // workgroup the partial sums of W~_r^dagger T_r (complex) and |T_r|^2, in FP64.
@@ -508,13 +525,14 @@ k_dual(const typename Vec2<R>::T* __restrict__ links, const typename Vec2<R>::T*
        const int* __restrict__ it, typename Vec2<R>::T* __restrict__ out_t,
        typename Vec2<R>::T* __restrict__ out_s, double* __restrict__ partials, Geometry g,
        HopR<R> hA, HopR<R> hAd, const int* __restrict__ rhs_map, const int* __restrict__ n_active,
-       int nt, TileMap tm) {
+       int nt, TileMap tm, int off, BetaArgs ba, int nbeta) {
   using T2 = typename Vec2<R>::T;
   __shared__ double lds[(256 / 64) * 3 * B];
-  int site0, rb, tile;
-  if (!map_tile(blockIdx.x, tm, site0, rb, tile)) return;  // uniform over the workgroup
   const int na = *n_active;
-  const int iter = *it;
+  const int iter = *it + off;
+  if (beta_part<T2>(ba, blockIdx.x, nbeta, iter, basis, basis_stride, ring, rhs_map, na)) return;
+  int site0, rb, tile;
+  if (!map_tile(blockIdx.x - nbeta, tm, site0, rb, tile)) return;  // uniform over the workgroup
   const T2* in_v = basis + (long)(ring ? iter % 3 : iter) * basis_stride;
   const T2* in_w = wbuf + (long)(iter % 3) * basis_stride;
   const int j0 = rb * B;
@@ -631,14 +649,16 @@ k_dual_pair(const typename Vec2<R>::T* __restrict__ links,
             const int* __restrict__ it, typename Vec2<R>::T* __restrict__ out_t,
             typename Vec2<R>::T* __restrict__ out_s, double* __restrict__ partials, Geometry g,
             HopR<R> hA, HopR<R> hAd, const int* __restrict__ rhs_map,
-            const int* __restrict__ n_active, int nt, TileMap tm) {
+            const int* __restrict__ n_active, int nt, TileMap tm, int off, BetaArgs ba,
+            int nbeta) {
   using T2 = typename Vec2<R>::T;
   __shared__ double lds[(512 / 64) * 3 * B];
   __shared__ T2 plane[STAGE ? 2 * B * 12 * 256 : 1];  // [op][source][component][tile site]
-  int site0, rb, tile;
-  if (!map_tile(blockIdx.x, tm, site0, rb, tile)) return;  // uniform over the workgroup
   const int na = *n_active;
-  const int iter = *it;
+  const int iter = *it + off;
+  if (beta_part<T2>(ba, blockIdx.x, nbeta, iter, basis, basis_stride, ring, rhs_map, na)) return;
+  int site0, rb, tile;
+  if (!map_tile(blockIdx.x - nbeta, tm, site0, rb, tile)) return;  // uniform over the workgroup
   const T2* in_v = basis + (long)(ring ? iter % 3 : iter) * basis_stride;
   const T2* in_w = wbuf + (long)(iter % 3) * basis_stride;
   const int j0 = rb * B;
@@ -791,8 +811,12 @@ k_dual_op(const typename Vec2<R>::T* __restrict__ links,
           const int* __restrict__ it, typename Vec2<R>::T* __restrict__ out_t,
           typename Vec2<R>::T* __restrict__ out_s, double* __restrict__ partials, Geometry g,
           HopR<R> hA, HopR<R> hAd, const int* __restrict__ rhs_map,
-          const int* __restrict__ n_active, int nt, TileMap tm) {
-  dual_op_body<R, B, STAGE>(blockIdx.x, *it, links, basis, wbuf, basis_stride, ring, out_t, out_s,
+          const int* __restrict__ n_active, int nt, TileMap tm, int off, BetaArgs ba, int nbeta) {
+  const int iter = *it + off;
+  if (beta_part<typename Vec2<R>::T>(ba, blockIdx.x, nbeta, iter, basis, basis_stride, ring, rhs_map,
+                                     *n_active))
+    return;
+  dual_op_body<R, B, STAGE>(blockIdx.x - nbeta, iter, links, basis, wbuf, basis_stride, ring, out_t, out_s,
                             partials, g, hA, hAd, rhs_map, *n_active, nt, tm);
 }
 
@@ -818,12 +842,16 @@ k_dual_march(const typename Vec2<R>::T* __restrict__ links,
              const int* __restrict__ it, typename Vec2<R>::T* __restrict__ out_t,
              typename Vec2<R>::T* __restrict__ out_s, double* __restrict__ partials, Geometry g,
              HopR<R> hA, HopR<R> hAd, const int* __restrict__ rhs_map,
-             const int* __restrict__ n_active, int nslots, int nt, TileMap tm, int order) {
+             const int* __restrict__ n_active, int nslots, int nt, TileMap tm, int order, int off,
+             BetaArgs ba, int nbeta) {
   using T2 = typename Vec2<R>::T;
   __shared__ double lds[(256 / 64) * 3];
   __shared__ T2 plane[12 * 256];  // the tile's spinors at the current t: [component][site]
-  const int tc = blockIdx.x & 7;  // the XCD's time chunk
-  int local = blockIdx.x >> 3;
+  const int iter = *it + off;
+  if (beta_part<T2>(ba, blockIdx.x, nbeta, iter, basis, basis_stride, ring, rhs_map, *n_active))
+    return;
+  const int tc = blockIdx.x & 7;  // the XCD's time chunk (nbeta is a multiple of 8)
+  int local = ((int)blockIdx.x - nbeta) >> 3;
   const int op = local & 1;       // the A and A^dag workgroups of a column are adjacent
   local >>= 1;
   const int ncol = tm.ppt * tm.lz;
@@ -836,7 +864,6 @@ k_dual_march(const typename Vec2<R>::T* __restrict__ links,
     j = local - col * nslots;
   }
   if (col >= ncol || j >= *n_active) return;  // uniform over the workgroup
-  const int iter = *it;
   const T2* in_v = basis + (long)(ring ? iter % 3 : iter) * basis_stride;
   const T2* in_w = wbuf + (long)(iter % 3) * basis_stride;
   const int slot = rhs_map[j];
@@ -956,17 +983,27 @@ k_hops_dual(const typename Vec2<R>::T* __restrict__ links,
             const int* __restrict__ it, typename Vec2<R>::T* __restrict__ out_t,
             typename Vec2<R>::T* __restrict__ out_s, double* __restrict__ partials, Geometry g,
             HopR<R> hA, HopR<R> hAd, const int* __restrict__ rhs_map,
-            const int* __restrict__ n_active, TileMap tm) {
+            const int* __restrict__ n_active, TileMap tm, int off, BetaArgs ba) {
   using T2 = typename Vec2<R>::T;
-  if ((int)blockIdx.y >= *n_active) return;  // uniform over the workgroup
-  const int iter = *it;
+  const int na = *n_active;
+  if ((int)blockIdx.y >= na) return;  // uniform over the workgroup
+  const int iter = *it + off;
+  int bx = blockIdx.x;
+  if (ba.on) {  // the first workgroup of a source: its beta step (the next seven idle)
+    if (bx < 8) {
+      if (bx == 0)
+        beta_part<T2>(ba, blockIdx.y, gridDim.y, iter, basis, basis_stride, ring, rhs_map, na);
+      return;
+    }
+    bx -= 8;
+  }
   const int slot = rhs_map[blockIdx.y];
   const long base = (long)slot * 12 * g.Vs;
   const T2* in_v = basis + (long)(ring ? iter % 3 : iter) * basis_stride + base;
   const T2* in_w = wbuf + (long)(iter % 3) * basis_stride + base;
-  const int local = blockIdx.x >> 3;
+  const int local = bx >> 3;
   const bool dag = local & 1;
-  const int quarter = xcd_chunk(local >> 1, blockIdx.x & 7, 4 * tm.ntiles);
+  const int quarter = xcd_chunk(local >> 1, bx & 7, 4 * tm.ntiles);
   if (quarter >= 4 * tm.ntiles) return;  // uniform over the workgroup
   const int site0 = tile_site(quarter >> 2, tm) + 64 * (quarter & 3);
   double* part =
@@ -1030,14 +1067,15 @@ static hipError_t launch_d(const DualArgs& a, const Geometry& g, const Hop& hA, 
   using T2 = typename Vec2<R>::T;
   if (a.pair == kDualHops) {
     const TileMap th = make_tile_map(g, 256, 1, 0);
-    hipLaunchKernelGGL(k_hops_dual<R>, dim3(16 * ((4 * th.ntiles + 7) / 8), a.nrhs_slots),
-                       dim3(512), 0, s,
+    hipLaunchKernelGGL(k_hops_dual<R>, dim3(16 * ((4 * th.ntiles + 7) / 8) + (a.beta.on ? 8 : 0), a.nrhs_slots), dim3(512), 0,
+                       s,
                        (const T2*)a.links, (const T2*)a.basis, (const T2*)a.wbuf, a.basis_stride,
                        (int)a.ring, a.it, (T2*)a.out_t, (T2*)a.out_s, a.partials, g,
-                       HopR<R>::make(hA), HopR<R>::make(hAd), a.rhs_map, a.n_active, th);
+                       HopR<R>::make(hA), HopR<R>::make(hAd), a.rhs_map, a.n_active, th, a.off, a.beta);
     return hipSuccess;
   }
   const TileMap tm = make_tile_map(g, 256, (a.nrhs_slots + B - 1) / B, a.order);
+  const int nbeta = beta_blocks(a);
   // the staged planes take 2 B 12 256 complex values of LDS: one or two sources
   constexpr bool kStage = 2 * B * 12 * 256 * sizeof(T2) <= 100 * 1024;
   // the operator-per-workgroup variant stages one field: B 12 256 values
@@ -1059,11 +1097,11 @@ static hipError_t launch_d(const DualArgs& a, const Geometry& g, const Hop& hA, 
       std::call_once(march_lds, [] { apply_lds_limit((const void*)k_dual_march<R>); });
       if (!lds_fits((const void*)k_dual_march<R>, a.lds_kb)) return hipErrorInvalidValue;
       const int per_xcd = 2 * tm.ppt * tm.lz * a.nrhs_slots;
-      hipLaunchKernelGGL((k_dual_march<R>), dim3(8 * per_xcd), dim3(256), a.lds_kb * 1024, s,
+      hipLaunchKernelGGL((k_dual_march<R>), dim3(8 * per_xcd + nbeta), dim3(256), a.lds_kb * 1024, s,
                          (const T2*)a.links, (const T2*)a.basis, (const T2*)a.wbuf,
                          a.basis_stride, (int)a.ring, a.it, (T2*)a.out_t, (T2*)a.out_s,
                          a.partials, g, HopR<R>::make(hA), HopR<R>::make(hAd), a.rhs_map,
-                         a.n_active, a.nrhs_slots, a.nt, tm, a.order == 1 ? 1 : 0);
+                         a.n_active, a.nrhs_slots, a.nt, tm, a.order == 1 ? 1 : 0, a.off, a.beta, nbeta);
       return hipSuccess;
     } else {
       return hipErrorInvalidValue;
@@ -1077,10 +1115,11 @@ static hipError_t launch_d(const DualArgs& a, const Geometry& g, const Hop& hA, 
     const void* fn = stage ? (const void*)k_dual_op<R, B, kStageOp> : (const void*)k_dual_op<R, B, false>;
     if (!lds_fits(fn, a.lds_kb)) return hipErrorInvalidValue;
 #define OVS_DUAL_OP(ST)                                                                        \
-  hipLaunchKernelGGL((k_dual_op<R, B, ST>), dim3(16 * tm.per_xcd), dim3(256), a.lds_kb * 1024, s, \
+  hipLaunchKernelGGL((k_dual_op<R, B, ST>), dim3(16 * tm.per_xcd + nbeta), dim3(256), a.lds_kb * 1024, s, \
                      (const T2*)a.links, (const T2*)a.basis, (const T2*)a.wbuf, a.basis_stride, \
                      (int)a.ring, a.it, (T2*)a.out_t, (T2*)a.out_s, a.partials, g,             \
-                     HopR<R>::make(hA), HopR<R>::make(hAd), a.rhs_map, a.n_active, a.nt, tm)
+                     HopR<R>::make(hA), HopR<R>::make(hAd), a.rhs_map, a.n_active, a.nt, tm, a.off,           \
+                     a.beta, nbeta)
     if (stage) OVS_DUAL_OP(kStageOp);
     else OVS_DUAL_OP(false);
 #undef OVS_DUAL_OP
@@ -1089,11 +1128,11 @@ static hipError_t launch_d(const DualArgs& a, const Geometry& g, const Hop& hA, 
   if (a.pair == 2) {
     if constexpr (kStage) {
       if (!lds_fits((const void*)k_dual_pair<R, B, true>, a.lds_kb)) return hipErrorInvalidValue;
-      hipLaunchKernelGGL((k_dual_pair<R, B, true>), dim3(8 * tm.per_xcd), dim3(512),
+      hipLaunchKernelGGL((k_dual_pair<R, B, true>), dim3(8 * tm.per_xcd + nbeta), dim3(512),
                          a.lds_kb * 1024, s, (const T2*)a.links, (const T2*)a.basis,
                          (const T2*)a.wbuf, a.basis_stride, (int)a.ring, a.it, (T2*)a.out_t,
                          (T2*)a.out_s, a.partials, g, HopR<R>::make(hA), HopR<R>::make(hAd),
-                         a.rhs_map, a.n_active, a.nt, tm);
+                         a.rhs_map, a.n_active, a.nt, tm, a.off, a.beta, nbeta);
       return hipSuccess;
     } else {
       return hipErrorInvalidValue;
@@ -1102,16 +1141,16 @@ static hipError_t launch_d(const DualArgs& a, const Geometry& g, const Hop& hA, 
   const void* fn = a.pair == 1 ? (const void*)k_dual_pair<R, B, false> : (const void*)k_dual<R, B>;
   if (!lds_fits(fn, a.lds_kb)) return hipErrorInvalidValue;
   if (a.pair == 1)
-    hipLaunchKernelGGL((k_dual_pair<R, B, false>), dim3(8 * tm.per_xcd), dim3(512),
+    hipLaunchKernelGGL((k_dual_pair<R, B, false>), dim3(8 * tm.per_xcd + nbeta), dim3(512),
                        a.lds_kb * 1024, s, (const T2*)a.links, (const T2*)a.basis,
                        (const T2*)a.wbuf, a.basis_stride, (int)a.ring, a.it, (T2*)a.out_t,
                        (T2*)a.out_s, a.partials, g, HopR<R>::make(hA), HopR<R>::make(hAd),
-                       a.rhs_map, a.n_active, a.nt, tm);
+                       a.rhs_map, a.n_active, a.nt, tm, a.off, a.beta, nbeta);
   else
-    hipLaunchKernelGGL((k_dual<R, B>), dim3(8 * tm.per_xcd), dim3(256), a.lds_kb * 1024, s,
+    hipLaunchKernelGGL((k_dual<R, B>), dim3(8 * tm.per_xcd + nbeta), dim3(256), a.lds_kb * 1024, s,
                        (const T2*)a.links, (const T2*)a.basis, (const T2*)a.wbuf, a.basis_stride,
                        (int)a.ring, a.it, (T2*)a.out_t, (T2*)a.out_s, a.partials, g,
-                       HopR<R>::make(hA), HopR<R>::make(hAd), a.rhs_map, a.n_active, a.nt, tm);
+                       HopR<R>::make(hA), HopR<R>::make(hAd), a.rhs_map, a.n_active, a.nt, tm, a.off, a.beta, nbeta);
   return hipSuccess;
 }
 
