@@ -129,6 +129,27 @@ ovs_status ensure_ws(ovs_lattice_s* l, size_t bytes) {
   return OVS_OK;
 }
 
+// Grows the handle's pinned host buffer to at least bytes.  Kernels read their
+// small inputs from it and write their small results to it directly; the host
+// looks at results after a stream synchronisation.
+static ovs_status ensure_pin(ovs_lattice_s* l, size_t bytes) {
+  if (l->pin_bytes >= bytes) return OVS_OK;
+  std::lock_guard<std::mutex> lock(g_capture_mu);
+  if (l->pin) {
+    OVS_HIP(hipStreamSynchronize(l->stream));
+    (void)hipHostFree(l->pin);
+    l->pin = nullptr;
+    l->pin_bytes = 0;
+  }
+  if (hipHostMalloc(&l->pin, bytes, hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    l->pin = nullptr;
+    return OVS_ERR_ALLOC;
+  }
+  l->pin_bytes = bytes;
+  return OVS_OK;
+}
+
 void pack_field(const ovs_lattice_s* l, const void* canon, void* field, int nrhs) {
   if (l->prec == OVS_F32_STORE)
     launch_pack_f32((const double2*)canon, (float2*)field, nrhs, l->g, l->stream);
@@ -213,8 +234,8 @@ int max_nodes() {
 }
 
 // Scratch of the inner sign (sizes in ovs_krylov.h): mult, swp, part for
-// the tridiagonal form; ys, acc for the Hessenberg form; xtmp [nrhs][kmax]
-// and kv [nrhs] for the refinement levels.
+// the tridiagonal form; ys, acc, and xtmp [nrhs][kmax], kv [nrhs] for the
+// refinement levels, of the Hessenberg form.
 struct InnerScratch {
   double2* mult = nullptr;
   unsigned long long* swp = nullptr;
@@ -223,7 +244,6 @@ struct InnerScratch {
   double2* acc = nullptr;
   double2* xtmp = nullptr;
   int* kv = nullptr;
-  QuadNodes* rules = nullptr;  // [nrhs] the rule of each source (tridiagonal form)
 };
 
 // Quadrature target of each source (see kQuadAccept); tol may be NULL.
@@ -234,35 +254,107 @@ std::vector<double> quad_targets(const double* tol, int nrhs) {
   return t;
 }
 
-// x[r] = sgn(T_r) e_1 for the sources with kvec[r] > 0 (rows of the others
-// are zero).  Runs the quadrature at h = 0.25 and halves h for the sources
-// whose coarse/fine difference is above their target, down to h = kHMin;
-// each source keeps the x of the first step that met its target (or of the
-// finest), so its result does not depend on the other sources of the batch.
-// err_host[r]: that step's difference.
+// x[r] = sgn(T_r) e_1 for the sources with kcap[r] > 0 (rows of the others
+// are zero), T_r of size min(kcap[r], kstop[r]) (kstop: device, or null).  Runs
+// the quadrature at h = 0.25 and halves h for the sources whose coarse/fine
+// difference is above their target, down to h = kHMin; each source keeps the x
+// of the first step that met its target (or of the finest), so its result does
+// not depend on the other sources of the batch.  out[r]: that step's difference,
+// and the source's k, kstop and status (device array, or null).
 //
 // h_level (optional, per source, in and out): on entry the step at which the
 // source's refinement starts (kHStart or a power-of-two fraction of it), on
 // return the step it was accepted at.  Without it every source starts at
-// kHStart.  Every round takes each unaccepted source at its own step: the
-// tridiagonal form in one launch (per-source rules), the Hessenberg form in
-// one launch per distinct step.  A source's steps depend only on its own
-// differences, so its x, and with it the convergence checks that pass their
-// levels from one check to the next, do not depend on the rest of the batch.
-ovs_status inner_sign(ovs_lattice_s* l, bool tri, const double2* alpha, const double* beta,
-                      const double2* gamma, const double2* H, int kmax,
-                      const std::vector<int>& kvec, int nrhs, InnerScratch& sc, double2* x,
-                      double* err_dev, const std::vector<double>& target,
-                      std::vector<double>& err_host, std::vector<double>* h_level = nullptr) {
+// kHStart.  Every round takes each unaccepted source at its own step and, where
+// both fit the scratch, the next finer one in the same launch: a launch takes
+// the time of one elimination however many solves it holds, and the device
+// picks the first step that meets the target.  A source's steps depend only on
+// its own differences, so its x, and with it the convergence checks that pass
+// their levels from one check to the next, do not depend on the rest of the
+// batch.
+//
+// kout: device [nrhs], the sizes of the first round, or null.  then (optional):
+// enqueues work that uses x and kout; called after the launches of the first
+// round, and again if a later round changed x.
+ovs_status inner_sign_tri(ovs_lattice_s* l, const double2* alpha, const double* beta,
+                          const double2* gamma, int kmax, const std::vector<int>& kcap,
+                          const int* kstop, const int* status, int nrhs, InnerScratch& sc,
+                          double2* x, int* kout, const std::vector<double>& target,
+                          std::vector<IsignResult>& out, std::vector<double>* h_level = nullptr,
+                          const std::function<ovs_status()>& then = nullptr) {
+  hipStream_t s = l->stream;
+  const size_t tb = sizeof(IsignTask) * (size_t)nrhs;
+  ovs_status st = ensure_pin(l, tb + sizeof(IsignResult) * (size_t)nrhs);
+  if (st != OVS_OK) return st;
+  IsignTask* task = (IsignTask*)l->pin;
+  IsignResult* res = (IsignResult*)((char*)l->pin + tb);
+  out.assign(nrhs, IsignResult{0.0, 0, 0, 0, 0});
+  const bool lev = h_level && (int)h_level->size() >= nrhs;
+  std::vector<double> cur(nrhs, kHStart);
+  std::vector<char> open(nrhs, 0);
+  for (int r = 0; r < nrhs; ++r) {
+    open[r] = kcap[r] > 0;
+    if (lev) cur[r] = std::max(kHMin, std::min(kHStart, (*h_level)[r]));
+  }
+  const int cap = isign_tri_nwave(max_nodes());
+  for (bool first = true;; first = false) {
+    int nw = 0;
+    for (int r = 0; r < nrhs; ++r) {
+      IsignTask& t = task[r];
+      t = IsignTask{};
+      t.k = open[r] ? kcap[r] : 0;
+      t.target = target[r];
+      t.hmin = kHMin;
+      if (!open[r]) continue;
+      int w = 0;
+      for (int q = 0; q < 2; ++q) {
+        const double h = q ? 0.5 * cur[r] : cur[r];
+        int n0, nn;
+        quad_range(h, n0, nn);
+        if (q && (h < kHMin || w + isign_tri_nwave(nn) > cap)) break;
+        t.rule[q] = QuadNodes{h, n0, nn};
+        w += isign_tri_nwave(nn);
+      }
+      nw = std::max(nw, w);
+    }
+    launch_isign_tri(alpha, beta, gamma, kmax, task, kstop, status, nrhs, nw,
+                     isign_wave_chunk(nrhs), first, sc.mult, sc.swp, sc.part, x, kout, res, s);
+    OVS_HIP(hipGetLastError());
+    if (then) {
+      st = then();
+      if (st != OVS_OK) return st;
+    }
+    OVS_HIP(hipStreamSynchronize(s));
+    bool any = false;
+    for (int r = 0; r < nrhs; ++r) {
+      if (first) out[r] = res[r];
+      if (!open[r]) continue;
+      out[r] = res[r];
+      if (res[r].k <= 0) {
+        open[r] = 0;
+      } else if (res[r].level >= 0) {
+        if (lev) (*h_level)[r] = task[r].rule[res[r].level].h;
+        open[r] = 0;
+      } else {
+        cur[r] = 0.5 * (task[r].rule[1].nnode ? task[r].rule[1].h : task[r].rule[0].h);
+        any = true;
+      }
+    }
+    if (!any) return OVS_OK;
+  }
+}
+
+// The same for upper Hessenberg matrices of size kvec[r] (Arnoldi), one launch
+// per distinct step of a round.
+ovs_status inner_sign_hess(ovs_lattice_s* l, const double2* H, int kmax,
+                           const std::vector<int>& kvec, int nrhs, InnerScratch& sc, double2* x,
+                           double* err_dev, const std::vector<double>& target,
+                           std::vector<double>& err_host) {
   hipStream_t s = l->stream;
   std::vector<int> klev(kvec.begin(), kvec.begin() + nrhs);
   std::vector<int> kl(nrhs, 0);
   std::vector<double> eh(nrhs, 0.0), cur(nrhs, kHStart);
-  std::vector<QuadNodes> rules(nrhs);
   err_host.assign(nrhs, 0.0);
-  const bool lev = h_level && (int)h_level->size() >= nrhs;
-  if (lev)
-    for (int r = 0; r < nrhs; ++r) cur[r] = std::max(kHMin, std::min(kHStart, (*h_level)[r]));
   bool first = true;  // the first launch writes every row of x
   // accept or refine the sources that took part in the launch just read back
   auto settle = [&](const std::vector<int>& part_in) -> ovs_status {
@@ -274,7 +366,6 @@ ovs_status inner_sign(ovs_lattice_s* l, bool tri, const double2* alpha, const do
                                  sizeof(double2) * kmax, hipMemcpyDeviceToDevice, s));
         err_host[r] = eh[r];
         klev[r] = 0;
-        if (lev) (*h_level)[r] = cur[r];
       } else {
         cur[r] *= 0.5;
       }
@@ -285,48 +376,26 @@ ovs_status inner_sign(ovs_lattice_s* l, bool tri, const double2* alpha, const do
     bool any = false;
     for (int r = 0; r < nrhs; ++r) any = any || klev[r] > 0;
     if (!any && !first) break;
-    if (tri) {
-      int nw = 1;
-      for (int r = 0; r < nrhs; ++r) {
-        int n0, nn;
-        quad_range(klev[r] > 0 ? cur[r] : kHStart, n0, nn);
-        rules[r] = QuadNodes{klev[r] > 0 ? cur[r] : kHStart, n0, nn};
-        if (klev[r] > 0) nw = std::max(nw, isign_tri_nwave(nn));
-      }
-      OVS_HIP(hipMemcpyAsync(sc.kv, klev.data(), sizeof(int) * nrhs, hipMemcpyHostToDevice, s));
-      OVS_HIP(hipMemcpyAsync(sc.rules, rules.data(), sizeof(QuadNodes) * nrhs,
-                             hipMemcpyHostToDevice, s));
-      launch_isign_tri(alpha, beta, gamma, kmax, sc.kv, nrhs, sc.rules, nw, sc.mult, sc.swp,
-                       sc.part, first ? x : sc.xtmp, err_dev, s);
+    // one launch per distinct step of the round, coarsest first
+    std::vector<double> steps;
+    for (int r = 0; r < nrhs; ++r)
+      if (klev[r] > 0 && std::find(steps.begin(), steps.end(), cur[r]) == steps.end())
+        steps.push_back(cur[r]);
+    if (steps.empty()) steps.push_back(kHStart);  // no active source: zero rows
+    std::sort(steps.begin(), steps.end(), std::greater<double>());
+    for (double h : steps) {
+      for (int r = 0; r < nrhs; ++r) kl[r] = (klev[r] > 0 && cur[r] == h) ? klev[r] : 0;
+      int n0, nn;
+      quad_range(h, n0, nn);
+      OVS_HIP(hipMemcpyAsync(sc.kv, kl.data(), sizeof(int) * nrhs, hipMemcpyHostToDevice, s));
+      launch_isign_hess(H, kmax, sc.kv, nrhs, h, n0, nn, sc.ys, sc.acc, first ? x : sc.xtmp,
+                        err_dev, s);
       OVS_HIP(hipGetLastError());
       OVS_HIP(hipMemcpyAsync(eh.data(), err_dev, sizeof(double) * nrhs, hipMemcpyDeviceToHost, s));
       OVS_HIP(hipStreamSynchronize(s));
-      const std::vector<int> took = klev;
-      const ovs_status sst = settle(took);
+      const ovs_status sst = settle(kl);
       if (sst != OVS_OK) return sst;
       first = false;
-    } else {
-      // one launch per distinct step of the round, coarsest first
-      std::vector<double> steps;
-      for (int r = 0; r < nrhs; ++r)
-        if (klev[r] > 0 && std::find(steps.begin(), steps.end(), cur[r]) == steps.end())
-          steps.push_back(cur[r]);
-      if (steps.empty()) steps.push_back(kHStart);  // no active source: zero rows
-      std::sort(steps.begin(), steps.end(), std::greater<double>());
-      for (double h : steps) {
-        for (int r = 0; r < nrhs; ++r) kl[r] = (klev[r] > 0 && cur[r] == h) ? klev[r] : 0;
-        int n0, nn;
-        quad_range(h, n0, nn);
-        OVS_HIP(hipMemcpyAsync(sc.kv, kl.data(), sizeof(int) * nrhs, hipMemcpyHostToDevice, s));
-        launch_isign_hess(H, kmax, sc.kv, nrhs, h, n0, nn, sc.ys, sc.acc, first ? x : sc.xtmp,
-                          err_dev, s);
-        OVS_HIP(hipGetLastError());
-        OVS_HIP(hipMemcpyAsync(eh.data(), err_dev, sizeof(double) * nrhs, hipMemcpyDeviceToHost, s));
-        OVS_HIP(hipStreamSynchronize(s));
-        const ovs_status sst = settle(kl);
-        if (sst != OVS_OK) return sst;
-        first = false;
-      }
     }
   }
   OVS_HIP(hipStreamSynchronize(s));  // host vector lifetimes
@@ -404,6 +473,7 @@ static void destroy_shadow(ovs_lattice_s* l) {
   if (!sh) return;
   if (sh->ws) (void)hipFree(sh->ws);
   if (sh->bbuf) (void)hipFree(sh->bbuf);
+  if (sh->pin) (void)hipHostFree(sh->pin);
   (void)hipEventDestroy(sh->ev_in);
   (void)hipEventDestroy(sh->ev_out);
   delete sh;  // links (the parent's links64) and stream belong to the parent
@@ -416,6 +486,7 @@ static void destroy_worker(ovs_lattice_s* l) {
   (void)hipStreamSynchronize(w->stream);
   if (w->ws) (void)hipFree(w->ws);
   if (w->bbuf) (void)hipFree(w->bbuf);
+  if (w->pin) (void)hipHostFree(w->pin);
   (void)hipEventDestroy(w->ev_in);
   (void)hipEventDestroy(w->ev_out);
   (void)hipStreamDestroy(w->stream);
@@ -434,6 +505,7 @@ ovs_status ovs_lattice_destroy(ovs_lattice l) {
   if (l->links64) (void)hipFree(l->links64);
   if (l->ws) (void)hipFree(l->ws);
   if (l->bbuf) (void)hipFree(l->bbuf);
+  if (l->pin) (void)hipHostFree(l->pin);
   (void)hipEventDestroy(l->ev_in);
   (void)hipEventDestroy(l->ev_out);
   (void)hipStreamDestroy(l->stream);
@@ -1089,9 +1161,8 @@ static ovs_status sign_apply_impl(ovs_lattice l, ovs_deflation defl, int32_t n_d
     double2 *alpha, *gamma, *sw, *coef, *x, *mult, *part, *H, *hcur, *ys, *acc, *xtmp;
     double *beta, *sv, *tnorm2, *qerr, *red, *apart, *red_n, *red_tn, *scl, *dnorm;
     int *kstop, *status, *rhs_map, *ints, *kused, *pidx, *kv;
-    QuadNodes* rules;
     unsigned long long* swp;
-    double2 *probes, *yp;
+    double2* probes;
     unsigned* bar;
   } B{};
   const bool probing = tol != nullptr;
@@ -1133,16 +1204,12 @@ static ovs_status sign_apply_impl(ovs_lattice l, ovs_deflation defl, int32_t n_d
     B.x = a.take<double2>((size_t)nr * K);
     B.qerr = a.take<double>(nr);
     B.coef = a.take<double2>((size_t)nr * K);
-    B.xtmp = a.take<double2>((size_t)nr * K);
-    B.kv = a.take<int>(nr);
-    B.rules = a.take<QuadNodes>(nr);
     if (probing) {
       B.pidx = a.take<int>(P);
       B.probes = a.take<double2>((size_t)nr * K * P);
-      B.yp = a.take<double2>((size_t)nr * P);
     }
     if (!arn) {
-      const int wchunk = std::min(kIsignWaveChunk, nwave_max);
+      const int wchunk = isign_wave_chunk(nr);
       B.mult = a.take<double2>((size_t)nr * wchunk * K * 64);
       B.swp = a.take<unsigned long long>((size_t)nr * wchunk * isign_swp_words(K) * 64);
       B.part = a.take<double2>((size_t)nr * nwave_max * 2 * K);
@@ -1161,6 +1228,8 @@ static ovs_status sign_apply_impl(ovs_lattice l, ovs_deflation defl, int32_t n_d
       B.scl = a.take<double>(nr);
       B.ys = a.take<double2>((size_t)nr * nq_chunk * K);
       B.acc = a.take<double2>((size_t)nr * 2 * K);
+      B.xtmp = a.take<double2>((size_t)nr * K);
+      B.kv = a.take<int>(nr);
     }
   };
   {
@@ -1393,9 +1462,19 @@ static ovs_status sign_apply_impl(ovs_lattice l, ovs_deflation defl, int32_t n_d
   std::vector<double> best_est(nr, HUGE_VAL);
   std::vector<int> since_best(nr, 0);
   std::vector<char> stalled(nr, 0);
-  InnerScratch isc{B.mult, B.swp, B.part, B.ys, B.acc, B.xtmp, B.kv, B.rules};
+  InnerScratch isc{B.mult, B.swp, B.part, B.ys, B.acc, B.xtmp, B.kv};
   const std::vector<double> qtarget = quad_targets(tol, nr);
   std::vector<double> errh;
+  std::vector<IsignResult> ires;
+  // sampled entries of the result, written by the device (pinned, behind the
+  // exchange of the inner sign)
+  const size_t pin_head = ((sizeof(IsignTask) + sizeof(IsignResult)) * (size_t)nr + 255) & ~size_t(255);
+  double* yph = nullptr;
+  {
+    ovs_status st = ensure_pin(l, pin_head + (probing ? sizeof(double2) * (size_t)nr * P : 0));
+    if (st != OVS_OK) return st;
+    yph = (double*)((char*)l->pin + pin_head);
+  }
 
   if (!arn) {
     // ---- two-sided Lanczos (Section 4) ----
@@ -1542,27 +1621,26 @@ static ovs_status sign_apply_impl(ovs_lattice l, ovs_deflation defl, int32_t n_d
         // convergence check at k = i (the paper gives no stopping rule): the
         // relative change of y on the sampled entries since the previous check
         // against tol / 10
-        std::vector<int> ks(nr, 0);
-        OVS_HIP(hipMemcpyAsync(hkstop.data(), B.kstop, sizeof(int) * nr, hipMemcpyDeviceToHost, s));
-        OVS_HIP(hipStreamSynchronize(s));
-        for (int r : amap) ks[r] = std::min(i, hkstop[r]);
-        OVS_HIP(hipMemcpyAsync(B.kused, ks.data(), sizeof(int) * nr, hipMemcpyHostToDevice, s));
+        std::vector<int> kcap(nr, 0);
+        for (int r : amap) kcap[r] = i;
         hlev = hcheck;
-        st = inner_sign(l, true, B.alpha, B.beta, B.gamma, nullptr, K, ks, nr, isc, B.x,
-                        B.qerr, qtarget, errh, &hlev);
+        st = inner_sign_tri(l, B.alpha, B.beta, B.gamma, K, kcap, B.kstop, B.status, nr, isc, B.x,
+                            B.kused, qtarget, ires, &hlev, [&]() -> ovs_status {
+                              launch_probe_y(B.probes, B.x, B.sv, B.nb, B.kused, K, B.yex, N,
+                                             B.pidx, P, (double2*)yph, nr, s);
+                              OVS_HIP(hipGetLastError());
+                              return OVS_OK;
+                            });
         if (st != OVS_OK) return st;
         // a source that needed refinement starts its next check where it was
         // accepted; one accepted at its first step tries one step coarser (a
         // Ritz value near the imaginary axis may have moved away)
-        for (int r = 0; r < nr; ++r)
-          if (ks[r] > 0)
+        for (int r : amap) {
+          hkstop[r] = ires[r].kstop;
+          if (ires[r].k > 0)
             hcheck[r] = hlev[r] < hcheck[r] ? hlev[r] : std::min(kHStart, 2.0 * hcheck[r]);
-        // relative change of y on the sampled entries since the previous check
-        launch_make_coef(B.x, B.sv, B.nb, K, nr, B.coef, s);
-        launch_probe_y(B.probes, B.coef, B.kused, K, B.yex, N, B.pidx, P, B.yp, nr, s);
-        std::vector<double> yph((size_t)nr * P * 2);
-        OVS_HIP(hipMemcpyAsync(yph.data(), B.yp, sizeof(double2) * nr * P, hipMemcpyDeviceToHost, s));
-        OVS_HIP(hipStreamSynchronize(s));
+        }
+        const size_t nact = amap.size();
         for (int r : amap) {
           const double* yr = &yph[(size_t)r * P * 2];
           std::vector<double>& yprev = xprev[r];
@@ -1576,7 +1654,7 @@ static ovs_status sign_apply_impl(ovs_lattice l, ovs_deflation defl, int32_t n_d
           yprev.assign(yr, yr + 2 * P);
           if (hkstop[r] <= i || (had_prev && est[r] <= 0.1 * tol[r])) {
             done[r] = 1;
-            kused[r] = ks[r];
+            kused[r] = ires[r].k;
           } else if (f32 && had_prev) {
             // FP32 rounding of the stored vectors can stall one source's
             // recurrence: an estimate that has not halved in kStallChecks
@@ -1587,13 +1665,17 @@ static ovs_status sign_apply_impl(ovs_lattice l, ovs_deflation defl, int32_t n_d
               since_best[r] = 0;
             } else if (++since_best[r] >= kStallChecks) {
               done[r] = 1;
-              kused[r] = ks[r];
+              kused[r] = ires[r].k;
               stalled[r] = 1;
             }
           }
         }
-        st = push_map();
-        if (st != OVS_OK) return st;
+        size_t left = 0;
+        for (int r = 0; r < nr; ++r) left += !done[r];
+        if (left != nact) {
+          st = push_map();
+          if (st != OVS_OK) return st;
+        }
       }
     }
     if (use_persist) {
@@ -1609,18 +1691,18 @@ static ovs_status sign_apply_impl(ovs_lattice l, ovs_deflation defl, int32_t n_d
     }
     rg.phase("inner_sign");
     OVS_HIP(hipEventRecord(ev[2], s));
-    OVS_HIP(hipMemcpyAsync(hkstop.data(), B.kstop, sizeof(int) * nr, hipMemcpyDeviceToHost, s));
-    OVS_HIP(hipMemcpyAsync(hstatus.data(), B.status, sizeof(int) * nr, hipMemcpyDeviceToHost, s));
-    OVS_HIP(hipStreamSynchronize(s));
-    for (int r = 0; r < nr; ++r) {
-      if (!done[r]) kused[r] = std::min(K, hkstop[r]);
-      else if (kused[r] > 0) kused[r] = std::min(kused[r], hkstop[r]);
-    }
-    OVS_HIP(hipMemcpyAsync(B.kused, kused.data(), sizeof(int) * nr, hipMemcpyHostToDevice, s));
-    st = inner_sign(l, true, B.alpha, B.beta, B.gamma, nullptr, K, kused, nr, isc, B.x, B.qerr,
-                    qtarget, errh);
+    // the size of each source: where it stopped, or all steps (less after a breakdown)
+    std::vector<int> kcap(nr);
+    for (int r = 0; r < nr; ++r) kcap[r] = done[r] ? kused[r] : K;
+    st = inner_sign_tri(l, B.alpha, B.beta, B.gamma, K, kcap, B.kstop, B.status, nr, isc, B.x,
+                        B.kused, qtarget, ires);
     if (st != OVS_OK) return st;
-    qerr = errh;
+    for (int r = 0; r < nr; ++r) {
+      hkstop[r] = ires[r].kstop;
+      hstatus[r] = ires[r].status;
+      kused[r] = ires[r].k;
+      qerr[r] = ires[r].err;
+    }
     if (debug) {
       st = debug_inner(true);
       if (st != OVS_OK) return st;
@@ -1710,13 +1792,11 @@ static ovs_status sign_apply_impl(ovs_lattice l, ovs_deflation defl, int32_t n_d
         }
         if (nact == 0) break;
         OVS_HIP(hipMemcpyAsync(B.kused, ks.data(), sizeof(int) * nr, hipMemcpyHostToDevice, s));
-        ovs_status st = inner_sign(l, false, nullptr, nullptr, nullptr, B.H, K, ks, nr, isc,
-                                   B.x, B.qerr, qtarget, errh);
+        ovs_status st = inner_sign_hess(l, B.H, K, ks, nr, isc, B.x, B.qerr, qtarget, errh);
         if (st != OVS_OK) return st;
-        launch_make_coef(B.x, nullptr, B.nb, K, nr, B.coef, s);
-        launch_probe_y(B.probes, B.coef, B.kused, K, B.yex, N, B.pidx, P, B.yp, nr, s);
-        std::vector<double> yph((size_t)nr * P * 2);
-        OVS_HIP(hipMemcpyAsync(yph.data(), B.yp, sizeof(double2) * nr * P, hipMemcpyDeviceToHost, s));
+        launch_probe_y(B.probes, B.x, nullptr, B.nb, B.kused, K, B.yex, N, B.pidx, P, (double2*)yph,
+                       nr, s);
+        OVS_HIP(hipGetLastError());
         OVS_HIP(hipStreamSynchronize(s));
         bool all_done = true;
         for (int r = 0; r < nr; ++r) {
@@ -1750,8 +1830,7 @@ static ovs_status sign_apply_impl(ovs_lattice l, ovs_deflation defl, int32_t n_d
       else if (kused[r] > 0) kused[r] = std::min(kused[r], hkstop[r]);
     }
     OVS_HIP(hipMemcpyAsync(B.kused, kused.data(), sizeof(int) * nr, hipMemcpyHostToDevice, s));
-    ovs_status st = inner_sign(l, false, nullptr, nullptr, nullptr, B.H, K, kused, nr, isc, B.x,
-                               B.qerr, qtarget, errh);
+    ovs_status st = inner_sign_hess(l, B.H, K, kused, nr, isc, B.x, B.qerr, qtarget, errh);
     if (st != OVS_OK) return st;
     qerr = errh;
     if (debug) {
@@ -2107,11 +2186,11 @@ static ovs_status inner_sign_entry(ovs_lattice l, bool tri, int batch, int k, co
   StreamScope scope(l);
   hipStream_t s = l->stream;
   const int nwave = isign_tri_nwave(max_nodes());
-  const int wchunk = std::min(kIsignWaveChunk, nwave);
+  const int wchunk = isign_wave_chunk(batch);
   const int nq = std::min(kIsignHessChunk, 2 * max_nodes());
   Arena sizing{nullptr};
-  auto lay = [&](Arena& a, double2*& al, double*& be, double2*& ga, double2*& H, int*& kv,
-                 InnerScratch& sc, double2*& xd, double*& ed) {
+  auto lay = [&](Arena& a, double2*& al, double*& be, double2*& ga, double2*& H, InnerScratch& sc,
+                 double2*& xd, double*& ed) {
     if (tri) {
       al = a.take<double2>((size_t)batch * k);
       be = a.take<double>((size_t)batch * k);
@@ -2124,24 +2203,20 @@ static ovs_status inner_sign_entry(ovs_lattice l, bool tri, int batch, int k, co
       sc.ys = a.take<double2>((size_t)batch * nq * k);
       sc.acc = a.take<double2>((size_t)batch * 2 * k);
     }
-    kv = a.take<int>(batch);
     xd = a.take<double2>((size_t)batch * k);
     ed = a.take<double>(batch);
     sc.xtmp = a.take<double2>((size_t)batch * k);
     sc.kv = a.take<int>(batch);
-    sc.rules = a.take<QuadNodes>(batch);
   };
   double2 *al = nullptr, *ga = nullptr, *H = nullptr, *xd = nullptr;
   double *be = nullptr, *ed = nullptr;
-  int* kv = nullptr;
   InnerScratch sc;
-  lay(sizing, al, be, ga, H, kv, sc, xd, ed);
+  lay(sizing, al, be, ga, H, sc, xd, ed);
   ovs_status st = ensure_ws(l, sizing.off + 4096);
   if (st != OVS_OK) return st;
   Arena a{(char*)l->ws};
-  lay(a, al, be, ga, H, kv, sc, xd, ed);
+  lay(a, al, be, ga, H, sc, xd, ed);
   std::vector<int> kh(batch, k);
-  OVS_HIP(hipMemcpyAsync(kv, kh.data(), sizeof(int) * batch, hipMemcpyHostToDevice, s));
   if (tri) {
     std::vector<double> bre((size_t)batch * k);
     for (size_t q = 0; q < bre.size(); ++q) {
@@ -2157,7 +2232,13 @@ static ovs_status inner_sign_entry(ovs_lattice l, bool tri, int batch, int k, co
   }
   std::vector<double> eh;
   const std::vector<double> target = quad_targets(nullptr, batch);
-  st = inner_sign(l, tri, al, be, ga, H, k, kh, batch, sc, xd, ed, target, eh);
+  if (tri) {
+    std::vector<IsignResult> res;
+    st = inner_sign_tri(l, al, be, ga, k, kh, nullptr, nullptr, batch, sc, xd, nullptr, target, res);
+    for (const IsignResult& q : res) eh.push_back(q.err);
+  } else {
+    st = inner_sign_hess(l, H, k, kh, batch, sc, xd, ed, target, eh);
+  }
   if (st != OVS_OK) return st;
   OVS_HIP(hipMemcpyAsync(x, xd, sizeof(double2) * batch * k, hipMemcpyDeviceToHost, s));
   OVS_HIP(hipStreamSynchronize(s));

@@ -240,36 +240,48 @@ __global__ void __launch_bounds__(256) k_probe_gather(const T2* __restrict__ bas
     probes[((long)slot * kmax + j) * P + p] = d2(ld64(v + idx[p]));
 }
 
-// yp[r][p] = yex[r][idx[p]] + sum_{i < k_r} coef[r][i] probes[r][i][p]
-__global__ void __launch_bounds__(256) k_probe_y(const double2* __restrict__ probes,
-                                                 const double2* __restrict__ coef,
-                                                 const int* __restrict__ kvec, int kmax,
-                                                 const double2* __restrict__ yex, long N,
-                                                 const int* __restrict__ idx, int P,
-                                                 double2* __restrict__ yp) {
+// yp[r][p] = yex[r][idx[p]] + sum_{i < k_r} c_i probes[r][i][p] with the
+// combination's coefficients c_i = n_b x[r][i] sv[r][i] (k_make_coef's), formed
+// for 64 terms at a time by the workgroup.  Bound by memory latency along i:
+// the loads of 16 terms are issued before their multiply-adds (k = 375: 22 us a
+// launch with eight, behind a launch that formed the coefficients).
+__global__ void __launch_bounds__(64) k_probe_y(const double2* __restrict__ probes,
+                                                const double2* __restrict__ x,
+                                                const double* __restrict__ sv,
+                                                const double* __restrict__ nb,
+                                                const int* __restrict__ kvec, int kmax,
+                                                const double2* __restrict__ yex, long N,
+                                                const int* __restrict__ idx, int P,
+                                                double2* __restrict__ yp) {
+  __shared__ double2 cs[64];
   const int r = blockIdx.y;
   const int k = kvec[r];
-  for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < P; p += gridDim.x * blockDim.x) {
-    Cx<double> acc = yex ? c64(yex[(long)r * N + idx[p]]) : Cx<double>{0, 0};
-    const double2* cr = coef + (long)r * kmax;
-    const double2* pr = probes + (long)r * kmax * P + p;
-    // the same sequential sum as one term per step, with the loads of eight
-    // terms issued before their multiply-adds (one thread's loop is otherwise
-    // a chain of dependent memory latencies)
-    int i = 0;
-    for (; i + 8 <= k; i += 8) {
-      Cx<double> c[8], q[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        c[u] = c64(cr[i + u]);
-        q[u] = c64(pr[(long)(i + u) * P]);
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) acc = cfma(c[u], q[u], acc);
+  const int p = blockIdx.x * 64 + threadIdx.x;
+  const int pc = min(p, P - 1);
+  const double n_b = nb[r];
+  const double2* xr = x + (long)r * kmax;
+  const double* svr = sv ? sv + (long)r * (kmax + 1) : nullptr;
+  const double2* pr = probes + (long)r * kmax * P + pc;
+  Cx<double> acc = yex ? c64(yex[(long)r * N + idx[pc]]) : Cx<double>{0, 0};
+  for (int i0 = 0; i0 < k; i0 += 64) {
+    const int n = min(64, k - i0);
+    __syncthreads();
+    if ((int)threadIdx.x < n) {
+      const int i = i0 + threadIdx.x;
+      cs[threadIdx.x] = d2(scale(n_b * (svr ? svr[i] : 1.0), c64(xr[i])));
     }
-    for (; i < k; ++i) acc = cfma(c64(cr[i]), c64(pr[(long)i * P]), acc);
-    yp[(long)r * P + p] = d2(acc);
+    __syncthreads();
+    int t = 0;
+    for (; t + 16 <= n; t += 16) {
+      double2 q[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) q[u] = pr[(long)(i0 + t + u) * P];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) acc = cfma(c64(cs[t + u]), c64(q[u]), acc);
+    }
+    for (; t < n; ++t) acc = cfma(c64(cs[t]), c64(pr[(long)(i0 + t) * P]), acc);
   }
+  if (p < P) yp[(long)r * P + p] = d2(acc);
 }
 
 __global__ void k_advance(int* it) { *it += 1; }
@@ -519,13 +531,14 @@ __device__ __forceinline__ double lane_value(double v, int l) {
 }
 
 // One thread per (source r, shifted solve q): q = 2*node + (0: +tau, 1: -tau).
-// Tridiagonal T_r = tridiag(beta, alpha, gamma) of size k_r, with the rule of
-// source r (rules[r]: each source may be at its own step).  Wave results are
-// reduced over lanes: part[r][wave][2][kmax] complex (fine rule, coarse rule),
-// wave = wave0 + blockIdx.x of nwave in all; waves beyond a source's nodes
-// write zero rows.  A launch covers one chunk of waves; the multipliers of a
-// chunk live in mult [r][blockIdx.x][kmax][64] and swp, which the next chunk
-// (ordered on the stream) reuses.
+// Tridiagonal T_r = tridiag(beta, alpha, gamma) of size k_r, with the rules of
+// source r (task[r]: one or two steps, each source its own): the waves of the
+// first rule, then those of the second.  Wave results are reduced over lanes:
+// part[r][wave][2][kmax] complex (fine rule, coarse rule), wave = wave0 +
+// blockIdx.x of nwave in all; waves beyond a source's nodes write nothing.  A
+// launch covers one chunk of waves; the multipliers of a chunk live in mult
+// [r][blockIdx.x][kmax][64] and swp, which the next chunk (ordered on the
+// stream) reuses.
 //
 // swp holds the swaps as bits: word w of a wave and lane is steps 64 w to
 // 64 w + 63 from the bottom, isign_swp_words(kmax) words.
@@ -543,19 +556,23 @@ __device__ __forceinline__ double lane_value(double v, int l) {
 __global__ void __launch_bounds__(64) k_isign_tri(const double2* __restrict__ alpha,
                                                   const double* __restrict__ beta,
                                                   const double2* __restrict__ gamma, int kmax,
-                                                  const int* __restrict__ kvec,
-                                                  const QuadNodes* __restrict__ rules,
+                                                  const IsignTask* __restrict__ task,
+                                                  const int* __restrict__ kstop,
                                                   int wave0, int nwave,
                                                   double2* __restrict__ mult,
                                                   unsigned long long* __restrict__ swp,
                                                   double2* __restrict__ part) {
   const int r = blockIdx.y;
-  const QuadNodes qn = rules[r];
+  const IsignTask tk = task[r];
   const int wave = wave0 + blockIdx.x;
   const int lane = threadIdx.x;
-  const int q = wave * 64 + lane;
+  const int k = kstop ? min(tk.k, kstop[r]) : tk.k;
+  const int nw0 = (2 * tk.rule[0].nnode + 63) / 64;
+  const QuadNodes qn = wave < nw0 ? tk.rule[0] : tk.rule[1];
+  const int first = (wave < nw0 ? wave : wave - nw0) * 64;
   const int nq = 2 * qn.nnode;
-  const int k = kvec[r];
+  if (k <= 0 || first >= nq) return;  // uniform over the wave
+  const int q = first + lane;
   const bool live = q < nq;
   const int node = qn.n0 + (live ? q / 2 : 0);
   const double tau = exp(node * qn.h);
@@ -569,16 +586,6 @@ __global__ void __launch_bounds__(64) k_isign_tri(const double2* __restrict__ al
   unsigned long long* swap_w =
       swp + (long)(r * gridDim.x + blockIdx.x) * isign_swp_words(kmax) * 64 + lane;
   double2* part_r = part + ((long)r * nwave + wave) * 2 * kmax;
-  if (k <= 0) return;
-  if (wave * 64 >= nq) {
-    // beyond this source's nodes (its rule is coarser than another
-    // source's in the launch): zero rows, no solves (uniform over the wave)
-    for (int j = lane; j < k; j += 64) {
-      part_r[j] = make_double2(0.0, 0.0);
-      part_r[kmax + j] = make_double2(0.0, 0.0);
-    }
-    return;
-  }
   // elimination from the bottom: current column j holds (cu: row j-1, cd: row j)
   Cx<double> cu = (k >= 2) ? c64(ga[k - 2]) : Cx<double>{0, 0};
   Cx<double> cd = c64(al[k - 1]) + Cx<double>{0.0, sig};
@@ -699,47 +706,93 @@ __global__ void __launch_bounds__(64) k_isign_tri(const double2* __restrict__ al
   }
 }
 
-// x[r][j] = sum over waves (fixed order); err[r] = |x_fine - x_coarse| / |x_fine|.
+// For each source with a task (k > 0): x[r][j] = sum over the first rule's waves
+// (fixed order) and its error |x_fine - x_coarse| / |x_fine|; if that misses the
+// target and the step is not the finest allowed, the same with the second rule.
+// The result says which rule was accepted (-1: none, x is then not final), its
+// error, and the source's k, kstop and status.  A source without a task keeps
+// its row, or gets a zero row in the first round.  kout (optional): k of each
+// source in the first round.
 // One workgroup per source, bound by memory latency: the loads of eight waves
-// are issued before their additions (22 waves, k = 375: 21 us one at a time,
-// 10.6 us so).
-__global__ void __launch_bounds__(256) k_isign_final(const double2* __restrict__ part, int nwave,
-                                                     int kmax, const int* __restrict__ kvec,
-                                                     double2* __restrict__ x,
-                                                     double* __restrict__ err) {
+// are issued before their additions, 1024 rows at a time (22 waves, k = 375:
+// 21 us one load at a time and 256 rows).  The error sums keep the order of
+// 256 threads striding over the rows.
+__global__ void __launch_bounds__(1024) k_isign_final(const double2* __restrict__ part, int nwave,
+                                                      int kmax, const IsignTask* __restrict__ task,
+                                                      const int* __restrict__ kstop,
+                                                      const int* __restrict__ status, int first,
+                                                      double2* __restrict__ x,
+                                                      int* __restrict__ kout,
+                                                      IsignResult* __restrict__ res) {
   __shared__ double lds[4 * 2];
+  __shared__ double sq[2][1024];
+  __shared__ double err_s;
   const int r = blockIdx.x;
-  const int k = kvec[r];
-  double v[2] = {0, 0};
-  for (int j = threadIdx.x; j < kmax; j += blockDim.x) {
-    Cx<double> f = {0, 0}, c = {0, 0};
-    if (j < k) {
-      const double2* p = part + (long)r * nwave * 2 * kmax + j;
-      int w = 0;
-      for (; w + 8 <= nwave; w += 8) {
-        double2 a[8], b[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          a[u] = p[(long)(w + u) * 2 * kmax];
-          b[u] = p[(long)(w + u) * 2 * kmax + kmax];
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          f = f + c64(a[u]);
-          c = c + c64(b[u]);
-        }
-      }
-      for (; w < nwave; ++w) {
-        f = f + c64(p[(long)w * 2 * kmax]);
-        c = c + c64(p[(long)w * 2 * kmax + kmax]);
-      }
-    }
-    x[(long)r * kmax + j] = d2(f);
-    v[0] += cnorm2(f - c);
-    v[1] += cnorm2(f);
+  const int tid = threadIdx.x;
+  const IsignTask tk = task[r];
+  const int ks = kstop ? kstop[r] : tk.k;
+  const int k = min(tk.k, ks);
+  double2* xr = x + (long)r * kmax;
+  if (tid == 0 && kout && first) kout[r] = max(k, 0);
+  if (k <= 0) {  // uniform over the workgroup
+    if (first)
+      for (int j = tid; j < kmax; j += 1024) xr[j] = make_double2(0.0, 0.0);
+    if (tid == 0) res[r] = IsignResult{0.0, 0, 0, ks, status ? status[r] : 0};
+    return;
   }
-  block_sum<2>(v, lds);
-  if (threadIdx.x == 0) err[r] = v[1] > 0 ? sqrt(v[0] / v[1]) : 0.0;
+  const int nw0 = (2 * tk.rule[0].nnode + 63) / 64, nw1 = (2 * tk.rule[1].nnode + 63) / 64;
+  int level = -1;
+  double err = 0.0;
+  for (int lev = 0; lev < 2 && level < 0; ++lev) {
+    const int nw = lev ? nw1 : nw0;
+    if (nw == 0) break;
+    double v[2] = {0, 0};
+    for (int j0 = 0; j0 < kmax; j0 += 1024) {
+      const int j = j0 + tid;
+      if (j < kmax) {
+        Cx<double> f = {0, 0}, c = {0, 0};
+        if (j < k) {
+          const double2* p = part + ((long)r * nwave + (lev ? nw0 : 0)) * 2 * kmax + j;
+          int w = 0;
+          for (; w + 8 <= nw; w += 8) {
+            double2 a[8], b[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+              a[u] = p[(long)(w + u) * 2 * kmax];
+              b[u] = p[(long)(w + u) * 2 * kmax + kmax];
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+              f = f + c64(a[u]);
+              c = c + c64(b[u]);
+            }
+          }
+          for (; w < nw; ++w) {
+            f = f + c64(p[(long)w * 2 * kmax]);
+            c = c + c64(p[(long)w * 2 * kmax + kmax]);
+          }
+        }
+        xr[j] = d2(f);
+        sq[0][tid] = cnorm2(f - c);
+        sq[1][tid] = cnorm2(f);
+      }
+      __syncthreads();
+      if (tid < 256)
+        for (int t = tid; t < 1024 && j0 + t < kmax; t += 256) {
+          v[0] += sq[0][t];
+          v[1] += sq[1][t];
+        }
+      __syncthreads();
+    }
+    block_sum<2>(v, lds, 4);
+    if (tid == 0) err_s = v[1] > 0 ? sqrt(v[0] / v[1]) : 0.0;
+    __syncthreads();
+    err = err_s;
+    // NaN stays unaccepted until the finest step
+    if (err <= tk.target || tk.rule[lev].h <= tk.hmin) level = lev;
+    __syncthreads();
+  }
+  if (tid == 0) res[r] = IsignResult{err, level, k, ks, status ? status[r] : 0};
 }
 
 // Hessenberg variant: one workgroup per (source r, shifted solve q), q = q0 +
@@ -982,10 +1035,10 @@ void launch_probe_gather(bool f32, const void* basis, long basis_stride, long N,
                        probes);
 }
 
-void launch_probe_y(const double2* probes, const double2* coef, const int* kvec, int kmax,
-                    const double2* yex, long N, const int* idx, int P, double2* yp, int nrhs,
-                    hipStream_t s) {
-  hipLaunchKernelGGL(k_probe_y, dim3(cdiv_i(P, 64), nrhs), dim3(64), 0, s, probes, coef, kvec,
+void launch_probe_y(const double2* probes, const double2* x, const double* sv, const double* nb,
+                    const int* kvec, int kmax, const double2* yex, long N, const int* idx, int P,
+                    double2* yp, int nrhs, hipStream_t s) {
+  hipLaunchKernelGGL(k_probe_y, dim3(cdiv_i(P, 64), nrhs), dim3(64), 0, s, probes, x, sv, nb, kvec,
                      kmax, yex, N, idx, P, yp);
 }
 
@@ -1099,13 +1152,14 @@ void launch_scale_copy(bool f32, const void* T, void* out, long N, const double*
 int isign_tri_nwave(int nnode) { return cdiv_i(2L * nnode, 64); }
 
 void launch_isign_tri(const double2* alpha, const double* beta, const double2* gamma, int kmax,
-                      const int* kvec, int nrhs, const QuadNodes* rules, int nwave, double2* mult,
-                      unsigned long long* swp, double2* part, double2* x, double* err, hipStream_t s) {
-  const int nw = std::max(nwave, 1);
-  for (int w0 = 0; w0 < nw; w0 += kIsignWaveChunk)
-    hipLaunchKernelGGL(k_isign_tri, dim3(std::min(kIsignWaveChunk, nw - w0), nrhs), dim3(64), 0,
-                       s, alpha, beta, gamma, kmax, kvec, rules, w0, nw, mult, swp, part);
-  hipLaunchKernelGGL(k_isign_final, dim3(nrhs), dim3(256), 0, s, part, nw, kmax, kvec, x, err);
+                      const IsignTask* task, const int* kstop, const int* status, int nrhs,
+                      int nwave, int chunk, bool first, double2* mult, unsigned long long* swp,
+                      double2* part, double2* x, int* kout, IsignResult* res, hipStream_t s) {
+  for (int w0 = 0; w0 < nwave; w0 += chunk)
+    hipLaunchKernelGGL(k_isign_tri, dim3(std::min(chunk, nwave - w0), nrhs), dim3(64), 0, s, alpha,
+                       beta, gamma, kmax, task, kstop, w0, nwave, mult, swp, part);
+  hipLaunchKernelGGL(k_isign_final, dim3(nrhs), dim3(1024), 0, s, part, nwave, kmax, task, kstop,
+                     status, (int)first, x, kout, res);
 }
 
 void launch_isign_hess(const double2* H, int kmax, const int* kvec, int nrhs, double h, int n0,

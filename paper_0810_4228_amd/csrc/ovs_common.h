@@ -108,6 +108,9 @@ struct ovs_lattice_s {
   // cached one-pass Lanczos basis (grown as a solve needs it)
   void* bbuf = nullptr;
   size_t bbuf_bytes = 0;
+  // pinned host memory for the small exchanges of a solve with the device
+  void* pin = nullptr;
+  size_t pin_bytes = 0;
   // results of the last sign_apply (host copies) for diagnostics
   std::vector<double> last_alpha, last_beta, last_gamma, last_x;
   int last_nrhs = 0, last_kmax = 0;

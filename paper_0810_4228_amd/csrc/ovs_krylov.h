@@ -46,9 +46,11 @@ void launch_probe_gather(bool f32, const void* basis, long basis_stride, long N,
                          const int* it, bool first, const int* idx, int P, int kmax,
                          const int* rhs_map, const int* n_active, int nslots, double2* probes,
                          hipStream_t s);
-void launch_probe_y(const double2* probes, const double2* coef, const int* kvec, int kmax,
-                    const double2* yex, long N, const int* idx, int P, double2* yp, int nrhs,
-                    hipStream_t s);
+// yp[r][p]: the result at the sampled entries from the coefficients
+// n_b x[r][i] sv[r][i] (sv null: 1) of the k_r first basis vectors.
+void launch_probe_y(const double2* probes, const double2* x, const double* sv, const double* nb,
+                    const int* kvec, int kmax, const double2* yex, long N, const int* idx, int P,
+                    double2* yp, int nrhs, hipStream_t s);
 
 void launch_make_coef(const double2* x, const double* sv, const double* nb, int kmax, int nrhs,
                       double2* coef, hipStream_t s);
@@ -81,14 +83,11 @@ void launch_scale_copy(bool f32, const void* T, void* out, long N, const double*
                        hipStream_t s);
 
 // Inner sign by the tau = e^u trapezoid rule.  The tridiagonal form runs its
-// shifted solves in launches of at most kIsignWaveChunk waves of 64 solves
-// per source (mult: [nrhs][kIsignWaveChunk][kmax][64]; swp: [nrhs]
-// [kIsignWaveChunk][isign_swp_words(kmax)][64]; part: [nrhs][all waves][2][kmax]); the Hessenberg form kIsignHessChunk solves per source
-// (ys: [nrhs][kIsignHessChunk][kmax]; acc: [nrhs][2][kmax]).  A launch takes
-// about k sequential elimination steps whatever its number of waves, so the
-// chunk holds every solve of the rules down to step 1/16 (43 waves): one
-// launch for those, two at 1/32 and four at 1/64.
-constexpr int kIsignWaveChunk = 48;
+// shifted solves in launches of at most isign_wave_chunk(nrhs) waves of 64
+// solves per source (mult: [nrhs][chunk][kmax][64]; swp: [nrhs][chunk]
+// [isign_swp_words(kmax)][64]; part: [nrhs][all waves][2][kmax]); the Hessenberg
+// form kIsignHessChunk solves per source (ys: [nrhs][kIsignHessChunk][kmax];
+// acc: [nrhs][2][kmax]).
 constexpr int kIsignHessChunk = 1024;
 // A trapezoid rule in u: nodes u = n h for n0 <= n < n0 + nnode.
 struct QuadNodes {
@@ -96,14 +95,36 @@ struct QuadNodes {
   int n0;     // first node index (u = n h)
   int nnode;  // number of nodes
 };
+// What the inner sign of one source tries in a launch: one or two steps (rule[1]
+// is the next finer one, or has no nodes), for its leading k x k block (k = 0:
+// nothing; capped by kstop where that is given).
+struct IsignTask {
+  QuadNodes rule[2];
+  double target, hmin;
+  int k;
+};
+struct IsignResult {
+  double err;   // of the accepted rule (or the last one tried)
+  int level;    // rule accepted, or -1
+  int k, kstop, status;
+};
 int isign_tri_nwave(int nnode);
+// A launch takes about k sequential elimination steps whatever its number of
+// waves, until the waves of a compute unit's SIMDs share their issue slots: the
+// chunk holds every solve of the rules down to step 1/16 (43 waves), and for
+// few sources those of 1/32 (86) or all (171).
+inline int isign_wave_chunk(int nrhs) {
+  const int c = 192 / nrhs;
+  return c < 48 ? 48 : c > 172 ? 172 : c;
+}
 // 64-bit words that hold one swap bit for each of kmax elimination steps
 __host__ __device__ inline int isign_swp_words(int kmax) { return (kmax + 63) / 64; }
-// rules: device array [nrhs], the rule of each source; nwave: the largest
-// isign_tri_nwave over the sources with kvec[r] > 0 (the part stride).
+// task, res: [nrhs] (readable and writable by the device); nwave: the largest
+// number of waves of a source's rules together (the part stride).
 void launch_isign_tri(const double2* alpha, const double* beta, const double2* gamma, int kmax,
-                      const int* kvec, int nrhs, const QuadNodes* rules, int nwave, double2* mult,
-                      unsigned long long* swp, double2* part, double2* x, double* err, hipStream_t s);
+                      const IsignTask* task, const int* kstop, const int* status, int nrhs,
+                      int nwave, int chunk, bool first, double2* mult, unsigned long long* swp,
+                      double2* part, double2* x, int* kout, IsignResult* res, hipStream_t s);
 void launch_isign_hess(const double2* H, int kmax, const int* kvec, int nrhs, double h, int n0,
                        int nnode, double2* ys, double2* acc, double2* x, double* err,
                        hipStream_t s);
