@@ -435,8 +435,18 @@ __global__ void __launch_bounds__(256) k_block_axpy(const T2* __restrict__ basis
   double v[1] = {0.0};
   for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < N; e += (long)gridDim.x * blockDim.x) {
     Cx<double> t = ld64(T + (long)r * N + e);
-    for (int i = 0; i < nvec; ++i)
-      t = t - cmul(c64(hcur[(long)r * kmax + i]), ld64(basis + i * basis_stride + (long)r * N + e));
+    // one term after the other as written, the loads of eight issued together
+    const T2* br = basis + (long)r * N + e;
+    const double2* hr = hcur + (long)r * kmax;
+    int i = 0;
+    for (; i + 8 <= nvec; i += 8) {
+      T2 q[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) q[u] = br[(long)(i + u) * basis_stride];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) t = t - cmul(c64(hr[i + u]), ld64(&q[u]));
+    }
+    for (; i < nvec; ++i) t = t - cmul(c64(hr[i]), ld64(br + (long)i * basis_stride));
     st64(T + (long)r * N + e, t);
     v[0] += cnorm2(round_to(T, t));
   }

@@ -234,10 +234,37 @@ __device__ __forceinline__ bool map_tile(int bid, const TileMap& m, int& site0, 
 }
 
 // ---- deterministic reductions over one workgroup ------------------------
-// Wave64 tree by shuffles, then a fixed-order pass over the waves in LDS.
+// Wave64 tree, then a fixed-order pass over the waves in LDS.
+
+// The value of lane l + OFF, for the lanes l < OFF (OFF 1, 2, 4, 8: row shifts
+// within 16 lanes; 16, 32: row swaps): register moves, no LDS crossbar.
+template <int OFF>
+__device__ __forceinline__ double lane_down(double v) {
+  const int lo = __double2loint(v), hi = __double2hiint(v);
+  if constexpr (OFF == 32) {
+    const auto a = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    const auto b = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    return __hiloint2double(b[1], a[1]);
+  } else if constexpr (OFF == 16) {
+    const auto a = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto b = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    return __hiloint2double(b[1], a[1]);
+  } else {
+    constexpr int kRowShl = 0x100 + OFF;
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, hi, kRowShl, 0xf, 0xf, true),
+                            __builtin_amdgcn_update_dpp(0, lo, kRowShl, 0xf, 0xf, true));
+  }
+}
+// Sum over the 64 lanes, valid in lane 0: the tree of halves (lane + 32, + 16,
+// ... + 1).  Bound by the latency of its six steps: register moves instead of
+// shuffles through LDS.
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+  v += lane_down<32>(v);
+  v += lane_down<16>(v);
+  v += lane_down<8>(v);
+  v += lane_down<4>(v);
+  v += lane_down<2>(v);
+  v += lane_down<1>(v);
   return v;
 }
 

@@ -114,7 +114,7 @@ int isign_tri_nwave(int nnode);
 // chunk holds every solve of the rules down to step 1/16 (43 waves), and for
 // few sources those of 1/32 (86) or all (171).
 inline int isign_wave_chunk(int nrhs) {
-  const int c = 192 / nrhs;
+  const int c = 512 / nrhs;
   return c < 48 ? 48 : c > 172 ? 172 : c;
 }
 // 64-bit words that hold one swap bit for each of kmax elimination steps
