@@ -4,10 +4,10 @@
 //
 // The driver (gradient.cpp) runs the Lanczos recurrences forward storing the
 // FP64 bases V, W (or checkpoints), then walks them backwards.  Every vector
-// step is a short linear combination of stored fields with fused dot
-// products (k_lin, k_lin_multi); the per-source scalar steps mostly run at
-// the start of the combination launch that uses their coefficient rows
-// (k_lin_step, k_lin_multi_step); the pairs of A and A^dagger applications
+// step is a pass over stored fields, short linear combinations with fused dot
+// products (k_pass_*; k_lin, k_lin_multi for the first and last steps); the
+// per-source scalar steps run at the start of the pass that uses their
+// coefficient rows; the pairs of A and A^dagger applications
 // are the dual stencil; the link and mu derivatives are accumulated by
 // k_gforce (one step) and k_gforce_group (a group of steps).  Reductions
 // are fixed-order.
@@ -31,24 +31,13 @@ int lin_nchunk(long stride) {
   return (int)c;
 }
 
-// TAB: the launch ran a scalar step whose coefficient rows are in `tab`
-// (LDS); a combination with a.tab >= 0 takes them from there instead of the
-// global table a.coef.
-template <bool TAB>
-__device__ __forceinline__ void lin_body(const LinArgs& a, long stride, int nrhs, double* lds,
-                                         const double2 (*tab)[kLinTerms]) {
+__device__ __forceinline__ void lin_body(const LinArgs& a, long stride, int nrhs, double* lds) {
   const int r = blockIdx.y;
   const long off = (long)r * stride;
   Cx<double> c[kLinTerms];
-  if (TAB && a.tab >= 0) {
 #pragma unroll
-    for (int j = 0; j < kLinTerms; ++j)
-      c[j] = (j < a.nterm) ? c64(tab[a.tab][j]) : Cx<double>{0.0, 0.0};
-  } else {
-#pragma unroll
-    for (int j = 0; j < kLinTerms; ++j)
-      c[j] = (j < a.nterm) ? c64(a.coef[(long)j * nrhs + r]) : Cx<double>{0.0, 0.0};
-  }
+  for (int j = 0; j < kLinTerms; ++j)
+    c[j] = (j < a.nterm) ? c64(a.coef[(long)j * nrhs + r]) : Cx<double>{0.0, 0.0};
   double part[2 * kLinDots];
 #pragma unroll
   for (int q = 0; q < 2 * kLinDots; ++q) part[q] = 0.0;
@@ -80,7 +69,7 @@ __device__ __forceinline__ void lin_body(const LinArgs& a, long stride, int nrhs
 
 __global__ void __launch_bounds__(kWG) k_lin(LinArgs a, long stride, int nrhs) {
   __shared__ double lds[(kWG / 64) * 2 * kLinDots];
-  lin_body<false>(a, stride, nrhs, lds, nullptr);
+  lin_body(a, stride, nrhs, lds);
 }
 
 // Several linear combinations in one launch: each is computed as k_lin
@@ -93,7 +82,7 @@ __global__ void __launch_bounds__(kWG) k_lin_multi(LinMulti m, long stride, int 
   __shared__ double lds[(kWG / 64) * 2 * kLinDots];
   for (int j = 0; j < m.n; ++j) {
     __syncthreads();  // lds of the previous combination
-    lin_body<false>(m.a[j], stride, nrhs, lds, nullptr);
+    lin_body(m.a[j], stride, nrhs, lds);
   }
 }
 
@@ -145,11 +134,11 @@ __device__ __forceinline__ void set_coef(const GradScalars& s, int t, int j, int
 }
 
 // Where a scalar step puts the coefficient rows it forms for source r: the
-// LDS table of the linear combination that follows it in the same launch
+// LDS table of the pass that follows it in the same launch
 // (`lds`, read by all of that launch's threads), and/or the global tables
 // (`coef`) for later launches.  `wr`: the step also writes its scalars
-// (alpha, beta, ...) to global memory; in a combination launch only its
-// first workgroup of each source does.
+// (alpha, beta, ...) to global memory; in a pass only its first workgroup
+// of each source does.
 struct TabOut {
   double2 (*lds)[kLinTerms];
   double2* coef;
@@ -463,7 +452,7 @@ __device__ void gp_coef_rows(const GradScalars& s, int i, const TabOut& o) {
 }
 
 
-// ---- linear combinations preceded by their scalar step ------------------------
+// ---- passes preceded by their scalar step --------------------------------------
 // Every workgroup of source r forms the step's coefficient rows itself (the
 // same dot sums in the same order, kWG = kScalarWG threads, so the same
 // values as the separate scalar kernel) and keeps them in LDS; the first
@@ -474,8 +463,7 @@ __device__ void gp_coef_rows(const GradScalars& s, int i, const TabOut& o) {
 // workgroup of the launch reads.
 __device__ void run_step(const ScalarStep& st, double2 (*tab)[kLinTerms]) {
   const bool first = blockIdx.x == 0;
-  const TabOut o{tab, (st.global_tabs && first) ? st.s.coef : nullptr, st.s.nrhs, (int)blockIdx.y,
-                 first};
+  const TabOut o{tab, nullptr, st.s.nrhs, (int)blockIdx.y, first};
   switch (st.kind) {
     case kStepAlpha: step_gf_alpha(st.s, st.i, st.pa, st.nchunk, o); break;
     case kStepBeta: step_gf_beta(st.s, st.i, st.pa, st.pb, st.nchunk, o); break;
@@ -490,33 +478,322 @@ __device__ void run_step(const ScalarStep& st, double2 (*tab)[kLinTerms]) {
   __syncthreads();  // the rows in LDS for every thread
 }
 
-__global__ void __launch_bounds__(kWG) k_lin_step(LinArgs a, long stride, int nrhs, ScalarStep st) {
-  __shared__ double lds[(kWG / 64) * 2 * kLinDots];
-  __shared__ double2 tab[kCoefTables][kLinTerms];
-  run_step(st, tab);
-  lin_body<true>(a, stride, nrhs, lds, tab);
+// ---- the vector passes of a Lanczos step and of its reverse -----------------------
+// One kernel per pass, each doing what launches of k_lin with the same
+// coefficient rows and dots do, bit for bit (every output element and every
+// thread's share of a dot by the same operations in the same order, the same
+// grid).  An element's loads are all issued before its arithmetic, the first
+// element's before the scalar step, the next one's before the current one's
+// stores: on small lattices a pass is one memory latency, the dot sums of the
+// scalar step and one reduction, on large ones it streams.  (A general kernel
+// over a run-time list of combinations waited for each term's load in turn and
+// for its arguments: the five passes of a step took 9.1 us on average at 8^4 and
+// 27 us at 16^4.)
+
+// Sweeps this workgroup's elements: cur holds the first one's loads.
+template <class E, class Fetch, class Body>
+__device__ __forceinline__ void sweep(long stride, E& cur, Fetch fetch, Body body) {
+  long e = (long)blockIdx.x * kWG + threadIdx.x;
+  while (e < stride) {
+    const E c = cur;
+    const long n = e + (long)gridDim.x * kWG;
+    if (n < stride) fetch(n, cur);
+    body(e, c);
+    e = n;
+  }
+}
+template <class E, class Fetch>
+__device__ __forceinline__ void sweep_begin(long stride, E& cur, Fetch fetch) {
+  const long e = (long)blockIdx.x * kWG + threadIdx.x;
+  if (e < stride) fetch(e, cur);
 }
 
-__global__ void __launch_bounds__(kWG) k_lin_multi_step(LinMulti m, long stride, int nrhs,
-                                                        ScalarStep st) {
-  __shared__ double lds[(kWG / 64) * 2 * kLinDots];
-  __shared__ double2 tab[kCoefTables][kLinTerms];
-  run_step(st, tab);
-  for (int j = 0; j < m.n; ++j) {
-    __syncthreads();  // lds of the previous combination
-    lin_body<true>(m.a[j], stride, nrhs, lds, tab);
+// Adds conj(y) v to a dot's running sums.
+__device__ __forceinline__ void dot_acc(double* p, Cx<double> y, Cx<double> v) {
+  const Cx<double> d = cmulc(y, v);
+  p[0] += d.re;
+  p[1] += d.im;
+}
+
+// The workgroup's share of two dots to the partials of source r.
+__device__ __forceinline__ void put_dots(double (&part)[2 * kLinDots], double* lds,
+                                         double* partials) {
+  block_sum<2 * kLinDots>(part, lds);
+  if (threadIdx.x == 0) {
+    double* dst = partials + ((long)blockIdx.y * gridDim.x + blockIdx.x) * 2 * kLinDots;
+#pragma unroll
+    for (int q = 0; q < 2 * kLinDots; ++q) dst[q] = part[q];
   }
 }
 
-void launch_lin_step(const LinArgs& a, long stride, int nrhs, const ScalarStep& st, hipStream_t s) {
-  hipLaunchKernelGGL(k_lin_step, dim3(lin_nchunk(stride), nrhs), dim3(kWG), 0, s, a, stride, nrhs,
-                     st);
+// Dots w^dagger t and |t|^2; the first workgroup of a source also runs the step
+// (xbar of the iteration, from the previous pass's dots).
+__global__ void __launch_bounds__(kWG) k_pass_dots(const double2* t, const double2* w,
+                                                   double* partials, long stride, ScalarStep st) {
+  __shared__ double lds[(kWG / 64) * 2 * kLinDots];
+  const long off = (long)blockIdx.y * stride;
+  struct E {
+    double2 t, w;
+  } cur;
+  auto fetch = [&](long e, E& v) {
+    v.t = t[off + e];
+    v.w = w[off + e];
+  };
+  sweep_begin(stride, cur, fetch);
+  if (st.kind == kStepXbar && blockIdx.x == 0) run_step(st, nullptr);
+  double part[2 * kLinDots] = {0.0, 0.0, 0.0, 0.0};
+  sweep(stride, cur, fetch, [&](long, const E& c) {
+    // the combination 1 t
+    const Cx<double> v = cfma(Cx<double>{1.0, 0.0}, c64(c.t), Cx<double>{0.0, 0.0});
+    dot_acc(part, c64(c.w), v);
+    dot_acc(part + 2, v, v);
+  });
+  put_dots(part, lds, partials);
 }
-void launch_lin_multi_step(const LinMulti& m, long stride, int nrhs, const ScalarStep& st,
-                           hipStream_t s) {
-  hipLaunchKernelGGL(k_lin_multi_step, dim3(lin_nchunk(stride), nrhs), dim3(kWG), 0, s, m, stride,
-                     nrhs, st);
+
+struct StepElem {
+  double2 t, v, vm, s, w, wm;
+};
+__device__ __forceinline__ void fetch_step(const StepFields& f, long e, StepElem& c) {
+  c.t = f.t[e];
+  c.v = f.v[e];
+  c.s = f.s[e];
+  c.w = f.w[e];
+  if (f.vm) {
+    c.vm = f.vm[e];
+    c.wm = f.wm[e];
+  }
 }
+__device__ __forceinline__ void step_vectors(const StepFields& f, const StepElem& c,
+                                             const double2 (*tab)[kLinTerms], Cx<double>& v,
+                                             Cx<double>& w) {
+  const Cx<double> zero = {0.0, 0.0};
+  v = cfma(c64(tab[kTabV][1]), c64(c.v), cfma(c64(tab[kTabV][0]), c64(c.t), zero));
+  w = cfma(c64(tab[kTabW][1]), c64(c.w), cfma(c64(tab[kTabW][0]), c64(c.s), zero));
+  if (f.vm) {
+    v = cfma(c64(tab[kTabV][2]), c64(c.vm), v);
+    w = cfma(c64(tab[kTabW][2]), c64(c.wm), w);
+  }
+}
+
+// alpha, then v~ and w~ with |v~|^2 (pv), v~^dagger w~ and |w~|^2 (pw).
+__global__ void __launch_bounds__(kWG) k_pass_update(StepFields f, double2* vn, double2* wn,
+                                                     double* pv, double* pw, long stride,
+                                                     ScalarStep st) {
+  __shared__ double lds[(kWG / 64) * 2 * kLinDots];
+  __shared__ double2 tab[kCoefTables][kLinTerms];
+  const long off = (long)blockIdx.y * stride;
+  StepElem cur;
+  auto fetch = [&](long e, StepElem& c) { fetch_step(f, off + e, c); };
+  sweep_begin(stride, cur, fetch);
+  run_step(st, tab);
+  double a[2 * kLinDots] = {0.0, 0.0, 0.0, 0.0}, b[2 * kLinDots] = {0.0, 0.0, 0.0, 0.0};
+  sweep(stride, cur, fetch, [&](long e, const StepElem& c) {
+    Cx<double> v, w;
+    step_vectors(f, c, tab, v, w);
+    vn[off + e] = d2(v);
+    wn[off + e] = d2(w);
+    dot_acc(a, v, v);
+    dot_acc(b, v, w);
+    dot_acc(b + 2, w, w);
+  });
+  put_dots(a, lds, pv);
+  put_dots(b, lds, pw);
+}
+
+// beta and gamma, then the normalisation of v~ and w~ in place with chi^dagger v
+// (chi null: no dot).
+__global__ void __launch_bounds__(kWG) k_pass_norm(double2* vn, double2* wn, const double2* chi,
+                                                   double* pchi, long stride, ScalarStep st) {
+  __shared__ double lds[(kWG / 64) * 2 * kLinDots];
+  __shared__ double2 tab[kCoefTables][kLinTerms];
+  const long off = (long)blockIdx.y * stride;
+  struct E {
+    double2 v, w, chi;
+  } cur;
+  auto fetch = [&](long e, E& c) {
+    c.v = vn[off + e];
+    c.w = wn[off + e];
+    if (chi) c.chi = chi[off + e];
+  };
+  sweep_begin(stride, cur, fetch);
+  run_step(st, tab);
+  const Cx<double> cv = c64(tab[kTabSV][0]), cw = c64(tab[kTabSW][0]);
+  double part[2 * kLinDots] = {0.0, 0.0, 0.0, 0.0};
+  sweep(stride, cur, fetch, [&](long e, const E& c) {
+    const Cx<double> v = cfma(cv, c64(c.v), Cx<double>{0.0, 0.0});
+    vn[off + e] = d2(v);
+    wn[off + e] = d2(cfma(cw, c64(c.w), Cx<double>{0.0, 0.0}));
+    if (chi) dot_acc(part, c64(c.chi), v);
+  });
+  if (chi) put_dots(part, lds, pchi);
+}
+
+// The replayed step: v~, w~ and their normalisation with the stored rows.
+__global__ void __launch_bounds__(kWG) k_pass_replay(StepFields f, double2* vn, double2* wn,
+                                                     long stride, ScalarStep st) {
+  __shared__ double2 tab[kCoefTables][kLinTerms];
+  const long off = (long)blockIdx.y * stride;
+  StepElem cur;
+  auto fetch = [&](long e, StepElem& c) { fetch_step(f, off + e, c); };
+  sweep_begin(stride, cur, fetch);
+  run_step(st, tab);
+  const Cx<double> cv = c64(tab[kTabSV][0]), cw = c64(tab[kTabSW][0]);
+  sweep(stride, cur, fetch, [&](long e, const StepElem& c) {
+    Cx<double> v, w;
+    step_vectors(f, c, tab, v, w);
+    vn[off + e] = d2(cfma(cv, v, Cx<double>{0.0, 0.0}));
+    wn[off + e] = d2(cfma(cw, w, Cx<double>{0.0, 0.0}));
+  });
+}
+
+// Reverse step 1.
+__global__ void __launch_bounds__(kWG) k_pass_rev1(Rev1Fields f, double* pv, double* pw,
+                                                   long stride, ScalarStep st) {
+  __shared__ double lds[(kWG / 64) * 2 * kLinDots];
+  __shared__ double2 tab[kCoefTables][kLinTerms];
+  const long off = (long)blockIdx.y * stride;
+  struct E {
+    double2 vb, v1, w1, wb, v, vm, w, wm;
+  } cur;
+  auto fetch = [&](long e, E& c) {
+    c.vb = f.vb[off + e];
+    c.v1 = f.v1[off + e];
+    c.w1 = f.w1[off + e];
+    c.wb = f.wb[off + e];
+    c.v = f.v[off + e];
+    c.w = f.w[off + e];
+    if (f.vm) {
+      c.vm = f.vm[off + e];
+      c.wm = f.wm[off + e];
+    }
+  };
+  sweep_begin(stride, cur, fetch);
+  run_step(st, tab);
+  double a[2 * kLinDots] = {0.0, 0.0, 0.0, 0.0}, b[2 * kLinDots] = {0.0, 0.0, 0.0, 0.0};
+  sweep(stride, cur, fetch, [&](long e, const E& c) {
+    const Cx<double> zero = {0.0, 0.0};
+    Cx<double> v = cfma(c64(tab[kTabV][0]), c64(c.vb), zero);
+    v = cfma(c64(tab[kTabV][1]), c64(c.v1), v);
+    v = cfma(c64(tab[kTabV][2]), c64(c.w1), v);
+    Cx<double> w = cfma(c64(tab[kTabW][0]), c64(c.wb), zero);
+    w = cfma(c64(tab[kTabW][1]), c64(c.v1), w);
+    f.vtb[off + e] = d2(v);
+    f.sb[off + e] = d2(w);
+    dot_acc(a, c64(c.v), v);
+    dot_acc(b, c64(c.w), w);
+    if (f.vm) {
+      dot_acc(a + 2, c64(c.vm), v);
+      dot_acc(b + 2, c64(c.wm), w);
+    }
+  });
+  put_dots(a, lds, pv);
+  put_dots(b, lds, pw);
+}
+
+// Reverse step 2.
+__global__ void __launch_bounds__(kWG) k_pass_rev2(Rev2Fields f, long stride, ScalarStep st) {
+  __shared__ double2 tab[kCoefTables][kLinTerms];
+  const long off = (long)blockIdx.y * stride;
+  struct E {
+    double2 vtb, vtbn, w, chi, sbn, sb, v1, v, vm, ya;
+  } cur;
+  auto fetch = [&](long e, E& c) {
+    c.vtb = f.vtb[off + e];
+    c.vtbn = f.vtbn[off + e];
+    c.w = f.w[off + e];
+    c.chi = f.chi[off + e];
+    c.sbn = f.sbn[off + e];
+    c.sb = f.sb[off + e];
+    c.v1 = f.v1[off + e];
+    c.v = f.v[off + e];
+    if (f.vm) c.vm = f.vm[off + e];
+    if (f.ya) c.ya = f.ya[off + e];
+  };
+  sweep_begin(stride, cur, fetch);
+  run_step(st, tab);
+  sweep(stride, cur, fetch, [&](long e, const E& c) {
+    const Cx<double> zero = {0.0, 0.0};
+    Cx<double> t = cfma(c64(tab[kTabSV][0]), c64(c.vtb), zero);
+    t = cfma(c64(tab[kTabSV][1]), c64(c.w), t);
+    Cx<double> v = cfma(c64(tab[kTabSW][0]), c64(c.chi), zero);
+    v = cfma(c64(tab[kTabSW][1]), c64(c.vtbn), v);
+    v = cfma(c64(tab[kTabSW][2]), c64(c.vtb), v);
+    Cx<double> w = cfma(c64(tab[kTabWB][0]), c64(c.sbn), zero);
+    w = cfma(c64(tab[kTabWB][1]), c64(c.sb), w);
+    w = cfma(c64(tab[kTabWB][2]), c64(c.v1), w);
+    w = cfma(c64(tab[kTabWB][3]), c64(c.v), w);
+    if (f.vm) w = cfma(c64(tab[kTabWB][4]), c64(c.vm), w);
+    f.tb[off + e] = d2(t);
+    f.vb[off + e] = d2(v);
+    f.wb[off + e] = d2(w);
+    if (f.ya) f.ya[off + e] = d2(cfma(c64(tab[kTabY][0]), c64(c.v), c64(c.ya)));
+  });
+}
+
+// vbar += A^dagger tbar and wbar += A sbar with their dots with v_i and w_i.
+__global__ void __launch_bounds__(kWG) k_pass_add(double2* vb, const double2* t1, const double2* v,
+                                                  double* pv, double2* wb, const double2* t2,
+                                                  const double2* w, double* pw, long stride) {
+  __shared__ double lds[(kWG / 64) * 2 * kLinDots];
+  const long off = (long)blockIdx.y * stride;
+  struct E {
+    double2 vb, t1, v, wb, t2, w;
+  } cur;
+  auto fetch = [&](long e, E& c) {
+    c.vb = vb[off + e];
+    c.t1 = t1[off + e];
+    c.v = v[off + e];
+    c.wb = wb[off + e];
+    c.t2 = t2[off + e];
+    c.w = w[off + e];
+  };
+  sweep_begin(stride, cur, fetch);
+  double a[2 * kLinDots] = {0.0, 0.0, 0.0, 0.0}, b[2 * kLinDots] = {0.0, 0.0, 0.0, 0.0};
+  sweep(stride, cur, fetch, [&](long e, const E& c) {
+    const Cx<double> one = {1.0, 0.0};
+    const Cx<double> x = cfma(one, c64(c.t1), c64(c.vb)), y = cfma(one, c64(c.t2), c64(c.wb));
+    vb[off + e] = d2(x);
+    wb[off + e] = d2(y);
+    dot_acc(a, c64(c.v), x);
+    dot_acc(b, c64(c.w), y);
+  });
+  put_dots(a, lds, pv);
+  put_dots(b, lds, pw);
+}
+
+#define OVS_PASS(kernel, ...) \
+  hipLaunchKernelGGL(kernel, dim3(lin_nchunk(stride), nrhs), dim3(kWG), 0, s, __VA_ARGS__)
+void launch_pass_dots(const double2* t, const double2* w, double* partials, long stride, int nrhs,
+                      const ScalarStep& st, hipStream_t s) {
+  OVS_PASS(k_pass_dots, t, w, partials, stride, st);
+}
+void launch_pass_update(const StepFields& f, double2* vn, double2* wn, double* pv, double* pw,
+                        long stride, int nrhs, const ScalarStep& st, hipStream_t s) {
+  OVS_PASS(k_pass_update, f, vn, wn, pv, pw, stride, st);
+}
+void launch_pass_norm(double2* vn, double2* wn, const double2* chi, double* pchi, long stride,
+                      int nrhs, const ScalarStep& st, hipStream_t s) {
+  OVS_PASS(k_pass_norm, vn, wn, chi, pchi, stride, st);
+}
+void launch_pass_replay(const StepFields& f, double2* vn, double2* wn, long stride, int nrhs,
+                        const ScalarStep& st, hipStream_t s) {
+  OVS_PASS(k_pass_replay, f, vn, wn, stride, st);
+}
+void launch_pass_rev1(const Rev1Fields& f, double* pv, double* pw, long stride, int nrhs,
+                      const ScalarStep& st, hipStream_t s) {
+  OVS_PASS(k_pass_rev1, f, pv, pw, stride, st);
+}
+void launch_pass_rev2(const Rev2Fields& f, long stride, int nrhs, const ScalarStep& st,
+                      hipStream_t s) {
+  OVS_PASS(k_pass_rev2, f, stride, st);
+}
+void launch_pass_add(double2* vb, const double2* t1, const double2* v, double* pv, double2* wb,
+                     const double2* t2, const double2* w, double* pw, long stride, int nrhs,
+                     hipStream_t s) {
+  OVS_PASS(k_pass_add, vb, t1, v, pv, wb, t2, w, pw, stride);
+}
+#undef OVS_PASS
 
 // ---- inner sign and its vector-Jacobian product -----------------------------------
 // One thread per (node, sign): LU with row interchanges of the tridiagonal

@@ -338,20 +338,7 @@ static ovs_status vjp_impl(ovs_lattice l, ovs_deflation defl, int32_t n_defl, co
                   std::initializer_list<const double2*> ys, int ndot, double* part) {
     launch_lin(mks(S2, xs, tab, out, acc, ys, ndot, part), F, nrhs, l->stream);
   };
-  // independent combinations (none reads another's output) in one launch
-  auto multi = [&](std::initializer_list<LinArgs> las) {
-    LinMulti m;
-    for (const LinArgs& a : las) m.a[m.n++] = a;
-    launch_lin_multi(m, F, nrhs, l->stream);
-  };
-  // a combination whose coefficients come from the scalar step run at the
-  // start of the same launch (table `tab` of the step)
-  auto from_step = [](LinArgs a, int tab) {
-    a.tab = tab;
-    return a;
-  };
-  auto step_of_s = [&](const GradScalars& Sx, int kind, int i, const double* pa, const double* pb,
-                       bool global_tabs) {
+  auto step_of_s = [&](const GradScalars& Sx, int kind, int i, const double* pa, const double* pb) {
     ScalarStep st;
     st.kind = kind;
     st.i = i;
@@ -359,16 +346,10 @@ static ovs_status vjp_impl(ovs_lattice l, ovs_deflation defl, int32_t n_defl, co
     st.pb = pb;
     st.nchunk = nch;
     st.s = Sx;
-    st.global_tabs = global_tabs ? 1 : 0;
     return st;
   };
-  auto step_of = [&](int kind, int i, const double* pa, const double* pb, bool global_tabs) {
-    return step_of_s(S, kind, i, pa, pb, global_tabs);
-  };
-  auto multi_step = [&](const ScalarStep& st, std::initializer_list<LinArgs> las) {
-    LinMulti m;
-    for (const LinArgs& a : las) m.a[m.n++] = a;
-    launch_lin_multi_step(m, F, nrhs, st, l->stream);
+  auto step_of = [&](int kind, int i, const double* pa, const double* pb) {
+    return step_of_s(S, kind, i, pa, pb);
   };
   auto copy = [&](double2* dst, const double2* src) {
     return hipMemcpyAsync(dst, src, sizeof(double2) * NF, hipMemcpyDeviceToDevice, l->stream);
@@ -415,38 +396,26 @@ static ovs_status vjp_impl(ovs_lattice l, ovs_deflation defl, int32_t n_defl, co
     lin({B}, kTabNorm, Wf(0), false, {}, 0, nullptr);
   }
   OVS_HIP(save_ckpt(0));
-  // Each step's scalar kernels (alpha, beta, xbar) run at the start of the
-  // combination launch that follows them (launch_lin_step): five launches
-  // per step.
+  // Each step's scalar kernels (alpha, beta, xbar) run at the start of the pass
+  // that follows them: four launches per step.
   for (int i = 0; i < k; ++i) {
     if (i < k - 1) OVS_HIP(applyBoth(Vf(i), Wf(i), T, Sv));
     else OVS_HIP(applyA(Vf(i), T));
     // dots w_i^dagger t, |t|^2; xbar_i from the previous step's chi^dagger v_i
-    if (i > 0)
-      launch_lin_step(mk({T}, kTabOne, nullptr, false, {Wf(i), nullptr}, 2, P[0]), F, nrhs,
-                      step_of(kStepXbar, i, P[3], nullptr, false), l->stream);
-    else
-      lin({T}, kTabOne, nullptr, false, {Wf(i), nullptr}, 2, P[0]);
+    launch_pass_dots(T, Wf(i), P[0], F, nrhs, step_of(i > 0 ? kStepXbar : kStepNone, i, P[3], nullptr),
+                     l->stream);
     if (i == k - 1) {
       launch_gf_alpha(S, i, P[0], nch, l->stream);
       break;
     }
-    // alpha_i (written by workgroup 0), then v~ and w~ in one launch (the dot
-    // v~^dagger w~ reads v~ at the element the same thread has just written)
-    const ScalarStep sa = step_of(kStepAlpha, i, P[0], nullptr, false);
-    if (i > 0)
-      multi_step(sa, {from_step(mk({T, Vf(i), Vf(i - 1)}, kTabV, Vf(i + 1), false, {nullptr}, 1,
-                                   P[1]), kTabV),
-                      from_step(mk({Sv, Wf(i), Wf(i - 1)}, kTabW, Wf(i + 1), false,
-                                   {Vf(i + 1), nullptr}, 2, P[2]), kTabW)});
-    else
-      multi_step(sa, {from_step(mk({T, Vf(i)}, kTabV, Vf(i + 1), false, {nullptr}, 1, P[1]), kTabV),
-                      from_step(mk({Sv, Wf(i)}, kTabW, Wf(i + 1), false, {Vf(i + 1), nullptr}, 2,
-                                   P[2]), kTabW)});
-    // beta_i, gamma_i, then the normalisation
-    multi_step(step_of(kStepBeta, i, P[1], P[2], false),
-               {from_step(mk({Vf(i + 1)}, kTabSV, Vf(i + 1), false, {CHI}, 1, P[3]), kTabSV),
-                from_step(mk({Wf(i + 1)}, kTabSW, Wf(i + 1), false, {}, 0, nullptr), kTabSW)});
+    // alpha_i (written by workgroup 0), then v~ and w~; beta_i, gamma_i, then
+    // the normalisation
+    launch_pass_update(StepFields{T, Vf(i), i > 0 ? Vf(i - 1) : nullptr, Sv, Wf(i),
+                                  i > 0 ? Wf(i - 1) : nullptr},
+                       Vf(i + 1), Wf(i + 1), P[1], P[2], F, nrhs,
+                       step_of(kStepAlpha, i, P[0], nullptr), l->stream);
+    launch_pass_norm(Vf(i + 1), Wf(i + 1), CHI, P[3], F, nrhs, step_of(kStepBeta, i, P[1], P[2]),
+                     l->stream);
     OVS_HIP(save_ckpt(i + 1));
   }
   OVS_HIP(copy(TL, T));  // t_k = A v_k, needed by the first reverse step
@@ -599,26 +568,18 @@ static ovs_status vjp_impl(ovs_lattice l, ovs_deflation defl, int32_t n_defl, co
     for (int i = 0; i < k; ++i) {
       if (i < k - 1) OVS_HIP(applyBoth(W2(i), V2(i), Sv, T));
       else OVS_HIP(applyAd(V2(i), T));
-      lin2({T}, kTabOne, nullptr, false, {W2(i), nullptr}, 2, P[0]);
+      launch_pass_dots(T, W2(i), P[0], F, nrhs, step_of_s(S2, kStepNone, i, nullptr, nullptr),
+                       l->stream);
       if (i == k - 1) {
         launch_gf_alpha(S2, i, P[0], nch, l->stream);
         break;
       }
-      const ScalarStep sa = step_of_s(S2, kStepAlpha, i, P[0], nullptr, false);
-      if (i > 0)
-        multi_step(sa, {from_step(mks(S2, {T, V2(i), V2(i - 1)}, kTabV, V2(i + 1), false, {nullptr},
-                                      1, P[1]), kTabV),
-                        from_step(mks(S2, {Sv, W2(i), W2(i - 1)}, kTabW, W2(i + 1), false,
-                                      {V2(i + 1), nullptr}, 2, P[2]), kTabW)});
-      else
-        multi_step(sa, {from_step(mks(S2, {T, V2(i)}, kTabV, V2(i + 1), false, {nullptr}, 1, P[1]),
-                                  kTabV),
-                        from_step(mks(S2, {Sv, W2(i)}, kTabW, W2(i + 1), false,
-                                      {V2(i + 1), nullptr}, 2, P[2]), kTabW)});
-      multi_step(step_of_s(S2, kStepBeta, i, P[1], P[2], false),
-                 {from_step(mks(S2, {V2(i + 1)}, kTabSV, V2(i + 1), false, {}, 0, nullptr), kTabSV),
-                  from_step(mks(S2, {W2(i + 1)}, kTabSW, W2(i + 1), false, {}, 0, nullptr),
-                            kTabSW)});
+      launch_pass_update(StepFields{T, V2(i), i > 0 ? V2(i - 1) : nullptr, Sv, W2(i),
+                                    i > 0 ? W2(i - 1) : nullptr},
+                         V2(i + 1), W2(i + 1), P[1], P[2], F, nrhs,
+                         step_of_s(S2, kStepAlpha, i, P[0], nullptr), l->stream);
+      launch_pass_norm(V2(i + 1), W2(i + 1), nullptr, nullptr, F, nrhs,
+                       step_of_s(S2, kStepBeta, i, P[1], P[2]), l->stream);
     }
     OVS_HIP(hipGetLastError());
     OVS_HIP(hipMemcpyAsync(status.data(), S2.status, sizeof(int) * nrhs, hipMemcpyDeviceToHost,
@@ -732,25 +693,11 @@ static ovs_status vjp_impl(ovs_lattice l, ovs_deflation defl, int32_t n_defl, co
       OVS_HIP(copy(Wr(lo), P_.ckW + (size_t)(2 * j + 1) * NF));
       for (int i = lo; i < top; ++i) {
         // the rows of step i from the stored coefficients, formed in each launch
-        // and v~, w~ and their normalisation in one launch (the scaling reads
-        // each element the same thread has just written)
-        const ScalarStep sc = step_of(kStepCoef, i, nullptr, nullptr, false);
         OVS_HIP(applyBoth(Vr(i), Wr(i), T, Sv));
-        const LinArgs nv =
-            from_step(mk({Vr(i + 1)}, kTabSV, Vr(i + 1), false, {}, 0, nullptr), kTabSV);
-        const LinArgs nw =
-            from_step(mk({Wr(i + 1)}, kTabSW, Wr(i + 1), false, {}, 0, nullptr), kTabSW);
-        if (i > 0)
-          multi_step(sc, {from_step(mk({T, Vr(i), Vr(i - 1)}, kTabV, Vr(i + 1), false, {}, 0,
-                                       nullptr), kTabV),
-                          from_step(mk({Sv, Wr(i), Wr(i - 1)}, kTabW, Wr(i + 1), false, {}, 0,
-                                       nullptr), kTabW),
-                          nv, nw});
-        else
-          multi_step(sc, {from_step(mk({T, Vr(i)}, kTabV, Vr(i + 1), false, {}, 0, nullptr), kTabV),
-                          from_step(mk({Sv, Wr(i)}, kTabW, Wr(i + 1), false, {}, 0, nullptr),
-                                    kTabW),
-                          nv, nw});
+        launch_pass_replay(StepFields{T, Vr(i), i > 0 ? Vr(i - 1) : nullptr, Sv, Wr(i),
+                                      i > 0 ? Wr(i - 1) : nullptr},
+                           Vr(i + 1), Wr(i + 1), F, nrhs, step_of(kStepCoef, i, nullptr, nullptr),
+                           l->stream);
       }
     }
     for (int i = hi; i >= lo; --i) {
@@ -771,36 +718,19 @@ static ovs_status vjp_impl(ovs_lattice l, ovs_deflation defl, int32_t n_defl, co
       }
       const int c = i & 1, p = (i + 1) & 1;
       // step 1 of the reverse scalars (from the dots of vbar_{i+1}, wbar_{i+1})
-      const ScalarStep s1 = step_of(kStepS1, i, P[2], P[3], false);
       double2* const tbi = TBc(i);
       double2* const sbi = WTBc(i);
       const double2* const sbn = WTBc(i + 1);  // sbar_{i+1}
-      if (i > 0)
-        multi_step(s1, {from_step(mk({VB[p], Vr(i + 1), Wr(i + 1)}, kTabV, VTB[c], false,
-                                     {Vr(i), Vr(i - 1)}, 2, P[0]), kTabV),
-                        from_step(mk({WB[p], Vr(i + 1)}, kTabW, sbi, false,
-                                     {Wr(i), Wr(i - 1)}, 2, P[1]), kTabW)});
-      else
-        multi_step(s1, {from_step(mk({VB[p], Vr(i + 1), Wr(i + 1)}, kTabV, VTB[c], false, {Vr(i)},
-                                     1, P[0]), kTabV),
-                        from_step(mk({WB[p], Vr(i + 1)}, kTabW, sbi, false, {Wr(i)}, 1, P[1]),
-                                  kTabW)});
+      const double2* const vm = i > 0 ? Vr(i - 1) : nullptr;
+      launch_pass_rev1(Rev1Fields{VB[p], Vr(i + 1), Wr(i + 1), WB[p], Vr(i), vm, Wr(i),
+                                  i > 0 ? Wr(i - 1) : nullptr, VTB[c], sbi},
+                       P[0], P[1], F, nrhs, step_of(kStepS1, i, P[2], P[3]), l->stream);
       // step 2 (abar_i; bbar_{i-1}, gbar_{i-1} written by workgroup 0)
-      LinMulti m2;
-      m2.a[m2.n++] = from_step(mk({VTB[c], Wr(i)}, kTabSV, tbi, false, {}, 0, nullptr), kTabSV);
-      m2.a[m2.n++] = from_step(mk({CHI, VTB[p], VTB[c]}, kTabSW, VB[c], false, {}, 0, nullptr),
-                               kTabSW);
-      if (i > 0)
-        m2.a[m2.n++] = from_step(mk({sbn, sbi, Vr(i + 1), Vr(i), Vr(i - 1)}, kTabWB, WB[c], false,
-                                    {}, 0, nullptr), kTabWB);
-      else
-        m2.a[m2.n++] = from_step(mk({sbn, sbi, Vr(i + 1), Vr(i)}, kTabWB, WB[c], false, {}, 0,
-                                    nullptr), kTabWB);
-      if (y) m2.a[m2.n++] = from_step(mk({Vr(i)}, kTabY, YA, true, {}, 0, nullptr), kTabY);
-      launch_lin_multi_step(m2, F, nrhs, step_of(kStepS2, i, P[0], P[1], false), l->stream);
+      launch_pass_rev2(Rev2Fields{VTB[c], VTB[p], Wr(i), CHI, sbn, sbi, Vr(i + 1), Vr(i), vm, tbi,
+                                  VB[c], WB[c], y ? YA : nullptr},
+                       F, nrhs, step_of(kStepS2, i, P[0], P[1]), l->stream);
       OVS_HIP(applyBoth(sbi, tbi, T2, T1));
-      multi({mk({T1}, kTabOne, VB[c], true, {Vr(i)}, 1, P[2]),
-             mk({T2}, kTabOne, WB[c], true, {Wr(i)}, 1, P[3])});
+      launch_pass_add(VB[c], T1, Vr(i), P[2], WB[c], T2, Wr(i), P[3], F, nrhs, l->stream);
       // the force of this step waits in its group's slots; a group (the steps
       // i .. i + cg - 1 below k - 1) is summed when its lowest step is done
       if (md > 0) {

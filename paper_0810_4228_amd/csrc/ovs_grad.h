@@ -26,8 +26,6 @@ struct LinArgs {
   const double2* y[kLinDots] = {};
   int ndot = 0;
   double* partials = nullptr;      // [nrhs][lin_nchunk][kLinDots][2]
-  int tab = -1;                    // >= 0: coefficients from this table of the
-                                   // launch's scalar step (launch_lin_step), not coef
 };
 int lin_nchunk(long stride);
 void launch_lin(const LinArgs& a, long stride, int nrhs, hipStream_t s);
@@ -105,18 +103,15 @@ void launch_gr_final(const GradScalars& s, const double* part, int nchunk, hipSt
 void launch_gr_final_defl(const GradScalars& s, const double* part_v, const double* part_w,
                           int nchunk, hipStream_t st);
 
-// A scalar step run at the start of a combination launch (launch_lin_step,
-// launch_lin_multi_step), one workgroup per chunk and source, each forming
-// the step's rows with the same sums: alpha (pa: partials of w_i^dagger t
-// and |t|^2), beta (pa: |v~|^2; pb: v~^dagger w~ and |w~|^2), xbar (pa:
-// chi^dagger v_i), the replay rows of step i from the stored coefficients
-// (no dots, the arithmetic of alpha and beta, so replayed vectors are
-// bitwise equal), reverse step 1 (pa: vbar_{i+1}^dagger v_{i+1}; pb:
+// A scalar step run at the start of a pass, one workgroup per chunk and source,
+// each forming the step's rows with the same sums: alpha (pa: partials of
+// w_i^dagger t and |t|^2), beta (pa: |v~|^2; pb: v~^dagger w~ and |w~|^2), xbar
+// (pa: chi^dagger v_i; no rows), the replay rows of step i from the stored
+// coefficients (no dots, the arithmetic of alpha and beta, so replayed vectors
+// are bitwise equal), reverse step 1 (pa: vbar_{i+1}^dagger v_{i+1}; pb:
 // wbar_{i+1}^dagger w_{i+1}) and reverse step 2 (pa: v_i^dagger vbar~,
-// v_{i-1}^dagger vbar~; pb: the same with w and wbar~).  The rows go to the
-// launch's tables for combinations with LinArgs::tab >= 0; global_tabs: also
-// to the global tables (for later launches).  Reverse steps 1 and 2 do not
-// write back gbar_i, bbar_i and abar_i, which nothing reads after them.
+// v_{i-1}^dagger vbar~; pb: the same with w and wbar~).  Reverse steps 1 and 2 do
+// not write back gbar_i, bbar_i and abar_i, which nothing reads after them.
 enum { kStepNone = 0, kStepAlpha, kStepBeta, kStepXbar, kStepCoef, kStepS1, kStepS2 };
 struct ScalarStep {
   int kind = kStepNone;
@@ -125,11 +120,48 @@ struct ScalarStep {
   const double* pb = nullptr;
   int nchunk = 0;
   GradScalars s{};
-  int global_tabs = 0;
 };
-void launch_lin_step(const LinArgs& a, long stride, int nrhs, const ScalarStep& st, hipStream_t s);
-void launch_lin_multi_step(const LinMulti& m, long stride, int nrhs, const ScalarStep& st,
-                           hipStream_t s);
+
+// The passes (grad.hip), stride: elements of one source's field, partials
+// [nrhs][lin_nchunk][kLinDots][2].
+// dots w^dagger t, |t|^2; st: xbar or none
+void launch_pass_dots(const double2* t, const double2* w, double* partials, long stride, int nrhs,
+                      const ScalarStep& st, hipStream_t s);
+// A step's fields: t = A v, s = A^dagger w; vm, wm of the step before, or null.
+struct StepFields {
+  const double2 *t, *v, *vm, *s, *w, *wm;
+};
+// alpha, then v~ and w~ with |v~|^2 (pv), v~^dagger w~ and |w~|^2 (pw)
+void launch_pass_update(const StepFields& f, double2* vn, double2* wn, double* pv, double* pw,
+                        long stride, int nrhs, const ScalarStep& st, hipStream_t s);
+// beta, then the normalisation in place with chi^dagger v (chi null: no dot)
+void launch_pass_norm(double2* vn, double2* wn, const double2* chi, double* pchi, long stride,
+                      int nrhs, const ScalarStep& st, hipStream_t s);
+// update and normalisation with the stored rows
+void launch_pass_replay(const StepFields& f, double2* vn, double2* wn, long stride, int nrhs,
+                        const ScalarStep& st, hipStream_t s);
+// Reverse step 1: vbar~ and wbar~ with their dots with v_i, v_{i-1} (pv) and
+// w_i, w_{i-1} (pw).
+struct Rev1Fields {
+  const double2 *vb, *v1, *w1, *wb;    // vbar_{i+1}, v_{i+1}, w_{i+1}, wbar_{i+1}
+  const double2 *v, *vm, *w, *wm;      // v_i, v_{i-1}, w_i, w_{i-1} (i = 0: vm, wm null)
+  double2 *vtb, *sb;                   // vbar~_i, wbar~_i
+};
+void launch_pass_rev1(const Rev1Fields& f, double* pv, double* pw, long stride, int nrhs,
+                      const ScalarStep& st, hipStream_t s);
+// Reverse step 2: tbar_i, the direct parts of vbar_i and wbar_i, and
+// y += |b| x_i v_i (ya null: not).
+struct Rev2Fields {
+  const double2 *vtb, *vtbn, *w, *chi;      // vbar~_i, vbar~_{i+1}, w_i, chi
+  const double2 *sbn, *sb, *v1, *v, *vm;    // wbar~_{i+1}, wbar~_i, v_{i+1}, v_i, v_{i-1} or null
+  double2 *tb, *vb, *wb, *ya;
+};
+void launch_pass_rev2(const Rev2Fields& f, long stride, int nrhs, const ScalarStep& st,
+                      hipStream_t s);
+// vbar += A^dagger tbar, wbar += A sbar with their dots with v_i (pv) and w_i (pw)
+void launch_pass_add(double2* vb, const double2* t1, const double2* v, double* pv, double2* wb,
+                     const double2* t2, const double2* w, double* pw, long stride, int nrhs,
+                     hipStream_t s);
 
 // xbar_i = nb * conj(dot 0) for the dot chi^dagger v_i of the partials.
 void launch_gf_xbar(const GradScalars& s, int i, const double* part, int nchunk, hipStream_t st);
