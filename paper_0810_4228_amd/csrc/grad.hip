@@ -128,7 +128,6 @@ __device__ void wg_dot_sums(const double* const (&parts)[ND], const int (&q)[ND]
   for (int d = 0; d < ND; ++d) out[d] = {res[2 * d], res[2 * d + 1]};
 }
 
-__device__ __forceinline__ Cx<double> cconj(Cx<double> a) { return {a.re, -a.im}; }
 __device__ __forceinline__ void set_coef(const GradScalars& s, int t, int j, int r, Cx<double> v) {
   s.coef[((long)t * kLinTerms + j) * s.nrhs + r] = d2(v);
 }
@@ -824,84 +823,148 @@ size_t isign_vjp_scratch_bytes(int k, int nnode) {
   return (size_t)n * (6 * sizeof(double2) + 1) + 256;
 }
 
-__global__ void k_isign_vjp(const double2* alpha, const double* beta, const double2* gamma,
-                            const double2* xbar, int k, double h, int n0, int nnode,
-                            VjpScratch sc) {
+// Bound by the latency of one wave's serial chain (the nodes fill a few dozen
+// waves): two sweeps over the rows, the way down factors and solves L q = e_1 and
+// U^H p = xbar as the rows become final, the way back finishes both.  What a row
+// needs from its neighbours stays in registers, the coefficients of 64 rows sit
+// in the lanes of the wave, loaded a block ahead, and the way back loads its rows
+// four ahead.  (Five sweeps, each waiting for the previous row's entries from
+// memory, took 840 us at k = 200.)
+__global__ void __launch_bounds__(64) k_isign_vjp(const double2* alpha, const double* beta,
+                                                  const double2* gamma, const double2* xbar,
+                                                  int k, double h, int n0, int nnode,
+                                                  VjpScratch sc) {
   const int nthr = 2 * nnode;
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= nthr) return;
+  const int lane = threadIdx.x;
+  const int tt = blockIdx.x * 64 + lane;
+  const bool live = tt < nthr;
+  const int t = live ? tt : nthr - 1;  // the spare lanes repeat the last solve, unstored
   const double tau = exp((double)(n0 + (t >> 1)) * h);
   const double sigma = (t & 1) ? -tau : tau;
 #define AT(arr, i) arr[(long)(i) * nthr + t]
-  for (int i = 0; i < k; ++i) {
-    const Cx<double> a = c64(alpha[i]);
-    AT(sc.d, i) = make_double2(a.re, a.im + sigma);
-    if (i < k - 1) {
-      AT(sc.dl, i) = make_double2(beta[i], 0.0);
-      AT(sc.du, i) = gamma[i];
-    }
-  }
-  // factor
-  for (int i = 0; i < k - 1; ++i) {
-    const Cx<double> di = c64(AT(sc.d, i)), li = c64(AT(sc.dl, i));
-    if (cabs1(di) >= cabs1(li)) {
-      const Cx<double> f = cdiv(li, di);
-      AT(sc.dl, i) = d2(f);
-      AT(sc.d, i + 1) = d2(c64(AT(sc.d, i + 1)) - cmul(f, c64(AT(sc.du, i))));
-      if (i < k - 2) AT(sc.du2, i) = make_double2(0.0, 0.0);
-      AT(sc.piv, i) = 0;
-    } else {
-      const Cx<double> f = cdiv(di, li);
-      const Cx<double> dn = c64(AT(sc.d, i + 1));
-      const Cx<double> ui = c64(AT(sc.du, i));
-      AT(sc.d, i) = d2(li);
-      AT(sc.dl, i) = d2(f);
-      AT(sc.du, i) = d2(dn);
-      AT(sc.d, i + 1) = d2(ui - cmul(f, dn));
-      if (i < k - 2) {
-        const Cx<double> un = c64(AT(sc.du, i + 1));
-        AT(sc.du2, i) = d2(un);
-        AT(sc.du, i + 1) = d2(-cmul(f, un));
+  const Cx<double> zero = {0.0, 0.0};
+  // lane l of a block holds alpha_{i0+l+1}, beta, gamma_{i0+l+1}, xbar of row i0+l
+  struct Block {
+    double2 a, g, x;
+    double b;
+  };
+  auto load_block = [&](int i0) {
+    const int i = i0 + lane;
+    Block o;
+    o.a = alpha[min(i + 1, k - 1)];
+    o.b = beta[min(i, k - 1)];
+    o.g = gamma[min(i + 1, k - 1)];
+    o.x = xbar[min(i, k - 1)];
+    return o;
+  };
+  Cx<double> d = {alpha[0].x, alpha[0].y + sigma};  // row i's diagonal, as updated
+  Cx<double> du = c64(gamma[0]);                     // row i's superdiagonal, as updated
+  Cx<double> q = {1.0, 0.0};                         // entry i of the right-hand side
+  Cx<double> dum = zero, du2m = zero, du2mm = zero;  // du_{i-1}, du2_{i-1}, du2_{i-2}
+  Cx<double> pm = zero, pmm = zero;                  // p_{i-1}, p_{i-2}
+  Block nxt = load_block(0);
+  for (int i0 = 0; i0 < k; i0 += 64) {
+    const Block cur = nxt;
+    nxt = load_block(i0 + 64);
+    const int n = min(64, k - i0);
+    for (int l = 0; l < n; ++l) {
+      const int i = i0 + l;
+      const bool last = i == k - 1;
+      const Cx<double> dn = {lane_value(cur.a.x, l), lane_value(cur.a.y, l) + sigma};
+      const Cx<double> un = {lane_value(cur.g.x, l), lane_value(cur.g.y, l)};
+      const double li = lane_value(cur.b, l);
+      const Cx<double> xb = {lane_value(cur.x.x, l), lane_value(cur.x.y, l)};
+      // rows i and i + 1 interchanged when |beta_i| > |d|
+      Cx<double> f = zero, df = d, duf = du, du2f = zero, qf = q, dnext = zero, dunext = un,
+                 qnext = zero;
+      bool sw = false;
+      if (!last) {  // uniform
+        f = pivot_quotient(li, d, sw);
+        const Cx<double> fm = cmul(f, csel(sw, dn, du));
+        dnext = csel(sw, du, dn) - fm;
+        df = csel(sw, Cx<double>{li, 0.0}, d);
+        duf = csel(sw, dn, du);
+        if (i < k - 2) {
+          du2f = csel(sw, un, zero);
+          dunext = csel(sw, -cmul(f, un), un);
+        }
+        // entry i + 1 of e_1 is still zero here
+        qf = csel(sw, zero, q);
+        qnext = csel(sw, q - cmul(f, zero), zero - cmul(f, q));
       }
-      AT(sc.piv, i) = 1;
+      Cx<double> b = xb;
+      if (i >= 1) b = b - cmulc(dum, pm);
+      if (i >= 2) b = b - cmulc(du2mm, pmm);
+      const Cx<double> p = cdiv_fast(b, cconj(df));
+      if (live) {
+        AT(sc.d, i) = d2(df);
+        AT(sc.du, i) = d2(duf);
+        AT(sc.du2, i) = d2(du2f);
+        AT(sc.dl, i) = d2(f);
+        AT(sc.q, i) = d2(qf);
+        AT(sc.p, i) = d2(p);
+        AT(sc.piv, i) = sw ? 1 : 0;
+      }
+      d = dnext;
+      du = dunext;
+      q = qnext;
+      du2mm = du2m;
+      du2m = du2f;
+      dum = duf;
+      pmm = pm;
+      pm = p;
     }
   }
-  // q = M^{-1} e_1: L then U
-  for (int i = 0; i < k; ++i) AT(sc.q, i) = make_double2(i == 0 ? 1.0 : 0.0, 0.0);
-  for (int i = 0; i < k - 1; ++i) {
-    const Cx<double> f = c64(AT(sc.dl, i));
-    if (AT(sc.piv, i)) {
-      const Cx<double> bi = c64(AT(sc.q, i)), bn = c64(AT(sc.q, i + 1));
-      AT(sc.q, i) = d2(bn);
-      AT(sc.q, i + 1) = d2(bi - cmul(f, bn));
-    } else {
-      AT(sc.q, i + 1) = d2(c64(AT(sc.q, i + 1)) - cmul(f, c64(AT(sc.q, i))));
+  // the way back: U q = (.), L^H p = (.); four rows' entries loaded together,
+  // one group ahead
+  constexpr int kGroup = 4;
+  struct Row {
+    double2 d, du, du2, f, q, p;
+    unsigned char piv;
+  };
+  Row rn[kGroup], rc[kGroup];
+  auto load_rows = [&](int i) {  // rows i, i - 1, ... (clamped to row 0)
+#pragma unroll
+    for (int u = 0; u < kGroup; ++u) {
+      const int j = max(i - u, 0);
+      rn[u].d = AT(sc.d, j);
+      rn[u].du = AT(sc.du, j);
+      rn[u].du2 = AT(sc.du2, j);
+      rn[u].f = AT(sc.dl, j);
+      rn[u].q = AT(sc.q, j);
+      rn[u].p = AT(sc.p, j);
+      rn[u].piv = AT(sc.piv, j);
+    }
+  };
+  Cx<double> q1 = zero, q2 = zero, pc = zero;  // q_{i+1}, q_{i+2}; p_{i+1} so far
+  load_rows(k - 1);
+  for (int i0 = k - 1; i0 >= 0; i0 -= kGroup) {
+#pragma unroll
+    for (int u = 0; u < kGroup; ++u) rc[u] = rn[u];
+    load_rows(i0 - kGroup);
+#pragma unroll
+    for (int u = 0; u < kGroup; ++u) {
+      const int i = i0 - u;
+      if (i >= 0) {  // uniform
+        Cx<double> b = c64(rc[u].q);
+        if (i + 1 < k) b = b - cmul(c64(rc[u].du), q1);
+        if (i + 2 < k) b = b - cmul(c64(rc[u].du2), q2);
+        const Cx<double> qi = cdiv_fast(b, c64(rc[u].d));
+        if (live) AT(sc.q, i) = d2(qi);
+        q2 = q1;
+        q1 = qi;
+        if (i == k - 1) {
+          pc = c64(rc[u].p);
+        } else {
+          const Cx<double> v = c64(rc[u].p) - cmulc(c64(rc[u].f), pc);
+          const bool sw = rc[u].piv != 0;
+          if (live) AT(sc.p, i + 1) = d2(csel(sw, v, pc));
+          pc = csel(sw, pc, v);
+        }
+      }
     }
   }
-  for (int i = k - 1; i >= 0; --i) {
-    Cx<double> b = c64(AT(sc.q, i));
-    if (i + 1 < k) b = b - cmul(c64(AT(sc.du, i)), c64(AT(sc.q, i + 1)));
-    if (i + 2 < k) b = b - cmul(c64(AT(sc.du2, i)), c64(AT(sc.q, i + 2)));
-    AT(sc.q, i) = d2(cdiv(b, c64(AT(sc.d, i))));
-  }
-  // p = M^{-H} xbar: U^H then L^H
-  for (int i = 0; i < k; ++i) {
-    Cx<double> b = c64(xbar[i]);
-    if (i >= 1) b = b - cmulc(c64(AT(sc.du, i - 1)), c64(AT(sc.p, i - 1)));
-    if (i >= 2) b = b - cmulc(c64(AT(sc.du2, i - 2)), c64(AT(sc.p, i - 2)));
-    AT(sc.p, i) = d2(cdiv(b, cconj(c64(AT(sc.d, i)))));
-  }
-  for (int i = k - 2; i >= 0; --i) {
-    const Cx<double> f = c64(AT(sc.dl, i));
-    const Cx<double> bi = c64(AT(sc.p, i)), bn = c64(AT(sc.p, i + 1));
-    const Cx<double> v = bi - cmulc(f, bn);
-    if (AT(sc.piv, i)) {
-      AT(sc.p, i) = d2(bn);
-      AT(sc.p, i + 1) = d2(v);
-    } else {
-      AT(sc.p, i) = d2(v);
-    }
-  }
+  if (live) AT(sc.p, 0) = d2(pc);
 #undef AT
 }
 
@@ -909,45 +972,72 @@ __global__ void k_isign_vjp(const double2* alpha, const double* beta, const doub
 // coarse.x set, also the rule of step 2h (the nodes of even index, weights
 // 2 h tau / pi) into coarse (x, gd, gsup), for the first comparison of two
 // levels without a launch at step 2h.
-__global__ void k_isign_vjp_reduce(int k, double h, int n0, int nnode, VjpScratch sc,
-                                   IsignVjpOut out, IsignVjpOut coarse) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= k) return;
+// One wave per row: the lanes load and weight 64 solves at a time (coalesced),
+// then one lane per sum adds them in order from LDS.  (One thread per row,
+// walking its row of memory by itself, took 540 us at k = 200.)
+__global__ void __launch_bounds__(64) k_isign_vjp_reduce(int k, double h, int n0, int nnode,
+                                                         VjpScratch sc, IsignVjpOut out,
+                                                         IsignVjpOut coarse) {
+  constexpr int kSums = 13;  // x, gd, Re gs, gu; coarse x, gd, gu
+  __shared__ double term[kSums][65];
+  const int i = blockIdx.x;
+  const int lane = threadIdx.x;
   const int nthr = 2 * nnode;
-  const bool two = coarse.x != nullptr;
-  Cx<double> x = {0.0, 0.0}, gd = {0.0, 0.0}, gs = {0.0, 0.0}, gu = {0.0, 0.0};
-  Cx<double> xc = {0.0, 0.0}, gdc = {0.0, 0.0}, guc = {0.0, 0.0};
-  for (int t = 0; t < nthr; ++t) {
+  const bool two = coarse.x != nullptr, up = i + 1 < k;
+  double acc = 0.0;
+  for (int t0 = 0; t0 < nthr; t0 += 64) {
+    const int t = min(t0 + lane, nthr - 1);
     const int node = n0 + (t >> 1);
+    const Cx<double> qi = c64(sc.q[(long)i * nthr + t]), pi_ = c64(sc.p[(long)i * nthr + t]);
+    Cx<double> qn = {0.0, 0.0}, pn = {0.0, 0.0};
+    if (up) {
+      qn = c64(sc.q[(long)(i + 1) * nthr + t]);
+      pn = c64(sc.p[(long)(i + 1) * nthr + t]);
+    }
     const double w = h * exp((double)node * h) / M_PI;
-    const Cx<double> qi = c64(sc.q[(long)i * nthr + t]);
-    const Cx<double> pi_ = c64(sc.p[(long)i * nthr + t]);
-    x = x + scale(w, qi);
-    gd = gd - scale(w, cmulc(qi, pi_));
     const bool even = two && (node & 1) == 0;
-    if (even) {
-      xc = xc + scale(2.0 * w, qi);
-      gdc = gdc - scale(2.0 * w, cmulc(qi, pi_));
+    const Cx<double> x = scale(w, qi), gd = scale(w, cmulc(qi, pi_));
+    const Cx<double> gs = scale(w, cmulc(qi, pn));   // -Gbar_{i+1,i} = p_{i+1} conj(q_i)
+    const Cx<double> gu = scale(w, cmulc(qn, pi_));  // -Gbar_{i,i+1} = p_i conj(q_{i+1})
+    const Cx<double> xc = scale(2.0 * w, qi), gdc = scale(2.0 * w, cmulc(qi, pi_)),
+                     guc = scale(2.0 * w, cmulc(qn, pi_));
+    __syncthreads();
+    const double v[kSums] = {x.re,
+                             x.im,
+                             -gd.re,
+                             -gd.im,
+                             -gs.re,
+                             -gu.re,
+                             -gu.im,
+                             even ? xc.re : 0.0,
+                             even ? xc.im : 0.0,
+                             even ? -gdc.re : 0.0,
+                             even ? -gdc.im : 0.0,
+                             even ? -guc.re : 0.0,
+                             even ? -guc.im : 0.0};
+#pragma unroll
+    for (int s = 0; s < kSums; ++s) term[s][lane] = v[s];
+    __syncthreads();
+    if (lane < kSums) {
+      const int n = min(64, nthr - t0);
+      int l = 0;
+      for (; l + 16 <= n; l += 16) {
+#pragma unroll
+        for (int u = 0; u < 16; ++u) acc += term[lane][l + u];
+      }
+      for (; l < n; ++l) acc += term[lane][l];
     }
-    if (i + 1 < k) {
-      const Cx<double> qn = c64(sc.q[(long)(i + 1) * nthr + t]);
-      const Cx<double> pn = c64(sc.p[(long)(i + 1) * nthr + t]);
-      gs = gs - scale(w, cmulc(qi, pn));   // Gbar_{i+1,i} = -p_{i+1} conj(q_i)
-      gu = gu - scale(w, cmulc(qn, pi_));  // Gbar_{i,i+1} = -p_i conj(q_{i+1})
-      if (even) guc = guc - scale(2.0 * w, cmulc(qn, pi_));
-    }
   }
-  out.x[i] = d2(x);
-  out.gd[i] = d2(gd);
-  if (i + 1 < k) {
-    out.gsub_re[i] = gs.re;
-    out.gsup[i] = d2(gu);
-  }
-  if (two) {
-    coarse.x[i] = d2(xc);
-    coarse.gd[i] = d2(gdc);
-    if (i + 1 < k) coarse.gsup[i] = d2(guc);
-  }
+  double* const dst[kSums] = {&out.x[i].x, &out.x[i].y, &out.gd[i].x, &out.gd[i].y,
+                              up ? &out.gsub_re[i] : nullptr, up ? &out.gsup[i].x : nullptr,
+                              up ? &out.gsup[i].y : nullptr, two ? &coarse.x[i].x : nullptr,
+                              two ? &coarse.x[i].y : nullptr, two ? &coarse.gd[i].x : nullptr,
+                              two ? &coarse.gd[i].y : nullptr,
+                              two && up ? &coarse.gsup[i].x : nullptr,
+                              two && up ? &coarse.gsup[i].y : nullptr};
+#pragma unroll
+  for (int s = 0; s < kSums; ++s)
+    if (lane == s && dst[s]) *dst[s] = acc;
 }
 
 void launch_isign_vjp(const double2* alpha, const double* beta, const double2* gamma,
@@ -958,7 +1048,7 @@ void launch_isign_vjp(const double2* alpha, const double* beta, const double2* g
   hipLaunchKernelGGL(k_isign_vjp, dim3((nthr + 63) / 64), dim3(64), 0, st, alpha, beta, gamma,
                      xbar, k, h, n0, nnode, sc);
   const IsignVjpOut none{};
-  hipLaunchKernelGGL(k_isign_vjp_reduce, dim3((k + 63) / 64), dim3(64), 0, st, k, h, n0, nnode, sc,
+  hipLaunchKernelGGL(k_isign_vjp_reduce, dim3(k), dim3(64), 0, st, k, h, n0, nnode, sc,
                      out, coarse ? *coarse : none);
 }
 
@@ -1049,15 +1139,28 @@ __device__ __forceinline__ void force_dir(double2* F, const double2* pbar, const
   }
 }
 
+// Site and direction of a thread: one thread per site and direction (each
+// direction writes only its own slots of F, so the directions are independent),
+// a workgroup takes 64 sites in the four directions (a wave each), and each XCD
+// a contiguous range of the lattice: the spinors that the directions of a site
+// and its neighbours share are then in one L1 and one L2 (16^4, ten steps: 460 us
+// with the directions in workgroups of their own, spread over the XCDs).
+__device__ __forceinline__ bool force_site(const Geometry& g, int& s, int& dir) {
+  const int ntile = (g.V + 63) / 64, per = (ntile + 7) / 8;
+  const int tile = ((int)blockIdx.x & 7) * per + ((int)blockIdx.x >> 3);
+  s = tile * 64 + ((int)threadIdx.x & 63);
+  dir = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  return tile < ntile && s < g.V;
+}
+static dim3 force_grid(const Geometry& g) { return dim3(8 * (((g.V + 63) / 64 + 7) / 8)); }
+
 __global__ void __launch_bounds__(kWG) k_gforce(double2* F, const double2* pbar, const double2* p,
                                                 const double2* qbar, const double2* q, long stride,
                                                 int nrhs, Geometry g, HopPair hp) {
-  // one thread per site and direction (blockIdx.y): each direction writes
-  // only its own slots of F, so the directions are independent
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= g.V) return;
+  int s, dir;
+  if (!force_site(g, s, dir)) return;
   const Nbr nb = neighbours(s, g);
-  switch (blockIdx.y) {
+  switch (dir) {
     case 0: force_dir<0>(F, pbar, p, qbar, q, stride, nrhs, g, s, nb.f[0], hp); break;
     case 1: force_dir<1>(F, pbar, p, qbar, q, stride, nrhs, g, s, nb.f[1], hp); break;
     case 2: force_dir<2>(F, pbar, p, qbar, q, stride, nrhs, g, s, nb.f[2], hp); break;
@@ -1080,7 +1183,7 @@ void launch_gforce(double2* F, const double2* pbar, const double2* p, const doub
                    const double2* q, long stride, int nrhs, const Geometry& g, const Hop& hA,
                    const Hop& hAd, hipStream_t st) {
   const HopPair hp = hop_pair(hA, hAd);
-  hipLaunchKernelGGL(k_gforce, dim3((g.V + kWG - 1) / kWG, 4), dim3(kWG), 0, st, F, pbar, p, qbar,
+  hipLaunchKernelGGL(k_gforce, force_grid(g), dim3(kWG), 0, st, F, pbar, p, qbar,
                      q, stride, nrhs, g, hp);
 }
 
@@ -1131,10 +1234,10 @@ __global__ void __launch_bounds__(kWG) k_gforce_group(double2* F, const double2*
                                                       const double2* q0, int nsteps,
                                                       long step_stride, long stride, int nrhs,
                                                       Geometry g, HopPair hp) {
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= g.V) return;
+  int s, dir;
+  if (!force_site(g, s, dir)) return;
   const Nbr nb = neighbours(s, g);
-  switch (blockIdx.y) {
+  switch (dir) {
     case 0: force_dir_group<0>(F, pbar0, p0, qbar0, q0, nsteps, step_stride, stride, nrhs, g, s, nb.f[0], hp); break;
     case 1: force_dir_group<1>(F, pbar0, p0, qbar0, q0, nsteps, step_stride, stride, nrhs, g, s, nb.f[1], hp); break;
     case 2: force_dir_group<2>(F, pbar0, p0, qbar0, q0, nsteps, step_stride, stride, nrhs, g, s, nb.f[2], hp); break;
@@ -1147,7 +1250,7 @@ void launch_gforce_group(double2* F, const double2* pbar0, const double2* p0,
                          long stride, int nrhs, const Geometry& g, const Hop& hA, const Hop& hAd,
                          hipStream_t st) {
   const HopPair hp = hop_pair(hA, hAd);
-  hipLaunchKernelGGL(k_gforce_group, dim3((g.V + kWG - 1) / kWG, 4), dim3(kWG), 0, st, F, pbar0,
+  hipLaunchKernelGGL(k_gforce_group, force_grid(g), dim3(kWG), 0, st, F, pbar0,
                      p0, qbar0, q0, nsteps, step_stride, stride, nrhs, g, hp);
 }
 

@@ -514,32 +514,6 @@ __global__ void k_scale_copy(const T2* __restrict__ T, T2* __restrict__ out, lon
 // multiplier and one swap bit per column.
 // ===========================================================================
 
-// 1 / d to within an ulp by two Newton steps, and n / d from it with one
-// residual correction: the quotient an IEEE division returns (whose expansion
-// is these steps between scalings by powers of two) while no intermediate
-// leaves the normal range.
-__device__ __forceinline__ double newton_rcp(double d) {
-  double y = __builtin_amdgcn_rcp(d);
-  y = fma(y, fma(-d, y, 1.0), y);
-  return fma(y, fma(-d, y, 1.0), y);
-}
-__device__ __forceinline__ double quotient(double n, double d, double y) {
-  const double q = n * y;
-  return fma(fma(-d, q, n), y, q);
-}
-
-// c ? a : b by components (a select of whole structures can go through scratch)
-__device__ __forceinline__ Cx<double> csel(bool c, Cx<double> a, Cx<double> b) {
-  return {c ? a.re : b.re, c ? a.im : b.im};
-}
-
-// The value that lane l (uniform) of the wave holds.
-__device__ __forceinline__ double lane_value(double v, int l) {
-  const int lo = __builtin_amdgcn_readlane(__double2loint(v), l);
-  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), l);
-  return __hiloint2double(hi, lo);
-}
-
 // One thread per (source r, shifted solve q): q = 2*node + (0: +tau, 1: -tau).
 // Tridiagonal T_r = tridiag(beta, alpha, gamma) of size k_r, with the rules of
 // source r (task[r]: one or two steps, each source its own): the waves of the
@@ -627,28 +601,8 @@ __global__ void __launch_bounds__(64) k_isign_tri(const double2* __restrict__ al
       const Cx<double> dm = Cx<double>{lane_value(cur.a.x, l), lane_value(cur.a.y, l)} +
                             Cx<double>{0.0, sig};
       const double dd = lane_value(cur.b, l);
-      // sw: |dd| > |cd| as hypot compares them; m = sw ? cd / dd : dd / cd, the
-      // latter by Smith's algorithm
-      const double b2 = dd * dd, c2 = fma(cd.re, cd.re, cd.im * cd.im);
-      const double top = fmax(b2, c2), low = fmin(b2, c2);
-      bool sw = b2 > c2;
-      const bool big = fabs(cd.re) >= fabs(cd.im);
-      const double hi = big ? cd.re : cd.im, lo = big ? cd.im : cd.re;
-      double rr = quotient(lo, hi, newton_rcp(hi));
-      // squares apart by more than their rounding, and every quotient in the
-      // normal range
-      const bool plain = (top > low * 1.0000000001) & (top < 1e280) & (c2 > 1e-280);
-      if (!plain) {
-        sw = fabs(dd) > cabs1(cd);
-        rr = lo / hi;
-      }
-      const double den = sw ? dd : hi + lo * rr;
-      const double br = dd * rr;
-      const double nre = sw ? cd.re : (big ? dd : br);
-      const double nim = sw ? cd.im : (big ? -br : -dd);
-      const double y = newton_rcp(den);
-      Cx<double> m = {quotient(nre, den, y), quotient(nim, den, y)};
-      if (!plain) m = {nre / den, nim / den};
+      bool sw;
+      const Cx<double> m = pivot_quotient(dd, cd, sw);
       // sw: column = (-m du, cu - m dm), else (du, dm - m cu)
       const Cx<double> t = cmul(m, csel(sw, dm, cu));
       const Cx<double> nu_ = -cmul(m, du);

@@ -152,6 +152,7 @@ __device__ __forceinline__ void st_pair64_nt(double2* p, Cx<double> a, Cx<double
   st_pair_nt(p, a, b);
 }
 
+__device__ __forceinline__ Cx<double> cconj(Cx<double> a) { return {a.re, -a.im}; }
 __device__ __forceinline__ Cx<double> c64(double2 v) { return {v.x, v.y}; }
 __device__ __forceinline__ double2 d2(Cx<double> a) { return make_double2(a.re, a.im); }
 __device__ __forceinline__ Cx<double> cdiv(Cx<double> a, Cx<double> b) {
@@ -165,6 +166,80 @@ __device__ __forceinline__ Cx<double> cdiv(Cx<double> a, Cx<double> b) {
   }
 }
 __device__ __forceinline__ double cabs1(Cx<double> a) { return hypot(a.re, a.im); }
+
+// 1 / d to within an ulp by two Newton steps, and n / d from it with one
+// residual correction: the quotient an IEEE division returns (whose expansion
+// is these steps between scalings by powers of two) while no intermediate
+// leaves the normal range.
+__device__ __forceinline__ double newton_rcp(double d) {
+  double y = __builtin_amdgcn_rcp(d);
+  y = fma(y, fma(-d, y, 1.0), y);
+  return fma(y, fma(-d, y, 1.0), y);
+}
+__device__ __forceinline__ double quotient(double n, double d, double y) {
+  const double q = n * y;
+  return fma(fma(-d, q, n), y, q);
+}
+
+// c ? a : b by components (a select of whole structures can go through scratch)
+__device__ __forceinline__ Cx<double> csel(bool c, Cx<double> a, Cx<double> b) {
+  return {c ? a.re : b.re, c ? a.im : b.im};
+}
+
+// The pivot decision and multiplier of a tridiagonal elimination step with the
+// real subdiagonal entry b and the pivot candidate c: sw = |b| > |c| as hypot
+// compares them, m = sw ? c / b : b / c as cdiv forms them (Smith's algorithm;
+// by a real divisor two plain quotients).  Squares where they are apart by more
+// than their rounding and every quotient is in the normal range, selects instead
+// of branches; hypot and IEEE divisions for the rest (skipped when no lane needs
+// them).
+__device__ __forceinline__ Cx<double> pivot_quotient(double b, Cx<double> c, bool& sw) {
+  const double b2 = b * b, c2 = fma(c.re, c.re, c.im * c.im);
+  const double top = fmax(b2, c2), low = fmin(b2, c2);
+  sw = b2 > c2;
+  const bool big = fabs(c.re) >= fabs(c.im);
+  const double hi = big ? c.re : c.im, lo = big ? c.im : c.re;
+  double rr = quotient(lo, hi, newton_rcp(hi));
+  const bool plain = (top > low * 1.0000000001) & (top < 1e280) & (c2 > 1e-280);
+  if (!plain) {
+    sw = fabs(b) > cabs1(c);
+    rr = lo / hi;
+  }
+  const double den = sw ? b : hi + lo * rr;
+  const double br = b * rr;
+  const double nre = sw ? c.re : (big ? b : br);
+  const double nim = sw ? c.im : (big ? -br : -b);
+  const double y = newton_rcp(den);
+  Cx<double> m = {quotient(nre, den, y), quotient(nim, den, y)};
+  if (!plain) m = {nre / den, nim / den};
+  return m;
+}
+
+// cdiv(a, b) with the quotients formed as above while all of them are in the
+// normal range, cdiv itself for the rest.
+__device__ __forceinline__ Cx<double> cdiv_fast(Cx<double> a, Cx<double> b) {
+  const double b2 = fma(b.re, b.re, b.im * b.im), na = fabs(a.re) + fabs(a.im);
+  const bool big = fabs(b.re) >= fabs(b.im);
+  const double hi = big ? b.re : b.im, lo = big ? b.im : b.re;
+  const double r = quotient(lo, hi, newton_rcp(hi));
+  const double den = hi + lo * r;
+  const double y = newton_rcp(den);
+  const double nre = big ? a.re + a.im * r : a.re * r + a.im;
+  const double nim = big ? a.im - a.re * r : a.im * r - a.re;
+  Cx<double> q = {quotient(nre, den, y), quotient(nim, den, y)};
+  const bool plain =
+      (b2 > 1e-280) & (b2 < 1e280) & (((na > 1e-150) & (na < 1e150)) | (na == 0.0));
+  if (!plain) q = cdiv(a, b);
+  return q;
+}
+
+// The value that lane l (uniform) of the wave holds.
+__device__ __forceinline__ double lane_value(double v, int l) {
+  const int lo = __builtin_amdgcn_readlane(__double2loint(v), l);
+  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), l);
+  return __hiloint2double(hi, lo);
+}
+
 
 // ---- XCD-aware workgroup -> (site tile, source block) map -----------------
 // Workgroups are handed to the 8 XCDs round robin (bid % 8).  The map gives
