@@ -150,17 +150,17 @@ static ovs_status ensure_pin(ovs_lattice_s* l, size_t bytes) {
   return OVS_OK;
 }
 
-void pack_field(const ovs_lattice_s* l, const void* canon, void* field, int nrhs) {
+void pack_field(const ovs_lattice_s* l, const void* canon, void* field, int nrhs, hipStream_t s) {
   if (l->prec == OVS_F32_STORE)
-    launch_pack_f32((const double2*)canon, (float2*)field, nrhs, l->g, l->stream);
+    launch_pack_f32((const double2*)canon, (float2*)field, nrhs, l->g, s);
   else
-    launch_pack_f64((const double2*)canon, (double2*)field, nrhs, l->g, l->stream);
+    launch_pack_f64((const double2*)canon, (double2*)field, nrhs, l->g, s);
 }
-void unpack_field(const ovs_lattice_s* l, const void* field, void* canon, int nrhs) {
+void unpack_field(const ovs_lattice_s* l, const void* field, void* canon, int nrhs, hipStream_t s) {
   if (l->prec == OVS_F32_STORE)
-    launch_unpack_f32((const float2*)field, (double2*)canon, nrhs, l->g, l->stream);
+    launch_unpack_f32((const float2*)field, (double2*)canon, nrhs, l->g, s);
   else
-    launch_unpack_f64((const double2*)field, (double2*)canon, nrhs, l->g, l->stream);
+    launch_unpack_f64((const double2*)field, (double2*)canon, nrhs, l->g, s);
 }
 
 bool ready(const ovs_lattice_s* l) { return l && l->links_set && l->params_set; }
@@ -573,24 +573,26 @@ ovs_status ovs_set_debug(ovs_lattice l, int32_t flags, int32_t breakdown_at) {
   return OVS_OK;
 }
 
+// Single kernels (operator applications, conversions) go on the caller's stream
+// itself: every call that uses the library stream leaves the caller's stream
+// waiting for it and starts behind the caller's, so the order is the same, and
+// the two event records and waits of StreamScope (4^4: more than the kernel)
+// are not needed.
 ovs_status ovs_apply(ovs_lattice l, ovs_op op, const void* x, void* y, int32_t nrhs) {
   if (!l || !x || !y || x == y || nrhs < 1 || nrhs > kMaxNrhs || !valid_op(op)) return OVS_ERR_ARG;
   if (!ready(l)) return OVS_ERR_STATE;
   const size_t fb = (size_t)nrhs * 12 * l->g.Vs * elem_bytes(l);
   ovs_status st = ensure_ws(l, 2 * fb + 512);
   if (st != OVS_OK) return st;
-  StreamScope sc(l);
+  (void)hipGetLastError();  // as StreamScope: drop a stale error
   Arena a{(char*)l->ws};
   void* fin = a.take<char>(fb);
   void* fout = a.take<char>(fb);
   Hop h;
   bool g5in, g5out;
   op_setup(l, op, h, g5in, g5out);
-  pack_field(l, x, fin, nrhs);
-  OVS_HIP(launch_wilson(l->prec == OVS_F32_STORE, l->links, fin, fout, nrhs, l->g, h, g5in, g5out,
-                        get_tuning(l, nrhs), l->stream));
-  unpack_field(l, fout, y, nrhs);
-  OVS_HIP(hipGetLastError());
+  OVS_HIP(launch_apply(l->prec == OVS_F32_STORE, l->links, (const double2*)x, (double2*)y, fin,
+                       fout, nrhs, l->g, h, g5in, g5out, get_tuning(l, nrhs), l->user_stream));
   return OVS_OK;
 }
 
@@ -621,27 +623,27 @@ ovs_status ovs_field_destroy(ovs_field f) {
 
 ovs_status ovs_field_import(ovs_field f, const void* x) {
   if (!f || !x) return OVS_ERR_ARG;
-  StreamScope sc(f->lat);
-  pack_field(f->lat, x, f->data, f->nrhs);
+  (void)hipGetLastError();
+  pack_field(f->lat, x, f->data, f->nrhs, f->lat->user_stream);
   OVS_HIP(hipGetLastError());
   return OVS_OK;
 }
 
 ovs_status ovs_field_export(ovs_field f, void* x) {
   if (!f || !x) return OVS_ERR_ARG;
-  StreamScope sc(f->lat);
-  unpack_field(f->lat, f->data, x, f->nrhs);
+  (void)hipGetLastError();
+  unpack_field(f->lat, f->data, x, f->nrhs, f->lat->user_stream);
   OVS_HIP(hipGetLastError());
   return OVS_OK;
 }
 
 static ovs_status field_apply_nosync(ovs_lattice l, ovs_op op, ovs_field in, ovs_field out,
-                                     const Tuning& tn) {
+                                     const Tuning& tn, hipStream_t s) {
   Hop h;
   bool g5in, g5out;
   op_setup(l, op, h, g5in, g5out);
   OVS_HIP(launch_wilson(l->prec == OVS_F32_STORE, l->links, in->data, out->data, in->nrhs, l->g, h,
-                        g5in, g5out, tn, l->stream));
+                        g5in, g5out, tn, s));
   return OVS_OK;
 }
 
@@ -653,8 +655,8 @@ static bool fields_ok(ovs_lattice l, ovs_op op, ovs_field in, ovs_field out) {
 ovs_status ovs_field_apply(ovs_lattice l, ovs_op op, ovs_field in, ovs_field out) {
   if (!fields_ok(l, op, in, out)) return OVS_ERR_ARG;
   if (!ready(l)) return OVS_ERR_STATE;
-  StreamScope sc(l);
-  return field_apply_nosync(l, op, in, out, get_tuning(l, in->nrhs));
+  (void)hipGetLastError();
+  return field_apply_nosync(l, op, in, out, get_tuning(l, in->nrhs), l->user_stream);
 }
 
 static ovs_status timed_loop(ovs_lattice l, ovs_op op, ovs_field in, ovs_field out, int iters,
@@ -664,7 +666,7 @@ static ovs_status timed_loop(ovs_lattice l, ovs_op op, ovs_field in, ovs_field o
   OVS_HIP(hipEventCreate(&e1));
   ovs_status st = OVS_OK;
   (void)hipEventRecord(e0, l->stream);
-  for (int i = 0; i < iters && st == OVS_OK; ++i) st = field_apply_nosync(l, op, in, out, tn);
+  for (int i = 0; i < iters && st == OVS_OK; ++i) st = field_apply_nosync(l, op, in, out, tn, l->stream);
   (void)hipEventRecord(e1, l->stream);
   (void)hipEventSynchronize(e1);
   float f = 0.f;

@@ -57,16 +57,13 @@ extern "C" ovs_status ovs_apply_noalloc(ovs_lattice l, ovs_op op, const void* x,
   void* base = nullptr;
   ovs_status st = scratch_address(l->device, &base);
   if (st != OVS_OK) return st;
-  StreamScope sc(l);
+  (void)hipGetLastError();  // drop a stale error left by an earlier call
   void* fin = base;
   void* fout = (char*)base + fb_al;
   Hop h;
   bool g5in, g5out;
   op_setup(l, op, h, g5in, g5out);
-  pack_field(l, x, fin, nrhs);
-  OVS_HIP(launch_wilson(l->prec == OVS_F32_STORE, l->links, fin, fout, nrhs, l->g, h, g5in, g5out,
-                        get_tuning(l, nrhs), l->stream));
-  unpack_field(l, fout, y, nrhs);
-  OVS_HIP(hipGetLastError());
+  OVS_HIP(launch_apply(l->prec == OVS_F32_STORE, l->links, (const double2*)x, (double2*)y, fin,
+                       fout, nrhs, l->g, h, g5in, g5out, get_tuning(l, nrhs), l->user_stream));
   return OVS_OK;
 }

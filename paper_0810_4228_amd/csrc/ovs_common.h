@@ -162,6 +162,10 @@ void launch_pack_links(const double2* canon, void* links, bool f32, const Geomet
 hipError_t launch_wilson(bool f32, const void* links, const void* in, void* out, int nrhs,
                          const Geometry& g, const Hop& hop, bool g5in, bool g5out,
                          const Tuning& tn, hipStream_t s);
+// y = op x on canonical fields of nrhs sources; fin, fout: scratch fields.
+hipError_t launch_apply(bool f32, const void* links, const double2* x, double2* y, void* fin,
+                        void* fout, int nrhs, const Geometry& g, const Hop& hop, bool g5in,
+                        bool g5out, const Tuning& tn, hipStream_t s);
 // Lets kernels request dynamic LDS above the default per-workgroup limit.
 void set_lds_limit(int kb);
 

@@ -48,8 +48,8 @@ Tuning get_tuning(const ovs_lattice_s* l, int nrhs, int launch = 0);
 // Grows the lattice's cached workspace to at least bytes.
 ovs_status ensure_ws(ovs_lattice_s* l, size_t bytes);
 // canonical complex128 <-> internal storage-precision fields
-void pack_field(const ovs_lattice_s* l, const void* canon, void* field, int nrhs);
-void unpack_field(const ovs_lattice_s* l, const void* field, void* canon, int nrhs);
+void pack_field(const ovs_lattice_s* l, const void* canon, void* field, int nrhs, hipStream_t s);
+void unpack_field(const ovs_lattice_s* l, const void* field, void* canon, int nrhs, hipStream_t s);
 // links and parameters set
 bool ready(const ovs_lattice_s* l);
 

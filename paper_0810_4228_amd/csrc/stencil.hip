@@ -23,19 +23,45 @@ namespace ovs {
 
 // ---- canonical <-> internal layout ----------------------------------------
 
+// A workgroup converts 128 sites of one source: canonical spinors (192 bytes a
+// site) are read and pair planes written in whole runs, transposed through LDS
+// (each lane picking its entries from memory read the canonical field 16 bytes
+// at a stride of 192: 16^3 x 32 x 12 to FP32 139 us).  Pad entries are zero.
+constexpr int kPackSites = 128;
 template <typename T2>
-__global__ void k_pack(const double2* __restrict__ canon, T2* __restrict__ field, int nrhs, int V,
-                       int Vs) {
-  const long n = (long)nrhs * 12 * Vs;
-  for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < n; e += (long)gridDim.x * blockDim.x) {
-    // e indexes the padded output (layout of fidx) so the store is coalesced;
-    // pad entries are zero
-    const long r = e / (12L * Vs);
-    const long loc = e - r * 12L * Vs;
-    const long t = loc >> 1;
-    const int s = (int)(t % Vs);
-    const int c = (int)(2 * (t / Vs) + (loc & 1));
-    st64(field + e, s < V ? c64(canon[(r * V + s) * 12 + c]) : Cx<double>{0.0, 0.0});
+__global__ void __launch_bounds__(256) k_pack(const double2* __restrict__ canon,
+                                              T2* __restrict__ field, int V, int Vs) {
+  __shared__ T2 tile[kPackSites * 13];  // [site][component], a row of 13 against bank conflicts
+  const int s0 = blockIdx.x * kPackSites;
+  const double2* in = canon + ((long)blockIdx.y * V + s0) * 12;
+  T2* out = field + (long)blockIdx.y * 12 * Vs;
+  const int nin = min(kPackSites, max(V - s0, 0)) * 12;  // entries of the tile's sites
+  double2 v[6];
+#pragma unroll
+  for (int u = 0; u < 6; ++u) {
+    const int e = u * 256 + (int)threadIdx.x;
+    if (e < nin) v[u] = in[e];
+  }
+#pragma unroll
+  for (int u = 0; u < 6; ++u) {
+    const int e = u * 256 + (int)threadIdx.x;
+    if (e < nin) st64(&tile[e / 12 * 13 + e % 12], c64(v[u]));
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < 3; ++u) {
+    const int e = u * 256 + (int)threadIdx.x;  // pair q of the tile's site
+    const int q = e / kPackSites, ls = e % kPackSites, s = s0 + ls;
+    if (s < Vs) {
+      T2 a = {0, 0}, b = {0, 0};
+      if (s < V) {
+        a = tile[ls * 13 + 2 * q];
+        b = tile[ls * 13 + 2 * q + 1];
+      }
+      T2* d = pair_at(out + (long)q * 2 * Vs, s);
+      d[0] = a;
+      d[1] = b;
+    }
   }
 }
 
@@ -61,12 +87,12 @@ static int grid_for(long n) {
 }
 
 void launch_pack_f64(const double2* canon, double2* field, int nrhs, const Geometry& g, hipStream_t s) {
-  long n = (long)nrhs * 12 * g.Vs;
-  hipLaunchKernelGGL(k_pack<double2>, dim3(grid_for(n)), dim3(kWG), 0, s, canon, field, nrhs, g.V, g.Vs);
+  hipLaunchKernelGGL(k_pack<double2>, dim3((g.Vs + kPackSites - 1) / kPackSites, nrhs), dim3(256), 0,
+                     s, canon, field, g.V, g.Vs);
 }
 void launch_pack_f32(const double2* canon, float2* field, int nrhs, const Geometry& g, hipStream_t s) {
-  long n = (long)nrhs * 12 * g.Vs;
-  hipLaunchKernelGGL(k_pack<float2>, dim3(grid_for(n)), dim3(kWG), 0, s, canon, field, nrhs, g.V, g.Vs);
+  hipLaunchKernelGGL(k_pack<float2>, dim3((g.Vs + kPackSites - 1) / kPackSites, nrhs), dim3(256), 0,
+                     s, canon, field, g.V, g.Vs);
 }
 void launch_unpack_f64(const double2* field, double2* canon, int nrhs, const Geometry& g, hipStream_t s) {
   long n = (long)nrhs * 12 * g.V;
@@ -210,13 +236,17 @@ __device__ __forceinline__ void dir_hops_staged(Cx<R> (&acc)[B][12], const T2* _
 // to LDS with one coalesced load per component, and neighbours inside the
 // tile are read from there; on lattices with Lx Ly = wg = 256 a tile is an
 // xy-plane and only the z and t hops go to L2/HBM.
-template <typename R, int B, bool STAGE>
+// CANON (B = 1, staged): the result goes to a canonical FP64 field ([V][12] per
+// source) instead, the tile transposed through the same LDS so that whole runs
+// are written: the conversion pass over the stored result (16^3 x 32 x 12: 74 us
+// and the stencil's own store) is gone.
+template <typename R, int B, bool STAGE, bool CANON = false>
 __global__ void __launch_bounds__(256)
 k_wilson(const typename Vec2<R>::T* __restrict__ links, const typename Vec2<R>::T* __restrict__ in,
          typename Vec2<R>::T* __restrict__ out, Geometry g, HopR<R> hop_c, int nrhs, int g5in,
-         int g5out, int nt, TileMap tm) {
+         int g5out, int nt, TileMap tm, double2* __restrict__ canon = nullptr) {
   using T2 = typename Vec2<R>::T;
-  __shared__ T2 plane[STAGE ? B * 12 * 256 : 1];
+  __shared__ T2 plane[STAGE ? B * (CANON ? 13 : 12) * 256 : 1];
   int site0, rb, tile;
   if (!map_tile(blockIdx.x, tm, site0, rb, tile)) return;  // uniform over the workgroup
   const int s = site0 + threadIdx.x;
@@ -242,14 +272,16 @@ k_wilson(const typename Vec2<R>::T* __restrict__ links, const typename Vec2<R>::
     }
     __syncthreads();
   }
-  if (s >= g.V) return;
-  const Nbr nb = neighbours(s, g);
+  if (!CANON && s >= g.V) return;
+  const Nbr nb = neighbours(min(s, g.V - 1), g);
   Cx<R> acc[B][12];
 #pragma unroll
   for (int r = 0; r < B; ++r)
 #pragma unroll
     for (int c = 0; c < 12; ++c) acc[r][c] = {R(0), R(0)};
-  if constexpr (STAGE) {
+  if (CANON && s >= g.V) {
+    // a spare lane of the last tile: nothing to form, but it takes part below
+  } else if constexpr (STAGE) {
     const int wg = blockDim.x;
     dir_hops_staged<R, T2, 0, B>(acc, links, inb, plane, site0, wg, Vs, s, nb, nsrc, g5in, hop_c.fwd[0], hop_c.bwd[0]);
     dir_hops_staged<R, T2, 1, B>(acc, links, inb, plane, site0, wg, Vs, s, nb, nsrc, g5in, hop_c.fwd[1], hop_c.bwd[1]);
@@ -279,7 +311,25 @@ k_wilson(const typename Vec2<R>::T* __restrict__ links, const typename Vec2<R>::
         psi[c] = psi[c] - acc[r][c];
         if (g5out && c >= 6) psi[c] = -psi[c];
       }
-      store_spinor(outb + (long)r * 12 * Vs, Vs, s, nt, psi);
+      if constexpr (CANON) {
+        __syncthreads();  // the tile's inputs have been read
+#pragma unroll
+        for (int c = 0; c < 12; ++c) plane[threadIdx.x * 13 + c] = T2{psi[c].re, psi[c].im};
+        __syncthreads();
+        const int wg = blockDim.x;
+        double2* dst = canon + ((long)r0 * g.V + site0) * 12;
+        const int n = min(wg, g.V - site0) * 12;
+#pragma unroll
+        for (int u = 0; u < 12; ++u) {
+          const int e = u * wg + (int)threadIdx.x;
+          if (e < n) {
+            const T2 v = plane[e / 12 * 13 + e % 12];
+            st64_nt(dst + e, Cx<double>{(double)v.x, (double)v.y});
+          }
+        }
+      } else {
+        store_spinor(outb + (long)r * 12 * Vs, Vs, s, nt, psi);
+      }
     }
   }
 }
@@ -342,6 +392,20 @@ k_hops(const typename Vec2<R>::T* __restrict__ links, const typename Vec2<R>::T*
   hops_body<R, false, false>(links, HopField<R, false>{const_cast<T2*>(in) + base},
                              HopField<R, false>{out + base}, g, hc, tile * 64, g5in, g5out,
                              nullptr, nullptr);
+}
+
+// The same from and to canonical FP64 fields (inputs rounded to storage precision).
+template <typename R>
+__global__ void __launch_bounds__(512)
+k_hops_canon(const typename Vec2<R>::T* __restrict__ links, const double2* __restrict__ in,
+             double2* __restrict__ out, Geometry g, HopR<R> hc, int g5in, int g5out) {
+  const long base = (long)blockIdx.y * 12 * g.V;
+  const int ntile = (g.V + 63) / 64;
+  const int tile = xcd_chunk(blockIdx.x >> 3, blockIdx.x & 7, ntile);
+  if (tile >= ntile) return;  // uniform over the workgroup
+  hops_body<R, true, false>(links, HopField<R, true>{const_cast<double2*>(in) + base},
+                            HopField<R, true>{out + base}, g, hc, tile * 64, g5in, g5out, nullptr,
+                            nullptr);
 }
 
 // Dynamic LDS requests above the default per-workgroup limit need a
@@ -437,6 +501,50 @@ static hipError_t launch_wg(const void* links, const void* in, void* out, int nr
                      (const T2*)links, (const T2*)in, (T2*)out, g, HopR<R>::make(hop_c), nrhs,
                      (int)g5in, (int)g5out, nt, tm);
   return hipSuccess;
+}
+
+// y = op x on canonical fields; fin, fout: scratch fields of the library's layout.
+// One wave per hop reads and writes the canonical fields itself (x and y apart);
+// the staged form converts its input first and writes the canonical result; the
+// others convert both.  (4^4: one launch instead of three.)
+template <typename R>
+static hipError_t launch_canon(const void* links, const double2* x, double2* y, void* fin,
+                               void* fout, int nrhs, const Geometry& g, const Hop& hop_c, bool g5in,
+                               bool g5out, const Tuning& tn, hipStream_t s) {
+  using T2 = typename Vec2<R>::T;
+  constexpr bool f32 = std::is_same_v<R, float>;
+  const long n = (long)nrhs * 12 * g.V;
+  const uintptr_t xa = (uintptr_t)x, ya = (uintptr_t)y, bytes = (uintptr_t)n * sizeof(double2);
+  if (tn.hops && (ya >= xa + bytes || xa >= ya + bytes)) {
+    const dim3 grid(8 * (((g.V + 63) / 64 + 7) / 8), nrhs);
+    hipLaunchKernelGGL(k_hops_canon<R>, grid, dim3(512), 0, s, (const T2*)links, x, y, g,
+                       HopR<R>::make(hop_c), (int)g5in, (int)g5out);
+    return hipGetLastError();
+  }
+  if constexpr (f32) launch_pack_f32(x, (float2*)fin, nrhs, g, s);
+  else launch_pack_f64(x, (double2*)fin, nrhs, g, s);
+  if (!tn.hops && tn.stage && tn.rhs_block == 1 && tn.g == 1) {
+    const TileMap tm = make_tile_map(g, tn.wg, nrhs, tn.order);
+    static std::once_flag lds_set;
+    std::call_once(lds_set, [] { apply_lds_limit((const void*)k_wilson<R, 1, true, true>); });
+    if (!lds_fits((const void*)k_wilson<R, 1, true, true>, tn.lds_kb)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_wilson<R, 1, true, true>), dim3(8 * tm.per_xcd), dim3(tn.wg),
+                       tn.lds_kb * 1024, s, (const T2*)links, (const T2*)fin, (T2*)nullptr, g,
+                       HopR<R>::make(hop_c), nrhs, (int)g5in, (int)g5out, 0, tm, y);
+    return hipGetLastError();
+  }
+  const hipError_t e = launch_wilson(f32, links, fin, fout, nrhs, g, hop_c, g5in, g5out, tn, s);
+  if (e != hipSuccess) return e;
+  if constexpr (f32) launch_unpack_f32((const float2*)fout, y, nrhs, g, s);
+  else launch_unpack_f64((const double2*)fout, y, nrhs, g, s);
+  return hipGetLastError();
+}
+
+hipError_t launch_apply(bool f32, const void* links, const double2* x, double2* y, void* fin,
+                        void* fout, int nrhs, const Geometry& g, const Hop& hop_c, bool g5in,
+                        bool g5out, const Tuning& tn, hipStream_t s) {
+  return f32 ? launch_canon<float>(links, x, y, fin, fout, nrhs, g, hop_c, g5in, g5out, tn, s)
+             : launch_canon<double>(links, x, y, fin, fout, nrhs, g, hop_c, g5in, g5out, tn, s);
 }
 
 hipError_t launch_wilson(bool f32, const void* links, const void* in, void* out, int nrhs,
