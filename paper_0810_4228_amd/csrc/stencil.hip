@@ -524,13 +524,15 @@ static hipError_t launch_canon(const void* links, const double2* x, double2* y, 
   if constexpr (f32) launch_pack_f32(x, (float2*)fin, nrhs, g, s);
   else launch_pack_f64(x, (double2*)fin, nrhs, g, s);
   if (!tn.hops && tn.stage && tn.rhs_block == 1 && tn.g == 1) {
-    const TileMap tm = make_tile_map(g, tn.wg, nrhs, tn.order);
-    static std::once_flag lds_set;
-    std::call_once(lds_set, [] { apply_lds_limit((const void*)k_wilson<R, 1, true, true>); });
-    if (!lds_fits((const void*)k_wilson<R, 1, true, true>, tn.lds_kb)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_wilson<R, 1, true, true>), dim3(8 * tm.per_xcd), dim3(tn.wg),
-                       tn.lds_kb * 1024, s, (const T2*)links, (const T2*)fin, (T2*)nullptr, g,
-                       HopR<R>::make(hop_c), nrhs, (int)g5in, (int)g5out, 0, tm, y);
+    // its own tile and order (16^3 x 32 x 12 FP32: 128 sites, order 4 217 us with
+    // the conversion, orders 0 and 7 236, 256 sites 222-228; x 4 FP64: 256 sites,
+    // order 0 119 us, 128 sites 122-126)
+    const int wg = f32 ? 128 : 256;
+    const TileMap tm = make_tile_map(g, wg, nrhs, f32 ? 4 : 0);
+    if (!lds_fits((const void*)k_wilson<R, 1, true, true>, 0)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_wilson<R, 1, true, true>), dim3(8 * tm.per_xcd), dim3(wg), 0, s,
+                       (const T2*)links, (const T2*)fin, (T2*)nullptr, g, HopR<R>::make(hop_c),
+                       nrhs, (int)g5in, (int)g5out, 0, tm, y);
     return hipGetLastError();
   }
   const hipError_t e = launch_wilson(f32, links, fin, fout, nrhs, g, hop_c, g5in, g5out, tn, s);

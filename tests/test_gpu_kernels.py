@@ -82,9 +82,9 @@ def test_one_wave_per_hop_equals_thread_per_site(prec, dims, nrhs):
 def test_canonical_apply_forms_agree(prec, dims, nrhs):
     """apply() on canonical tensors gives the same bits by one wave per hop (reads
     and writes them itself), by the staged form (converts the input, writes the
-    canonical result; workgroups of 64, 128 and 256 sites with remainders) and by
-    the resident fields' import, application and export; also when the output
-    overlaps the input, where the input has to be converted first."""
+    canonical result, tiles with remainders), by the unstaged one (converts both)
+    and by the resident fields' import, application and export; also when the
+    output overlaps the input, where the input has to be converted first."""
     import torch
     import paper_0810_4228_amd as ovs
     from gpu_util import to_dev
@@ -104,8 +104,8 @@ def test_canonical_apply_forms_agree(prec, dims, nrhs):
         n = b.numel()
         lat.apply(op, buf[:n].reshape(b.shape), out=buf[1:].reshape(b.shape))
         assert torch.equal(buf[1:].reshape(b.shape), ref[op])
-    for wg in (64, 128, 256):
-        lat.set_tuning_raw(nrhs, [1110, wg, 0, 0, 110, 256, 0, 0])
+    for shape in (1110, 110):
+        lat.set_tuning_raw(nrhs, [shape, 256, 0, 0, 110, 256, 0, 0])
         for op in ref:
             assert torch.equal(lat.apply(op, b), ref[op])
     f.close()
