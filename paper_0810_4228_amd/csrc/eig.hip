@@ -65,56 +65,89 @@ __global__ void k_resid(double2* __restrict__ D, const double2* __restrict__ AR,
     D[off + e] = d2(c64(AR[off + e]) - cmul(th, c64(R[off + e])));
 }
 
-// Conjugate gradients on the normal equations M^H M x = M^H y for n sources
-// at once (fields of Np entries, source j in workgroup row j).  With rr = |r|^2
-// and tt = |M p|^2 of the step: alpha = rr / tt, x += alpha p, r -= alpha w
-// (w = M^H M p), and per-workgroup partials of the new |r|^2.
+__global__ void k_divide(double2* __restrict__ c, const double* __restrict__ d, int n) {
+  for (int j = threadIdx.x; j < n; j += blockDim.x) c[j] = make_double2(c[j].x / d[j], c[j].y / d[j]);
+}
+
+// Conjugate gradients on the normal equations M^H M x = M^H y (one source, field
+// of Np entries).  With rr = |r|^2 and tt = |M p|^2 of the step (the sum of ntt
+// partials, formed by every workgroup): alpha = rr / tt, x += alpha p,
+// r -= alpha w (w = M^H M p), and per-workgroup partials of the new |r|^2.
+// Bound by latency on the small lattices this is for: the first four elements of
+// a thread (all of them up to 2^18 entries) load ahead of the sum's two barriers,
+// and the sum costs no launch of its own (4^3 x 8: 2.0 + 3.9 us before).
+constexpr int kCgAhead = 4;
 __global__ void __launch_bounds__(256) k_cg_xr(double2* __restrict__ X, double2* __restrict__ R,
                                                const double2* __restrict__ P,
                                                const double2* __restrict__ W,
                                                const double* __restrict__ rr,
-                                               const double* __restrict__ tt, long Np,
+                                               const double* __restrict__ ttpart, int ntt, long Np,
                                                double* __restrict__ part) {
   __shared__ double lds[4];
-  const int j = blockIdx.y;
-  const double a = tt[j] > 0.0 ? rr[j] / tt[j] : 0.0;
-  const long off = (long)j * Np;
-  double v[1] = {0.0};
-  for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < Np; e += (long)gridDim.x * blockDim.x) {
-    const double2 p = P[off + e], w = W[off + e], x = X[off + e], r = R[off + e];
-    X[off + e] = make_double2(x.x + a * p.x, x.y + a * p.y);
-    const double2 rn = make_double2(r.x - a * w.x, r.y - a * w.y);
-    R[off + e] = rn;
-    v[0] += rn.x * rn.x + rn.y * rn.y;
+  __shared__ double alpha;
+  const double num = *rr;
+  double t[1] = {0.0};
+  for (int q = threadIdx.x; q < ntt; q += 256) t[0] += ttpart[q];
+  const long st = gridDim.x * 256L, e0 = blockIdx.x * 256L + threadIdx.x;
+  double2 p[kCgAhead], w[kCgAhead], x[kCgAhead], r[kCgAhead];
+#pragma unroll
+  for (int k = 0; k < kCgAhead; ++k) {
+    const long e = e0 + k * st < Np ? e0 + k * st : Np - 1;
+    p[k] = P[e];
+    w[k] = W[e];
+    x[k] = X[e];
+    r[k] = R[e];
   }
+  block_sum<1>(t, lds);
+  if (threadIdx.x == 0) alpha = t[0] > 0.0 ? num / t[0] : 0.0;
+  __syncthreads();
+  const double a = alpha;
+  double v[1] = {0.0};
+  auto step = [&](long e, double2 pe, double2 we, double2 xe, double2 re) {
+    X[e] = make_double2(xe.x + a * pe.x, xe.y + a * pe.y);
+    const double2 rn = make_double2(re.x - a * we.x, re.y - a * we.y);
+    R[e] = rn;
+    v[0] += rn.x * rn.x + rn.y * rn.y;
+  };
+#pragma unroll
+  for (int k = 0; k < kCgAhead; ++k)
+    if (e0 + k * st < Np) step(e0 + k * st, p[k], w[k], x[k], r[k]);
+  for (long e = e0 + kCgAhead * st; e < Np; e += st) step(e, P[e], W[e], X[e], R[e]);
   block_sum<1>(v, lds);
-  if (threadIdx.x == 0) part[(long)j * gridDim.x + blockIdx.x] = v[0];
+  if (threadIdx.x == 0) part[blockIdx.x] = v[0];
 }
 
 // beta = rr' / rr with rr' the sum of k_cg_xr's partials (every workgroup
-// forms it; workgroup 0 stores it in rr_next); p = r + beta p.
-__global__ void __launch_bounds__(256) k_cg_p(double2* __restrict__ P, const double2* __restrict__ R,
+// forms it; workgroup 0 stores it in rr_next); next = r + beta p.
+__global__ void __launch_bounds__(256) k_cg_p(double2* __restrict__ next,
+                                              const double2* __restrict__ P,
+                                              const double2* __restrict__ R,
                                               const double* __restrict__ rr,
                                               double* __restrict__ rr_next,
-                                              const double* __restrict__ part, long Np) {
+                                              const double* __restrict__ part, int nch, long Np) {
   __shared__ double lds[4];
   __shared__ double beta;
-  const int j = blockIdx.y;
-  const int nch = gridDim.x;
   double v[1] = {0.0};
-  for (int q = threadIdx.x; q < nch; q += blockDim.x) v[0] += part[(long)j * nch + q];
+  for (int q = threadIdx.x; q < nch; q += 256) v[0] += part[q];
   block_sum<1>(v, lds);
   if (threadIdx.x == 0) {
-    beta = rr[j] > 0.0 ? v[0] / rr[j] : 0.0;
-    if (blockIdx.x == 0) rr_next[j] = v[0];
+    beta = *rr > 0.0 ? v[0] / *rr : 0.0;
+    if (blockIdx.x == 0) *rr_next = v[0];
   }
   __syncthreads();
   const double b = beta;
-  const long off = (long)j * Np;
-  for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < Np; e += (long)gridDim.x * blockDim.x) {
-    const double2 r = R[off + e], p = P[off + e];
-    P[off + e] = make_double2(r.x + b * p.x, r.y + b * p.y);
+  for (long e = blockIdx.x * 256L + threadIdx.x; e < Np; e += gridDim.x * 256L) {
+    const double2 r = R[e], p = P[e];
+    next[e] = make_double2(r.x + b * p.x, r.y + b * p.y);
   }
+}
+
+// The state ahead of a first step, from rr = |r|^2: partials that sum to it, and
+// an infinite predecessor, so that beta = 0 and the direction is r.
+__global__ void k_cg_start(double* __restrict__ rr, double* __restrict__ part, int nch) {
+  if ((int)threadIdx.x < nch) part[threadIdx.x] = threadIdx.x == 0 ? *rr : 0.0;
+  __syncthreads();
+  if (threadIdx.x == 0) *rr = __builtin_inf();
 }
 
 int cg_nchunk(long Np) {
@@ -125,13 +158,19 @@ int cg_nchunk(long Np) {
 }
 
 void launch_cg_xr(double2* X, double2* R, const double2* P, const double2* W, const double* rr,
-                  const double* tt, int n, long Np, double* part, hipStream_t s) {
-  hipLaunchKernelGGL(k_cg_xr, dim3(cg_nchunk(Np), n), dim3(256), 0, s, X, R, P, W, rr, tt, Np, part);
+                  const double* ttpart, int ntt, long Np, double* part, hipStream_t s) {
+  hipLaunchKernelGGL(k_cg_xr, dim3(cg_nchunk(Np)), dim3(256), 0, s, X, R, P, W, rr, ttpart, ntt, Np,
+                     part);
 }
 
-void launch_cg_p(double2* P, const double2* R, const double* rr, double* rr_next,
-                 const double* part, int n, long Np, hipStream_t s) {
-  hipLaunchKernelGGL(k_cg_p, dim3(cg_nchunk(Np), n), dim3(256), 0, s, P, R, rr, rr_next, part, Np);
+void launch_cg_p(double2* next, const double2* P, const double2* R, const double* rr,
+                 double* rr_next, const double* part, long Np, hipStream_t s) {
+  const int nch = cg_nchunk(Np);
+  hipLaunchKernelGGL(k_cg_p, dim3(nch), dim3(256), 0, s, next, P, R, rr, rr_next, part, nch, Np);
+}
+
+void launch_cg_start(double* rr, double* part, long Np, hipStream_t s) {
+  hipLaunchKernelGGL(k_cg_start, dim3(1), dim3(256), 0, s, rr, part, cg_nchunk(Np));
 }
 
 void launch_fill_random(double2* X, long nfields, const Geometry& g, unsigned long long seed,
@@ -143,6 +182,10 @@ void launch_fill_random(double2* X, long nfields, const Geometry& g, unsigned lo
 void launch_cheb(double2* Ynew, const double2* MY, const double2* Y, const double2* Yold,
                  double alpha, double c, double beta, long n, hipStream_t s) {
   hipLaunchKernelGGL(k_cheb, dim3(egrid(n)), dim3(256), 0, s, Ynew, MY, Y, Yold, alpha, c, beta, n);
+}
+
+void launch_divide(double2* c, const double* d, int n, hipStream_t s) {
+  hipLaunchKernelGGL(k_divide, dim3(1), dim3(64), 0, s, c, d, n);
 }
 
 void launch_resid(double2* D, const double2* AR, const double2* R, const double2* theta, int nb,

@@ -44,6 +44,22 @@ struct Handle {
   }
 };
 
+// Sums that the reduction kernel writes straight into pinned host memory, read
+// after a synchronisation: the solver's checks need no copy.
+struct PinnedSums {
+  double* v = nullptr;
+  explicit PinnedSums(int n) {
+    if (hipHostMalloc((void**)&v, sizeof(double) * n, hipHostMallocDefault) != hipSuccess) {
+      (void)hipGetLastError();
+      v = nullptr;
+    }
+  }
+  PinnedSums(const PinnedSums&) = delete;
+  ~PinnedSums() {
+    if (v) (void)hipHostFree(v);
+  }
+};
+
 struct DevMem {
   std::vector<void*> ptrs;
   ~DevMem() {
@@ -122,14 +138,16 @@ ovs_status compute_eigentriples(ovs_lattice_s* l, int m, double tol, int max_ite
   if (nbA >= 12L * g.V) return OVS_ERR_ARG;
   // dot partials for up to max(nev, nbA) vectors
   double* part = mem.alloc<double>((size_t)2 * std::max(nev, nbA) * std::max(cg_nchunk(Np), arn_nchunk(Np)));
-  double* red = mem.alloc<double>(nev);
-  double* rrd = mem.alloc<double>(2 * bs);
-  double* ttd = mem.alloc<double>(bs);
+  PinnedSums red(nev);
+  double* rrd = mem.alloc<double>(2);
+  // CG: the second direction buffer and the partials of |r|^2 and |M p|^2
+  double2* cP2 = mem.alloc<double2>(Np);
+  double *rpart = mem.alloc<double>(cg_nchunk(Np)), *tpart = mem.alloc<double>(arn_nchunk(Np));
   if (!cR || !cP || !cT || !cW || !cX || !cY || !vecs || !AS || !spare || !Lkeep || !Gd || !Cd || !thd ||
-      !part || !red || !rrd || !ttd)
+      !part || !red.v || !rrd || !cP2 || !rpart || !tpart)
     return OVS_ERR_ALLOC;
   // the stencil writes only lattice sites: pad entries stay zero from here on
-  for (double2* b : {cR, cP, cT, cW, cX, cY})
+  for (double2* b : {cR, cP, cT, cW, cX, cY, cP2})
     if (hipMemsetAsync(b, 0, sizeof(double2) * bs * Np, s) != hipSuccess) return OVS_ERR_HIP;
   for (double2* b : {vecs, AS, spare, Lkeep})
     if (hipMemsetAsync(b, 0, sizeof(double2) * nev * Np, s) != hipSuccess) return OVS_ERR_HIP;
@@ -150,11 +168,10 @@ ovs_status compute_eigentriples(ovs_lattice_s* l, int m, double tol, int max_ite
                          default_tuning(false, g, n), s) == hipSuccess;
   };
   auto norms2 = [&](const double2* X, int n, std::vector<double>& out) -> bool {
-    launch_norm2(false, X, Np, n, part, red, s);
-    out.resize(n);
-    if (hipMemcpyAsync(out.data(), red, sizeof(double) * n, hipMemcpyDeviceToHost, s) != hipSuccess)
-      return false;
-    return hipStreamSynchronize(s) == hipSuccess;
+    launch_norm2(false, X, Np, n, part, red.v, s);
+    if (hipStreamSynchronize(s) != hipSuccess) return false;
+    out.assign(red.v, red.v + n);
+    return true;
   };
   auto to_host = [&](const double2* d, int n, std::vector<cd>& h) -> bool {
     h.resize(n);
@@ -211,7 +228,9 @@ ovs_status compute_eigentriples(ovs_lattice_s* l, int m, double tol, int max_ite
   double2* Sd = mem.alloc<double2>((size_t)ns * Np);
   double2* Ud = mem.alloc<double2>((size_t)ns * Np);
   double2* cproj = mem.alloc<double2>(ns);
-  if (!Sd || !Ud || !cproj) return OVS_ERR_ALLOC;
+  double* etad = mem.alloc<double>(ns);
+  double2* one_d = mem.alloc<double2>(1);  // theta = 1: launch_resid as a plain difference
+  if (!Sd || !Ud || !cproj || !etad || !one_d) return OVS_ERR_ALLOC;
   int filter_passes = 0;
   rg.phase("singular_subspace");
   {
@@ -311,6 +330,9 @@ ovs_status compute_eigentriples(ovs_lattice_s* l, int m, double tol, int max_ite
     for (int j = 0; j < ns; ++j) D[j + (size_t)ns * j] = 1.0 / std::sqrt(eta[j]);
     if (!to_dev(D, CA)) return OVS_ERR_HIP;
     if (!zgemm_nn(bh.h, T1, ns, CA, ns, Np, Ud)) return OVS_ERR_HIP;
+    if (hipMemcpyAsync(etad, eta.data(), sizeof(double) * ns, hipMemcpyHostToDevice, s) != hipSuccess)
+      return OVS_ERR_HIP;
+    if (!to_dev(std::vector<cd>(1, cd(1.0)), one_d)) return OVS_ERR_HIP;
     if (hipStreamSynchronize(s) != hipSuccess) return OVS_ERR_HIP;
   }
 
@@ -318,16 +340,14 @@ ovs_status compute_eigentriples(ovs_lattice_s* l, int m, double tol, int max_ite
   // outer tolerance on A^{-1}; the inner solves run below it
   const double tol_outer = 0.5 * tol / anorm;
   const double tol_inner = std::max(0.1 * tol, 1e-14);
-  constexpr int kCgMax = 100000, kCgCheck = 24, kCgStall = 2000;  // even: graphs of two steps
+  constexpr int kCgMax = 100000, kCgGraph = 8;  // steps per graph; kCgMax and kCgCheck are multiples
+  constexpr int kCgCheck = 24, kCgStall = 2000;
   long cg_total = 0;
   int cg_fail = 0;
   // x += D diag(1 / eta) D^H r for one field (D = S or U)
   auto project_add = [&](const double2* D, const double2* r, double2* x) -> bool {
     launch_gram(D, ns, r, 1, Np, part, cproj, s);
-    std::vector<cd> c;
-    if (!to_host(cproj, ns, c)) return false;
-    for (int j = 0; j < ns; ++j) c[j] /= eta[j];
-    if (!to_dev(c, cproj)) return false;
+    launch_divide(cproj, etad, ns, s);
     const rocblas_double_complex one(1.0, 0.0);
     return rocblas_zgemm(bh.h, rocblas_operation_none, rocblas_operation_none, (rocblas_int)Np, 1, ns,
                          &one, (const rocblas_double_complex*)D, (rocblas_int)Np,
@@ -335,13 +355,16 @@ ovs_status compute_eigentriples(ovs_lattice_s* l, int m, double tol, int max_ite
                          (rocblas_int)Np) == rocblas_status_success;
   };
 
-  // x = M^{-1} y for one source, M = A (hf = hA, deflation space S) or
-  // A^dagger (hf = hAd, space U): CG on M^H M x = M^H y from the deflated
-  // start, restarted from the true residual with a second projection once it
-  // is 1e-5 of the start (rounding brings back the components along D).
-  // Two CG steps (parity back to rr[0]) on the fixed work fields, captured
-  // once per operator as a HIP graph: at 8^4 a step is a few microseconds of
-  // work per launch, so launch overhead would dominate the solve.
+  // Eight CG steps (an even number: parity back to rr[0] and cP) on the fixed work
+  // fields, captured once per operator as a HIP graph: at 8^4 a step is a few
+  // microseconds of work per launch, so launch overhead would dominate the solve
+  // (4^3 x 8, 8 triples: 712 ms with graphs of two steps, 600 with eight).  A step
+  // is bound by its launches up to there: three where the stencil runs with one
+  // wave per hop (12.9 us a step on 4^3 x 8, 14.8 on 8^4, 63.6 on 16^4, against
+  // 16.3, 17.8 and 64.3 in five), five on larger lattices, whose direction is
+  // read eight times by the stencil (16^3 x 24: 88.7 in three, 86.5 in five with
+  // one thread per site).
+  const bool one_wave_hops = default_tuning(false, g, 1).hops != 0;
   struct CgGraph {
     hipGraph_t g = nullptr;
     hipGraphExec_t x = nullptr;
@@ -350,13 +373,27 @@ ovs_status compute_eigentriples(ovs_lattice_s* l, int m, double tol, int max_ite
       if (g) (void)hipGraphDestroy(g);
     }
   } cg_graph[2];
-  auto enqueue_two_steps = [&](const Hop& hf, const Hop& hb) -> bool {
-    for (int c = 0; c < 2; ++c) {
-      if (!apply(cP, cT, 1, hf)) return false;  // t = M p
-      launch_norm2(false, cT, Np, 1, part, ttd, s);
-      if (!apply(cT, cW, 1, hb)) return false;  // w = M^H t
-      launch_cg_xr(cX, cR, cP, cW, rrd + c * bs, ttd, 1, Np, part, s);
-      launch_cg_p(cP, cR, rrd + c * bs, rrd + (1 - c) * bs, part, 1, Np, s);
+  auto enqueue_steps = [&](const Hop& hf, const Hop& hb) -> bool {
+    for (int k = 0; k < kCgGraph; ++k) {
+      const int c = k & 1;
+      const double2* p = c ? cP2 : cP;
+      double2* next = c ? cP : cP2;
+      double *rr = rrd + c, *rr_next = rrd + 1 - c;
+      const double2* links = (const double2*)links64;
+      const int ntt = arn_nchunk(Np);
+      // next = r + beta p, t = M next, w = M^H t
+      if (one_wave_hops) {
+        if (launch_hops_direction(links, cR, p, next, cT, rr, rr_next, rpart, cg_nchunk(Np), g, hf,
+                                  s) != hipSuccess ||
+            launch_hops_norm(links, cT, cW, tpart, ntt, g, hb, s) != hipSuccess)
+          return false;
+      } else {
+        launch_cg_p(next, p, cR, rr, rr_next, rpart, Np, s);
+        if (!apply(next, cT, 1, hf)) return false;
+        launch_norm2_part(false, cT, Np, tpart, s);
+        if (!apply(cT, cW, 1, hb)) return false;
+      }
+      launch_cg_xr(cX, cR, next, cW, rr_next, tpart, ntt, Np, rpart, s);
     }
     return true;
   };
@@ -373,23 +410,21 @@ ovs_status compute_eigentriples(ovs_lattice_s* l, int m, double tol, int max_ite
       return OVS_ERR_HIP;
     if (!norms2(cY, 1, yy)) return OVS_ERR_HIP;
     if (hipMemsetAsync(cX, 0, sizeof(double2) * Np, s) != hipSuccess) return OVS_ERR_HIP;
-    if (!to_dev(std::vector<cd>(1, cd(1.0)), thd)) return OVS_ERR_HIP;  // theta = 1: resid = a - b
     if (!apply(cY, cW, 1, hb)) return OVS_ERR_HIP;  // b = M^H y (kept in cW until the first step)
     if (!project_add(D, cW, cX)) return OVS_ERR_HIP;
-    // r = b - M^H M x, p = r
+    // r = b - M^H M x; the first step's direction is r (beta = 0)
     auto restart = [&]() -> bool {
       if (!apply(cX, cT, 1, hf)) return false;
-      launch_resid(cP, cY, cT, thd, 1, Np, s);  // y - M x
+      launch_resid(cP, cY, cT, one_d, 1, Np, s);  // y - M x
       if (!apply(cP, cR, 1, hb)) return false;  // r = M^H (y - M x)
-      if (hipMemcpyAsync(cP, cR, sizeof(double2) * Np, hipMemcpyDeviceToDevice, s) != hipSuccess)
-        return false;
       launch_norm2(false, cR, Np, 1, part, rrd, s);
+      launch_cg_start(rrd, rpart, Np, s);
       return true;
     };
     if (!restart()) return OVS_ERR_HIP;
     if (!cg.x) {
       if (hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal) != hipSuccess) return OVS_ERR_HIP;
-      const bool ok = enqueue_two_steps(hf, hb);
+      const bool ok = enqueue_steps(hf, hb);
       const hipError_t ce = hipStreamEndCapture(s, &cg.g);
       if (!ok || ce != hipSuccess) return OVS_ERR_HIP;
       if (hipGraphInstantiate(&cg.x, cg.g, nullptr, nullptr, 0) != hipSuccess) return OVS_ERR_HIP;
@@ -397,11 +432,11 @@ ovs_status compute_eigentriples(ovs_lattice_s* l, int m, double tol, int max_ite
     int nproj = 1;
     double best = 1e300;
     int best_it = 0;
-    for (int it = 2; it <= kCgMax; it += 2) {
+    for (int it = kCgGraph; it <= kCgMax; it += kCgGraph) {
       if (hipGraphLaunch(cg.x, s) != hipSuccess) return OVS_ERR_HIP;
       if (it % kCgCheck == 0 || it == kCgMax) {  // true residual y - M x
         if (!apply(cX, cT, 1, hf)) return OVS_ERR_HIP;
-        launch_resid(cW, cT, cY, thd, 1, Np, s);
+        launch_resid(cW, cT, cY, one_d, 1, Np, s);
         if (!norms2(cW, 1, res)) return OVS_ERR_HIP;
         const double rel = std::sqrt(res[0] / yy[0]);
         const bool done = rel <= tol_inner;

@@ -483,13 +483,8 @@ __global__ void k_arn_sub(const double* __restrict__ red_n, const double* __rest
 template <typename T2>
 __global__ void __launch_bounds__(256) k_norm2(const T2* __restrict__ T, long N,
                                                double* __restrict__ partials) {
-  __shared__ double lds[4];
   const int r = blockIdx.y;
-  double v[1] = {0.0};
-  for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < N; e += (long)gridDim.x * blockDim.x)
-    v[0] += cnorm2(ld64(T + (long)r * N + e));
-  block_sum<1>(v, lds);
-  if (threadIdx.x == 0) partials[(long)r * gridDim.x + blockIdx.x] = v[0];
+  norm2_part(T + (long)r * N, N, blockIdx.x, gridDim.x, partials + (long)r * gridDim.x);
 }
 
 // V_{j+1} = T / h, h = |T| (scale[r] = 1/h or 0 after breakdown)
@@ -1085,15 +1080,23 @@ void launch_arn_axpy(bool f32, const void* basis, long basis_stride, void* T, lo
   hipLaunchKernelGGL(k_reduce_partials<1>, dim3(nrhs), dim3(256), 0, s, partials, nch, red);
 }
 
-void launch_norm2(bool f32, const void* T, long N, int nrhs, double* partials, double* red,
-                  hipStream_t s) {
-  const int nch = arn_nchunk(N);
-  dim3 grid(nch, nrhs);
+static void launch_norm2_parts(bool f32, const void* T, long N, int nrhs, double* partials,
+                               hipStream_t s) {
+  dim3 grid(arn_nchunk(N), nrhs);
   if (f32)
     hipLaunchKernelGGL(k_norm2<float2>, grid, dim3(256), 0, s, (const float2*)T, N, partials);
   else
     hipLaunchKernelGGL(k_norm2<double2>, grid, dim3(256), 0, s, (const double2*)T, N, partials);
-  hipLaunchKernelGGL(k_reduce_partials<1>, dim3(nrhs), dim3(256), 0, s, partials, nch, red);
+}
+
+void launch_norm2(bool f32, const void* T, long N, int nrhs, double* partials, double* red,
+                  hipStream_t s) {
+  launch_norm2_parts(f32, T, N, nrhs, partials, s);
+  hipLaunchKernelGGL(k_reduce_partials<1>, dim3(nrhs), dim3(256), 0, s, partials, arn_nchunk(N), red);
+}
+
+void launch_norm2_part(bool f32, const void* T, long N, double* partials, hipStream_t s) {
+  launch_norm2_parts(f32, T, N, 1, partials, s);
 }
 
 void launch_arn_sub(const double* red_n, const double* red_tn, double2* H, int kmax, int j,

@@ -370,6 +370,19 @@ __device__ __forceinline__ void block_sum(double (&v)[NV], double* lds) {
   block_sum<NV>(v, lds, blockDim.x >> 6);
 }
 
+// partials[b] = workgroup b's share (of nb) of the sum of |T[e]|^2, e < N, by its
+// first 256 threads.
+template <typename T2>
+__device__ __forceinline__ void norm2_part(const T2* __restrict__ T, long N, int b, int nb,
+                                           double* __restrict__ partials) {
+  __shared__ double lds[4];
+  double v[1] = {0.0};
+  if (threadIdx.x < 256)
+    for (long e = b * 256L + threadIdx.x; e < N; e += nb * 256L) v[0] += cnorm2(ld64(T + e));
+  block_sum<1>(v, lds, 4);
+  if (threadIdx.x == 0) partials[b] = v[0];
+}
+
 // Two adjacent stored values as they come from memory, for loads issued ahead of
 // their use (a conversion at the load would wait for it).
 template <typename T2> struct RawPair;

@@ -12,13 +12,25 @@ void launch_cheb(double2* Ynew, const double2* MY, const double2* Y, const doubl
                  double alpha, double c, double beta, long n, hipStream_t s);
 void launch_resid(double2* D, const double2* AR, const double2* R, const double2* theta, int nb,
                   long Np, hipStream_t s);
-// One step of block CG on the normal equations (eig.hip): part holds
-// n * cg_nchunk(Np) doubles.
+// c[j] /= d[j], j < n (one workgroup)
+void launch_divide(double2* c, const double* d, int n, hipStream_t s);
+// One step of CG on the normal equations (eig.hip): part holds cg_nchunk(Np) <=
+// 256 partials of |r|^2 (of the last step; launch_cg_start sets them up from
+// rr = |r|^2), ttpart ntt partials of |M p|^2.
 int cg_nchunk(long Np);
 void launch_cg_xr(double2* X, double2* R, const double2* P, const double2* W, const double* rr,
-                  const double* tt, int n, long Np, double* part, hipStream_t s);
-void launch_cg_p(double2* P, const double2* R, const double* rr, double* rr_next,
-                 const double* part, int n, long Np, hipStream_t s);
+                  const double* ttpart, int ntt, long Np, double* part, hipStream_t s);
+void launch_cg_p(double2* next, const double2* P, const double2* R, const double* rr,
+                 double* rr_next, const double* part, long Np, hipStream_t s);
+void launch_cg_start(double* rr, double* part, long Np, hipStream_t s);
+// The step's stencils by one wave per hop (stencil.hip): out = M p', p' = r +
+// beta p (to next), as launch_cg_p; out = M^H in with nch partials of |in|^2.
+hipError_t launch_hops_direction(const double2* links, const double2* r, const double2* p,
+                                 double2* next, double2* out, const double* rr, double* rr_next,
+                                 const double* part, int nch, const Geometry& g, const Hop& hop,
+                                 hipStream_t s);
+hipError_t launch_hops_norm(const double2* links, const double2* in, double2* out, double* part,
+                            int nch, const Geometry& g, const Hop& hop, hipStream_t s);
 
 // Critical eigentriples of A = gamma5 Dw(mu): the m eigenvalues of smallest
 // magnitude with right and left eigenvectors, biorthonormalised.  Writes the

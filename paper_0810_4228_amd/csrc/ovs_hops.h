@@ -37,8 +37,22 @@ __device__ __forceinline__ int neighbour(int s, const Geometry& g) {
 template <typename R, bool CANON> struct HopField;
 template <typename R> struct HopField<R, false> {
   typename Vec2<R>::T* f;
-  __device__ void load(int Vs, int s, bool g5, Cx<R> (&p)[12]) const {
-    load_spinor_u(f, Vs, s, g5, p);
+  __device__ void head() const {}
+  struct Spinor {
+    Cx<R> v[12];
+  };
+  struct Pair {
+    Cx<R> a, b;
+  };
+  __device__ void load(int Vs, int s, Spinor& p) const { load_spinor_u(f, Vs, s, false, p.v); }
+  __device__ void form(const Spinor& p, Cx<R> (&o)[12]) const {
+#pragma unroll
+    for (int c = 0; c < 12; ++c) o[c] = p.v[c];
+  }
+  __device__ void load(int Vs, int s, int q, Pair& p) const { load_pair(Vs, s, q, p.a, p.b); }
+  __device__ void form(const Pair& p, int, int, int, bool, Cx<R>& a, Cx<R>& b) const {
+    a = p.a;
+    b = p.b;
   }
   __device__ void load_pair(int Vs, int s, int q, Cx<R>& a, Cx<R>& b) const {
     ld_pair(pair_at(f + (long)q * 2 * Vs, s), a, b);
@@ -50,16 +64,28 @@ template <typename R> struct HopField<R, false> {
 template <typename R> struct HopField<R, true> {
   double2* f;
   __device__ static Cx<R> conv(double2 v) { return {(R)v.x, (R)v.y}; }
-  __device__ void load(int, int s, bool g5, Cx<R> (&p)[12]) const {
+  __device__ void head() const {}
+  struct Spinor {
+    double2 v[12];
+  };
+  struct Pair {
+    double2 a, b;
+  };
+  __device__ void load(int, int s, Spinor& p) const {
 #pragma unroll
-    for (int c = 0; c < 12; ++c) {
-      p[c] = conv(f[12L * s + c]);
-      if (g5 && c >= 6) p[c] = -p[c];
-    }
+    for (int c = 0; c < 12; ++c) p.v[c] = f[12L * s + c];
   }
-  __device__ void load_pair(int, int s, int q, Cx<R>& a, Cx<R>& b) const {
-    a = conv(f[12L * s + 2 * q]);
-    b = conv(f[12L * s + 2 * q + 1]);
+  __device__ void form(const Spinor& p, Cx<R> (&o)[12]) const {
+#pragma unroll
+    for (int c = 0; c < 12; ++c) o[c] = conv(p.v[c]);
+  }
+  __device__ void load(int, int s, int q, Pair& p) const {
+    p.a = f[12L * s + 2 * q];
+    p.b = f[12L * s + 2 * q + 1];
+  }
+  __device__ void form(const Pair& p, int, int, int, bool, Cx<R>& a, Cx<R>& b) const {
+    a = conv(p.a);
+    b = conv(p.b);
   }
   __device__ void store_pair(int, int s, int q, Cx<R> a, Cx<R> b) const {
     f[12L * s + 2 * q] = make_double2((double)a.re, (double)a.im);
@@ -67,16 +93,66 @@ template <typename R> struct HopField<R, true> {
   }
 };
 
-// The half spinor of one hop: U (1 + g_nu) psi(s - nu) or U^dagger (1 - g_nu)
-// psi(s + nu), before expansion.
-template <typename R, int NU, bool FWD, bool CANON>
-__device__ __forceinline__ void hop_half(const typename Vec2<R>::T* __restrict__ links,
-                                         const HopField<R, CANON>& in, const Geometry& g, int s,
-                                         bool g5in, Cx<R> (&uh)[6]) {
-  const int n = neighbour<NU, FWD>(s, g);
-  Cx<R> u[9], psi[12], h[6];
-  load_link_u(links, g.Vs, NU, FWD ? s : n, u);
-  in.load(g.Vs, n, g5in, psi);
+// The direction p' = r + beta p of a conjugate gradient step, formed where it is
+// read (every workgroup forms beta itself) and stored to `next` once per site.
+// beta = rr' / rr, rr' the sum of the nch <= 256 partials (of the residual's
+// norm, in the order of a 256-thread reduction); workgroup 0 stores rr'.
+struct HopDirection {
+  const double2 *r, *p;
+  double2* next;
+  const double *rr, *part;
+  double* rr_next;
+  int nch;
+  bool first;   // the workgroup that stores rr'
+  double* lds;  // 5 entries
+  mutable double beta;
+  __device__ void head() const {
+    const double old = *rr;
+    double v[1] = {0.0};
+    if ((int)threadIdx.x < nch) v[0] += part[threadIdx.x];
+    block_sum<1>(v, lds, 4);
+    if (threadIdx.x == 0) {
+      lds[4] = old > 0.0 ? v[0] / old : 0.0;
+      if (first) *rr_next = v[0];
+    }
+    __syncthreads();
+    beta = lds[4];
+  }
+  struct Spinor {
+    Cx<double> r[12], p[12];
+  };
+  struct Pair {
+    Cx<double> r[2], p[2];
+  };
+  __device__ Cx<double> step(Cx<double> rv, Cx<double> pv) const {
+    return {rv.re + beta * pv.re, rv.im + beta * pv.im};
+  }
+  __device__ void load(int Vs, int s, Spinor& v) const {
+    load_spinor_u(r, Vs, s, false, v.r);
+    load_spinor_u(p, Vs, s, false, v.p);
+  }
+  __device__ void form(const Spinor& v, Cx<double> (&o)[12]) const {
+#pragma unroll
+    for (int c = 0; c < 12; ++c) o[c] = step(v.r[c], v.p[c]);
+  }
+  __device__ void load(int Vs, int s, int q, Pair& v) const {
+    ld_pair(pair_at(r + (long)q * 2 * Vs, s), v.r[0], v.r[1]);
+    ld_pair(pair_at(p + (long)q * 2 * Vs, s), v.p[0], v.p[1]);
+  }
+  __device__ void form(const Pair& v, int Vs, int s, int q, bool live, Cx<double>& a,
+                       Cx<double>& b) const {
+    a = step(v.r[0], v.p[0]);
+    b = step(v.r[1], v.p[1]);
+    if (live) st_pair(pair_at(next + (long)q * 2 * Vs, s), a, b);
+  }
+};
+
+// The half spinor of the hop (NU, FWD): U (1 + g_nu) psi(s - nu) or U^dagger
+// (1 - g_nu) psi(s + nu), before expansion.
+template <typename R, int NU, bool FWD>
+__device__ __forceinline__ void hop_half(const Cx<R> (&u)[9], const Cx<R> (&psi)[12],
+                                         Cx<R> (&uh)[6]) {
+  Cx<R> h[6];
   project<R, NU, FWD ? -1 : +1>(psi, h);
   link_mul<R, FWD>(u, h, uh);
 }
@@ -120,10 +196,9 @@ __device__ __forceinline__ Cx<R> hop_sum(const typename Vec2<R>::T* hops, const 
 // of conj(w) out (complex) and |out|^2 into part[0..3), w the source field at
 // `w` (library layout), summed per site over the components and then over the
 // lanes as the one-thread-per-site kernels do.
-template <typename R, bool CANON, bool PART>
+template <typename R, bool PART, typename In, typename Out>
 __device__ __forceinline__ void hops_body(const typename Vec2<R>::T* __restrict__ links,
-                                          const HopField<R, CANON>& in,
-                                          const HopField<R, CANON>& out, const Geometry& g,
+                                          const In& in, const Out& out, const Geometry& g,
                                           const HopR<R>& hc, int site0, bool g5in, bool g5out,
                                           const typename Vec2<R>::T* __restrict__ w,
                                           double* __restrict__ part) {
@@ -132,25 +207,49 @@ __device__ __forceinline__ void hops_body(const typename Vec2<R>::T* __restrict_
   __shared__ double prod[PART ? 12 * 3 * 64 : 1];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int s = site0 + lane;
-  const bool live = s < g.V;
+  const bool live = site0 + lane < g.V;
+  const int s = live ? site0 + lane : g.V - 1;  // lanes past the end load the last site
   const int q = wave;  // the component pair formed after the barrier (waves 0 to 5)
   Cx<R> p0 = {R(0), R(0)}, p1 = p0, w0 = p0, w1 = p0;
-  if (live) {
-    if (q < 6) {
-      in.load_pair(g.Vs, s, q, p0, p1);
-      if (PART && part) ld_pair(pair_at(w + (long)q * 2 * g.Vs, s), w0, w1);
+  // all loads, then what the input's head does meanwhile, then the arithmetic
+  int n;
+  switch (wave) {
+    case 0: n = neighbour<0, false>(s, g); break;
+    case 1: n = neighbour<0, true>(s, g); break;
+    case 2: n = neighbour<1, false>(s, g); break;
+    case 3: n = neighbour<1, true>(s, g); break;
+    case 4: n = neighbour<2, false>(s, g); break;
+    case 5: n = neighbour<2, true>(s, g); break;
+    case 6: n = neighbour<3, false>(s, g); break;
+    default: n = neighbour<3, true>(s, g); break;
+  }
+  Cx<R> u[9];
+  typename In::Spinor nb;
+  typename In::Pair own;
+  load_link_u(links, g.Vs, wave >> 1, (wave & 1) ? s : n, u);
+  in.load(g.Vs, n, nb);
+  if (q < 6) {
+    in.load(g.Vs, s, q, own);
+    if (PART && part) ld_pair(pair_at(w + (long)q * 2 * g.Vs, s), w0, w1);
+  }
+  in.head();
+  if (q < 6) in.form(own, g.Vs, s, q, live, p0, p1);
+  {
+    Cx<R> psi[12], uh[6];
+    in.form(nb, psi);
+    if (g5in) {
+#pragma unroll
+      for (int c = 6; c < 12; ++c) psi[c] = -psi[c];
     }
-    Cx<R> uh[6];
     switch (wave) {
-      case 0: hop_half<R, 0, false, CANON>(links, in, g, s, g5in, uh); break;
-      case 1: hop_half<R, 0, true, CANON>(links, in, g, s, g5in, uh); break;
-      case 2: hop_half<R, 1, false, CANON>(links, in, g, s, g5in, uh); break;
-      case 3: hop_half<R, 1, true, CANON>(links, in, g, s, g5in, uh); break;
-      case 4: hop_half<R, 2, false, CANON>(links, in, g, s, g5in, uh); break;
-      case 5: hop_half<R, 2, true, CANON>(links, in, g, s, g5in, uh); break;
-      case 6: hop_half<R, 3, false, CANON>(links, in, g, s, g5in, uh); break;
-      default: hop_half<R, 3, true, CANON>(links, in, g, s, g5in, uh); break;
+      case 0: hop_half<R, 0, false>(u, psi, uh); break;
+      case 1: hop_half<R, 0, true>(u, psi, uh); break;
+      case 2: hop_half<R, 1, false>(u, psi, uh); break;
+      case 3: hop_half<R, 1, true>(u, psi, uh); break;
+      case 4: hop_half<R, 2, false>(u, psi, uh); break;
+      case 5: hop_half<R, 2, true>(u, psi, uh); break;
+      case 6: hop_half<R, 3, false>(u, psi, uh); break;
+      default: hop_half<R, 3, true>(u, psi, uh); break;
     }
 #pragma unroll
     for (int i = 0; i < 6; ++i) hops[(wave * 6 + i) * 64 + lane] = T2{uh[i].re, uh[i].im};
@@ -189,8 +288,9 @@ __device__ __forceinline__ void hops_body(const typename Vec2<R>::T* __restrict_
         prod[(c * 3 + 1) * 64 + lane] = d.im;
         prod[(c * 3 + 2) * 64 + lane] = cnorm2(t64);
       };
-      put(2 * q, a0, w0);
-      put(2 * q + 1, a1, w1);
+      const Cx<R> zero = {R(0), R(0)};
+      put(2 * q, a0, live ? w0 : zero);
+      put(2 * q + 1, a1, live ? w1 : zero);
     }
   }
   if (PART && part) {

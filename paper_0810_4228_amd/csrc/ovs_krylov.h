@@ -75,6 +75,8 @@ void launch_arn_accum(const double* red, int nvec, int kmax, int j, bool first, 
 void launch_arn_axpy(bool f32, const void* basis, long basis_stride, void* T, long N, int nvec,
                      const double2* hcur, int kmax, int nrhs, double* partials, double* red,
                      hipStream_t s);
+// partials of |T|^2 of one source, arn_nchunk(N) of them
+void launch_norm2_part(bool f32, const void* T, long N, double* partials, hipStream_t s);
 void launch_norm2(bool f32, const void* T, long N, int nrhs, double* partials, double* red,
                   hipStream_t s);
 void launch_arn_sub(const double* red_n, const double* red_tn, double2* H, int kmax, int j,

@@ -15,6 +15,7 @@
 #include "ovs_common.h"
 #include "ovs_device.h"
 #include "ovs_dual.h"
+#include "ovs_eig.h"
 #include "ovs_hops.h"
 #include "ovs_lanczos.h"
 #include "ovs_spin.h"
@@ -389,7 +390,7 @@ k_hops(const typename Vec2<R>::T* __restrict__ links, const typename Vec2<R>::T*
   const int ntile = (g.V + 63) / 64;
   const int tile = xcd_chunk(blockIdx.x >> 3, blockIdx.x & 7, ntile);
   if (tile >= ntile) return;  // uniform over the workgroup
-  hops_body<R, false, false>(links, HopField<R, false>{const_cast<T2*>(in) + base},
+  hops_body<R, false>(links, HopField<R, false>{const_cast<T2*>(in) + base},
                              HopField<R, false>{out + base}, g, hc, tile * 64, g5in, g5out,
                              nullptr, nullptr);
 }
@@ -403,9 +404,66 @@ k_hops_canon(const typename Vec2<R>::T* __restrict__ links, const double2* __res
   const int ntile = (g.V + 63) / 64;
   const int tile = xcd_chunk(blockIdx.x >> 3, blockIdx.x & 7, ntile);
   if (tile >= ntile) return;  // uniform over the workgroup
-  hops_body<R, true, false>(links, HopField<R, true>{const_cast<double2*>(in) + base},
+  hops_body<R, false>(links, HopField<R, true>{const_cast<double2*>(in) + base},
                             HopField<R, true>{out + base}, g, hc, tile * 64, g5in, g5out, nullptr,
                             nullptr);
+}
+
+// The two operator applications of a conjugate gradient step on M^H M x = b
+// (one FP64 source).  First out = M p', the direction p' = r + beta p formed as
+// the stencil reads it (see HopDirection): the separate pass over the direction
+// was 3.4 of a step's 26 us on 4^3 x 8 and a launch.
+__global__ void __launch_bounds__(512)
+k_hops_direction(const double2* __restrict__ links, const double2* __restrict__ r,
+                 const double2* __restrict__ p, double2* __restrict__ next,
+                 double2* __restrict__ out, const double* __restrict__ rr,
+                 double* __restrict__ rr_next, const double* __restrict__ part, int nch, Geometry g,
+                 HopR<double> hc) {
+  __shared__ double lds[5];
+  const int ntile = (g.V + 63) / 64;
+  const int tile = xcd_chunk(blockIdx.x >> 3, blockIdx.x & 7, ntile);
+  if (tile >= ntile) return;  // uniform over the workgroup
+  const HopDirection in{r, p, next, rr, part, rr_next, nch, blockIdx.x == 0, lds, 0.0};
+  hops_body<double, false>(links, in, HopField<double, false>{out}, g, hc, tile * 64, false, true,
+                           nullptr, nullptr);
+}
+
+// Then out = M^H in with the partials of |in|^2 by the workgroups from nhop on:
+// they take the same time as the stencil's and run beside them.
+__global__ void __launch_bounds__(512)
+k_hops_norm(const double2* __restrict__ links, const double2* __restrict__ in,
+            double2* __restrict__ out, Geometry g, HopR<double> hc, int nhop,
+            double* __restrict__ part) {
+  if ((int)blockIdx.x >= nhop) {
+    norm2_part(in, 12L * g.Vs, blockIdx.x - nhop, gridDim.x - nhop, part);
+    return;
+  }
+  const int ntile = (g.V + 63) / 64;
+  const int tile = xcd_chunk(blockIdx.x >> 3, blockIdx.x & 7, ntile);
+  if (tile >= ntile) return;  // uniform over the workgroup
+  hops_body<double, false>(links, HopField<double, false>{const_cast<double2*>(in)},
+                           HopField<double, false>{out}, g, hc, tile * 64, false, true, nullptr,
+                           nullptr);
+}
+
+static int hops_grid(const Geometry& g) { return 8 * (((g.V + 63) / 64 + 7) / 8); }
+
+hipError_t launch_hops_direction(const double2* links, const double2* r, const double2* p,
+                                 double2* next, double2* out, const double* rr, double* rr_next,
+                                 const double* part, int nch, const Geometry& g, const Hop& hop_c,
+                                 hipStream_t s) {
+  if (nch > 256) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_hops_direction, dim3(hops_grid(g)), dim3(512), 0, s, links, r, p, next, out,
+                     rr, rr_next, part, nch, g, HopR<double>::make(hop_c));
+  return hipGetLastError();
+}
+
+hipError_t launch_hops_norm(const double2* links, const double2* in, double2* out, double* part,
+                            int nch, const Geometry& g, const Hop& hop_c, hipStream_t s) {
+  const int nhop = hops_grid(g);
+  hipLaunchKernelGGL(k_hops_norm, dim3(nhop + nch), dim3(512), 0, s, links, in, out, g,
+                     HopR<double>::make(hop_c), nhop, part);
+  return hipGetLastError();
 }
 
 // Dynamic LDS requests above the default per-workgroup limit need a
@@ -555,7 +613,7 @@ hipError_t launch_wilson(bool f32, const void* links, const void* in, void* out,
   const int wg = tn.wg;
   hipError_t e = hipSuccess;
   if (tn.hops) {
-    const dim3 grid(8 * (((g.V + 63) / 64 + 7) / 8), nrhs);
+    const dim3 grid(hops_grid(g), nrhs);
     if (f32)
       hipLaunchKernelGGL(k_hops<float>, grid, dim3(512), 0, s, (const float2*)links,
                          (const float2*)in, (float2*)out, g, HopR<float>::make(hop_c), (int)g5in,
@@ -1118,7 +1176,7 @@ k_hops_dual(const typename Vec2<R>::T* __restrict__ links,
   const int site0 = tile_site(quarter >> 2, tm) + 64 * (quarter & 3);
   double* part =
       partials && !dag ? partials + ((long)slot * tm.ntiles * 4 + quarter) * 3 : nullptr;
-  hops_body<R, false, true>(links, HopField<R, false>{const_cast<T2*>(dag ? in_w : in_v)},
+  hops_body<R, true>(links, HopField<R, false>{const_cast<T2*>(dag ? in_w : in_v)},
                             HopField<R, false>{(dag ? out_s : out_t) + base}, g, dag ? hAd : hA,
                             site0, false, true, in_w, part);
 }

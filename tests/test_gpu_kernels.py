@@ -111,3 +111,30 @@ def test_canonical_apply_forms_agree(prec, dims, nrhs):
     f.close()
     g.close()
     lat.close()
+
+
+@pytest.mark.parametrize("dims,m,tol", [((3, 2, 5, 7), 3, 1e-8), ((4, 4, 8, 8), 2, 1e-8),
+                                        ((24, 24, 16, 12), 4, 1e-3)])
+def test_eigentriples_both_forms_of_the_inner_solves(dims, m, tol):
+    """The deflation eigensolver's inner solves run their stencils with one wave per
+    hop up to 1e5 sites (directions formed in the stencil, norms beside it;
+    a last workgroup of 18 lanes, and full ones) and in separate launches beyond:
+    right and left residuals of the triples, by the operator itself, within the
+    requested tolerance (twice it: residuals are relative to |lambda|, whose own
+    relative error is below the tolerance)."""
+    import torch
+    import paper_0810_4228_amd as ovs
+    from gpu_util import to_dev
+    lat = ovs.Lattice(dims, precision="f64")
+    lat.set_links(to_dev(synth.random_links(dims, 0.3, seed=43)))
+    lat.set_params(MW, 0.1)
+    d, st = lat.deflation_compute(m, tol=tol, max_iter=60)
+    lam, R, L, info = d.get()
+    assert st == 0
+    lam = torch.as_tensor(np.asarray(lam), device=R.device)
+    rr = (lat.apply("A", R) - lam[:, None] * R).norm(dim=1) / (lam.abs() * R.norm(dim=1))
+    rl = (lat.apply("A_dag", L) - lam.conj()[:, None] * L).norm(dim=1) / (lam.abs() * L.norm(dim=1))
+    say(f"eigentriples {dims} m={m}: residuals {float(rr.max()):.1e} {float(rl.max()):.1e}, info {info}")
+    assert float(rr.max()) <= 2 * tol and float(rl.max()) <= 2 * tol
+    d.close()
+    lat.close()
