@@ -113,11 +113,12 @@ struct IsignResult {
 int isign_tri_nwave(int nnode);
 // A launch takes about k sequential elimination steps whatever its number of
 // waves, until the waves of a compute unit's SIMDs share their issue slots: the
-// chunk holds every solve of the rules down to step 1/16 (43 waves), and for
-// few sources those of 1/32 (86) or all (171).
+// chunk holds every solve of the rules down to step 1/16 (43 waves), and for up
+// to five sources those of 1/32 (86) or all (171).  Not for more: a chunk takes
+// 1 KiB a wave, source and Krylov step, as much as the basis of a small lattice.
 inline int isign_wave_chunk(int nrhs) {
   const int c = 512 / nrhs;
-  return c < 48 ? 48 : c > 172 ? 172 : c;
+  return nrhs > 5 ? 48 : c > 172 ? 172 : c;
 }
 // 64-bit words that hold one swap bit for each of kmax elimination steps
 __host__ __device__ inline int isign_swp_words(int kmax) { return (kmax + 63) / 64; }
