@@ -1161,7 +1161,7 @@ static ovs_status sign_apply_impl(ovs_lattice l, ovs_deflation defl, int32_t n_d
     char *basis, *wbuf, *T, *S;
     double *part1, *part2, *dpart, *CD, *spart, *sums, *sumsb, *nb;
     double2 *alpha, *gamma, *sw, *coef, *x, *mult, *part, *H, *hcur, *ys, *acc, *xtmp;
-    double *beta, *sv, *tnorm2, *qerr, *red, *apart, *red_n, *red_tn, *scl, *dnorm;
+    double *beta, *sv, *tnorm2, *qerr, *red, *apart, *npart, *tnpart, *dnorm;
     int *kstop, *status, *rhs_map, *ints, *kused, *pidx, *kv;
     unsigned long long* swp;
     double2* probes;
@@ -1223,11 +1223,9 @@ static ovs_status sign_apply_impl(ovs_lattice l, ovs_deflation defl, int32_t n_d
     } else {
       B.H = a.take<double2>((size_t)nr * K * K);
       B.hcur = a.take<double2>((size_t)nr * K);
-      B.red = a.take<double>((size_t)nr * K * 2);
       B.apart = a.take<double>((size_t)nr * K * nch_arn * 2);
-      B.red_n = a.take<double>(nr);
-      B.red_tn = a.take<double>(nr);
-      B.scl = a.take<double>(nr);
+      B.npart = a.take<double>((size_t)nr * nch_arn);
+      B.tnpart = a.take<double>((size_t)nr * nch_arn);
       B.ys = a.take<double2>((size_t)nr * nq_chunk * K);
       B.acc = a.take<double2>((size_t)nr * 2 * K);
       B.xtmp = a.take<double2>((size_t)nr * K);
@@ -1378,7 +1376,7 @@ static ovs_status sign_apply_impl(ovs_lattice l, ovs_deflation defl, int32_t n_d
   // from the dot products V~_m^dagger W~_i and the scales sv, sw.
   auto biorth_row = [&](int i) -> ovs_status {
     const int nv = i + 1;
-    launch_arn_dots(f32, B.basis, bstride, B.wbuf + (size_t)(i % 3) * bstride * es, N, nv, nr,
+    launch_block_dots(f32, B.basis, bstride, B.wbuf + (size_t)(i % 3) * bstride * es, N, nv, nr,
                     B.apart, B.red, s);
     std::vector<double> red((size_t)nr * nv * 2), svh((size_t)nr * (K + 1)),
         swh((size_t)nr * (K + 1) * 2);
@@ -1766,15 +1764,16 @@ static ovs_status sign_apply_impl(ovs_lattice l, ovs_deflation defl, int32_t n_d
     for (int j = 0; j < K; ++j) {
       OVS_HIP(launch_wilson(f32, l->links, B.basis + (size_t)j * bstride * es, B.T, nr, l->g, hA,
                             false, true, tn, s));
-      launch_norm2(f32, B.T, N, nr, B.apart, B.red_tn, s);
       for (int pass = 0; pass < 2; ++pass) {
-        launch_arn_dots(f32, B.basis, bstride, B.T, N, j + 1, nr, B.apart, B.red, s);
-        launch_arn_accum(B.red, j + 1, K, j, pass == 0, B.H, B.hcur, nr, s);
-        launch_arn_axpy(f32, B.basis, bstride, B.T, N, j + 1, B.hcur, K, nr, B.apart, B.red_n, s);
+        launch_arn_dots(f32, B.basis, bstride, B.T, N, j + 1, nr, B.apart,
+                        pass == 0 ? B.tnpart : nullptr, s);
+        launch_arn_accum(B.apart, N, j + 1, K, j, pass == 0, B.H, B.hcur, nr, s);
+        launch_arn_axpy(f32, B.basis, bstride, B.T, N, j + 1, B.hcur, K, nr,
+                        pass == 1 ? B.npart : nullptr, s);
       }
       if (j < K - 1) {
-        launch_arn_sub(B.red_n, B.red_tn, B.H, K, j, B.scl, B.kstop, B.status, nr, s);
-        launch_scale_copy(f32, B.T, B.basis + (size_t)(j + 1) * bstride * es, N, B.scl, nr, s);
+        launch_arn_next(f32, B.T, B.basis + (size_t)(j + 1) * bstride * es, N, B.npart, B.tnpart,
+                        B.H, K, j, B.kstop, B.status, nr, s);
         if (probing) {
           // sampled entries of v_{j+2} (B.ints[0] = j, so the gather takes j + 1)
           launch_probe_gather(f32, B.basis, bstride, N, false, B.ints, false, B.pidx, P, K,

@@ -74,17 +74,10 @@ __global__ void __launch_bounds__(256) k_defl_dots(const double2* __restrict__ R
       }
     }
   }
-  block_sum<4 * kDeflRhs>(v, lds);
-  if (threadIdx.x == 0) {
-    // compile-time bounds keep v[] in registers (a runtime bound indexes it
-    // dynamically, which puts it in scratch memory)
-#pragma unroll
-    for (int q = 0; q < kDeflRhs; ++q)
-      if (q < nr)
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-          partials[(((long)j * nrhs + r0 + q) * nchunk + blockIdx.x) * 4 + t] = v[4 * q + t];
-  }
+  const double a = block_sums(v, lds);
+  const int q = threadIdx.x;
+  if (q < 4 * nr)
+    partials[(((long)j * nrhs + r0 + (q >> 2)) * nchunk + blockIdx.x) * 4 + (q & 3)] = a;
 }
 
 // CD: [m][nrhs][4] reduced (C, D); sgn: [m] sign of Re lambda.
@@ -382,101 +375,120 @@ __global__ void k_overlap(const double2* __restrict__ b, double2* __restrict__ y
 // ===========================================================================
 constexpr int kArnVec = 8;  // basis vectors per workgroup in the dot kernel
 
-// partials [nrhs][nvec][nchunk][2] of v_i^dag t, i < nvec
+// partials [nrhs][nvec][nchunk][2] of v_i^dag t, i < nvec; npart != nullptr: the
+// last workgroups (in z) form the partials [nrhs][nchunk] of |t|^2 instead.
+// Bound by the basis' traffic: the loads of an element's eight vectors issue
+// together, past the last vector from the last one (each under a branch of its own
+// and with the sums by thread 0: 19.2 us for 100 vectors of 8^4, now 15.0, 5.3 TB/s).
 template <typename T2>
 __global__ void __launch_bounds__(256) k_block_dots(const T2* __restrict__ basis, long basis_stride,
                                                     const T2* __restrict__ T, long N, int nvec,
-                                                    int nchunk, double* __restrict__ partials) {
+                                                    int nchunk, double* __restrict__ partials,
+                                                    double* __restrict__ npart) {
   __shared__ double lds[4 * 2 * kArnVec];
   const int r = blockIdx.y;
   const int i0 = blockIdx.z * kArnVec;
+  if (i0 >= nvec) {
+    norm2_part(T + (long)r * N, N, blockIdx.x, nchunk, npart + (long)r * nchunk);
+    return;
+  }
   const int ni = min(kArnVec, nvec - i0);
   double v[2 * kArnVec];
 #pragma unroll
   for (int q = 0; q < 2 * kArnVec; ++q) v[q] = 0.0;
   for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < N; e += (long)gridDim.x * blockDim.x) {
+    T2 b[kArnVec];
+    const T2* bv = basis + i0 * basis_stride + (long)r * N + e;
+#pragma unroll
+    for (int q = 0; q < kArnVec; ++q) b[q] = bv[min(q, ni - 1) * basis_stride];
     const Cx<double> t = ld64(T + (long)r * N + e);
 #pragma unroll
     for (int q = 0; q < kArnVec; ++q) {
-      if (q < ni) {
-        const Cx<double> p = cmulc(ld64(basis + (i0 + q) * basis_stride + (long)r * N + e), t);
-        v[2 * q] += p.re;
-        v[2 * q + 1] += p.im;
-      }
+      const Cx<double> p = cmulc(ld64(&b[q]), t);
+      v[2 * q] += p.re;
+      v[2 * q + 1] += p.im;
     }
   }
-  block_sum<2 * kArnVec>(v, lds);
-  if (threadIdx.x == 0)
-    for (int q = 0; q < ni; ++q)
-      for (int t = 0; t < 2; ++t)
-        partials[(((long)r * nvec + i0 + q) * nchunk + blockIdx.x) * 2 + t] = v[2 * q + t];
+  const double a = block_sums(v, lds);
+  const int q = threadIdx.x;
+  if (q < 2 * ni)
+    partials[(((long)r * nvec + i0 + (q >> 1)) * nchunk + blockIdx.x) * 2 + (q & 1)] = a;
 }
 
-// H[r][j][i] += h_i (column-major: column j of H_r), hcur[r][i] = h_i
-__global__ void k_arn_accum(const double* __restrict__ red, int nvec, int kmax, int j, int first,
-                            double2* __restrict__ H, double2* __restrict__ hcur, int nrhs) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= nrhs * nvec) return;
-  const int r = e / nvec, i = e % nvec;
-  const Cx<double> h = {red[(long)e * 2], red[(long)e * 2 + 1]};
-  double2* hij = H + ((long)r * kmax + j) * kmax + i;
-  *hij = first ? d2(h) : d2(c64(*hij) + h);
-  hcur[(long)r * kmax + i] = d2(h);
+// h_i from its nparts partials (workgroup i of source r): H[r][j][i] += h_i
+// (column-major: column j of H_r), hcur[r][i] = h_i
+__global__ void __launch_bounds__(256) k_arn_accum(const double* __restrict__ partials, int nparts,
+                                                   int kmax, int j, int first,
+                                                   double2* __restrict__ H,
+                                                   double2* __restrict__ hcur) {
+  __shared__ double lds[4 * 2];
+  const int i = blockIdx.x, r = blockIdx.y;
+  const double* p = partials + ((long)r * gridDim.x + i) * nparts * 2;
+  double v[2] = {0.0, 0.0};
+  for (int q = threadIdx.x; q < nparts; q += blockDim.x) {
+    v[0] += p[2 * q];
+    v[1] += p[2 * q + 1];
+  }
+  block_sum<2>(v, lds);
+  if (threadIdx.x == 0) {
+    const Cx<double> h = {v[0], v[1]};
+    double2* hij = H + ((long)r * kmax + j) * kmax + i;
+    *hij = first ? d2(h) : d2(c64(*hij) + h);
+    hcur[(long)r * kmax + i] = d2(h);
+  }
 }
 
-// T -= sum_i hcur_i V_i ; partials of |T|^2 [nrhs][nchunk]
+// T -= sum_i hcur_i V_i ; partials of |T|^2 [nrhs][nchunk] (if given).  A small
+// lattice gives one workgroup per CU at most, so bound by latency unless enough
+// loads are in flight: two groups of 16 vectors take turns, one loading while the
+// other is subtracted, and the coefficients come from LDS (8^4, 100 vectors: 20.4 us with
+// scalar loads of them, now 15.7, 5.1 TB/s; a plain read 11.8).  One term after the other.
+constexpr int kArnAhead = 16;
 template <typename T2>
 __global__ void __launch_bounds__(256) k_block_axpy(const T2* __restrict__ basis, long basis_stride,
                                                     T2* __restrict__ T, long N, int nvec,
                                                     const double2* __restrict__ hcur, int kmax,
                                                     double* __restrict__ partials) {
   __shared__ double lds[4];
+  __shared__ double2 h[kHessMaxK];
   const int r = blockIdx.y;
   double v[1] = {0.0};
-  for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < N; e += (long)gridDim.x * blockDim.x) {
-    Cx<double> t = ld64(T + (long)r * N + e);
-    // one term after the other as written, the loads of eight issued together
+  T2 qa[kArnAhead], qb[kArnAhead];
+  auto load = [&](T2 (&q)[kArnAhead], long e, int i) {
+    if (i >= nvec) return;
     const T2* br = basis + (long)r * N + e;
-    const double2* hr = hcur + (long)r * kmax;
-    int i = 0;
-    for (; i + 8 <= nvec; i += 8) {
-      T2 q[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) q[u] = br[(long)(i + u) * basis_stride];
+    for (int u = 0; u < kArnAhead; ++u) q[u] = br[(long)min(i + u, nvec - 1) * basis_stride];
+  };
+  const long e0 = blockIdx.x * (long)blockDim.x + threadIdx.x;
+  load(qa, min(e0, N - 1), 0);
+  for (int i = threadIdx.x; i < nvec; i += blockDim.x) h[i] = hcur[(long)r * kmax + i];
+  __syncthreads();
+  for (long e = e0; e < N; e += (long)gridDim.x * blockDim.x) {
+    if (e != e0) load(qa, e, 0);
+    Cx<double> t = ld64(T + (long)r * N + e);
+    auto subtract = [&](const T2 (&q)[kArnAhead], int i) {
+      if (i + kArnAhead <= nvec) {
 #pragma unroll
-      for (int u = 0; u < 8; ++u) t = t - cmul(c64(hr[i + u]), ld64(&q[u]));
+        for (int u = 0; u < kArnAhead; ++u) t = t - cmul(c64(h[i + u]), ld64(&q[u]));
+      } else {
+#pragma unroll
+        for (int u = 0; u < kArnAhead; ++u)
+          if (i + u < nvec) t = t - cmul(c64(h[i + u]), ld64(&q[u]));
+      }
+    };
+    for (int i = 0; i < nvec; i += 2 * kArnAhead) {
+      load(qb, e, i + kArnAhead);
+      subtract(qa, i);
+      load(qa, e, i + 2 * kArnAhead);
+      subtract(qb, i + kArnAhead);
     }
-    for (; i < nvec; ++i) t = t - cmul(c64(hr[i]), ld64(br + (long)i * basis_stride));
     st64(T + (long)r * N + e, t);
     v[0] += cnorm2(round_to(T, t));
   }
+  if (!partials) return;
   block_sum<1>(v, lds);
   if (threadIdx.x == 0) partials[(long)r * gridDim.x + blockIdx.x] = v[0];
-}
-
-// H[j+1][j] = |t| and scl = 1/|t|; lucky breakdown |t| <= 1e-14 |A v_j| stops
-// the source at k = j+1 (scl = 0 from then on).
-__global__ void k_arn_sub(const double* __restrict__ red_n, const double* __restrict__ red_tn,
-                          double2* __restrict__ H, int kmax, int j, double* __restrict__ scl,
-                          int* __restrict__ kstop, int* __restrict__ status, int nrhs) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= nrhs) return;
-  double2* hsub = H + ((long)r * kmax + j) * kmax + (j + 1);
-  if (status[r] != 0) {
-    scl[r] = 0.0;
-    *hsub = make_double2(0.0, 0.0);
-    return;
-  }
-  const double h = sqrt(red_n[r]), tn = sqrt(red_tn[r]);
-  if (!(h > 1e-14 * tn)) {
-    status[r] = 1;
-    kstop[r] = j + 1;
-    scl[r] = 0.0;
-    *hsub = make_double2(0.0, 0.0);
-  } else {
-    scl[r] = 1.0 / h;
-    *hsub = make_double2(h, 0.0);
-  }
 }
 
 // partials of |T|^2 [nrhs][nchunk]
@@ -487,12 +499,42 @@ __global__ void __launch_bounds__(256) k_norm2(const T2* __restrict__ T, long N,
   norm2_part(T + (long)r * N, N, blockIdx.x, gridDim.x, partials + (long)r * gridDim.x);
 }
 
-// V_{j+1} = T / h, h = |T| (scale[r] = 1/h or 0 after breakdown)
+// V_{j+1} = T / h, h = |T| from the subtraction's partials (every workgroup sums
+// them; the first of a source writes H[j+1][j] = h); zero after the lucky
+// breakdown h <= 1e-14 |A v_j| (its norm from the dots' partials), which stops the
+// source at k = j+1.  Workgroups that read the status of this step or of the one
+// before take the same branch.
 template <typename T2>
-__global__ void k_scale_copy(const T2* __restrict__ T, T2* __restrict__ out, long N,
-                             const double* __restrict__ scl) {
+__global__ void __launch_bounds__(256) k_arn_next(const T2* __restrict__ T, T2* __restrict__ out,
+                                                  long N, const double* __restrict__ npart,
+                                                  const double* __restrict__ tnpart, int nparts,
+                                                  double2* __restrict__ H, int kmax, int j,
+                                                  int* __restrict__ kstop,
+                                                  int* __restrict__ status) {
+  __shared__ double lds[4 * 2];
+  __shared__ double scl;
   const int r = blockIdx.y;
-  const double s = scl[r];
+  double v[2] = {0.0, 0.0};
+  for (int q = threadIdx.x; q < nparts; q += blockDim.x) {
+    v[0] += npart[(long)r * nparts + q];
+    v[1] += tnpart[(long)r * nparts + q];
+  }
+  block_sum<2>(v, lds);
+  if (threadIdx.x == 0) {
+    const double h = sqrt(v[0]), tn = sqrt(v[1]);
+    const bool stopped = status[r] != 0;
+    const bool ok = !stopped && h > 1e-14 * tn;
+    scl = ok ? 1.0 / h : 0.0;
+    if (blockIdx.x == 0) {
+      H[((long)r * kmax + j) * kmax + (j + 1)] = make_double2(ok ? h : 0.0, 0.0);
+      if (!stopped && !ok) {
+        status[r] = 1;
+        kstop[r] = j + 1;
+      }
+    }
+  }
+  __syncthreads();
+  const double s = scl;
   for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < N; e += (long)gridDim.x * blockDim.x)
     st64(out + (long)r * N + e, scale(s, ld64(T + (long)r * N + e)));
 }
@@ -1042,42 +1084,45 @@ void launch_overlap(const double2* b, double2* y, long N, int V, hipStream_t s) 
 int arn_nchunk(long N) { return chunks_for(N, 256); }
 
 void launch_arn_dots(bool f32, const void* basis, long basis_stride, const void* T, long N,
-                     int nvec, int nrhs, double* partials, double* red, hipStream_t s) {
+                     int nvec, int nrhs, double* partials, double* npart, hipStream_t s) {
   const int nch = arn_nchunk(N);
-  dim3 grid(nch, nrhs, cdiv_i(nvec, kArnVec));
+  dim3 grid(nch, nrhs, cdiv_i(nvec, kArnVec) + (npart ? 1 : 0));
   if (f32)
     hipLaunchKernelGGL(k_block_dots<float2>, grid, dim3(256), 0, s, (const float2*)basis,
-                       basis_stride, (const float2*)T, N, nvec, nch, partials);
+                       basis_stride, (const float2*)T, N, nvec, nch, partials, npart);
   else
     hipLaunchKernelGGL(k_block_dots<double2>, grid, dim3(256), 0, s, (const double2*)basis,
-                       basis_stride, (const double2*)T, N, nvec, nch, partials);
-  hipLaunchKernelGGL(k_reduce_partials<2>, dim3(nrhs * nvec), dim3(256), 0, s, partials, nch, red);
+                       basis_stride, (const double2*)T, N, nvec, nch, partials, npart);
+}
+
+void launch_block_dots(bool f32, const void* basis, long basis_stride, const void* T, long N,
+                       int nvec, int nrhs, double* partials, double* red, hipStream_t s) {
+  launch_arn_dots(f32, basis, basis_stride, T, N, nvec, nrhs, partials, nullptr, s);
+  hipLaunchKernelGGL(k_reduce_partials<2>, dim3(nrhs * nvec), dim3(256), 0, s, partials,
+                     arn_nchunk(N), red);
 }
 
 void launch_gram(const double2* X, int nx, const double2* Y, int ny, long N, double* partials,
                  double2* G, hipStream_t s) {
   for (int j = 0; j < ny; ++j)
-    launch_arn_dots(false, X, N, Y + (long)j * N, N, nx, 1, partials, (double*)(G + (long)j * nx), s);
+    launch_block_dots(false, X, N, Y + (long)j * N, N, nx, 1, partials, (double*)(G + (long)j * nx), s);
 }
 
-void launch_arn_accum(const double* red, int nvec, int kmax, int j, bool first, double2* H,
-                      double2* hcur, int nrhs, hipStream_t s) {
-  hipLaunchKernelGGL(k_arn_accum, dim3(cdiv_i((long)nrhs * nvec, 256)), dim3(256), 0, s, red, nvec,
-                     kmax, j, (int)first, H, hcur, nrhs);
+void launch_arn_accum(const double* partials, long N, int nvec, int kmax, int j, bool first,
+                      double2* H, double2* hcur, int nrhs, hipStream_t s) {
+  hipLaunchKernelGGL(k_arn_accum, dim3(nvec, nrhs), dim3(256), 0, s, partials, arn_nchunk(N), kmax,
+                     j, (int)first, H, hcur);
 }
 
 void launch_arn_axpy(bool f32, const void* basis, long basis_stride, void* T, long N, int nvec,
-                     const double2* hcur, int kmax, int nrhs, double* partials, double* red,
-                     hipStream_t s) {
-  const int nch = arn_nchunk(N);
-  dim3 grid(nch, nrhs);
+                     const double2* hcur, int kmax, int nrhs, double* npart, hipStream_t s) {
+  dim3 grid(arn_nchunk(N), nrhs);
   if (f32)
     hipLaunchKernelGGL(k_block_axpy<float2>, grid, dim3(256), 0, s, (const float2*)basis,
-                       basis_stride, (float2*)T, N, nvec, hcur, kmax, partials);
+                       basis_stride, (float2*)T, N, nvec, hcur, kmax, npart);
   else
     hipLaunchKernelGGL(k_block_axpy<double2>, grid, dim3(256), 0, s, (const double2*)basis,
-                       basis_stride, (double2*)T, N, nvec, hcur, kmax, partials);
-  hipLaunchKernelGGL(k_reduce_partials<1>, dim3(nrhs), dim3(256), 0, s, partials, nch, red);
+                       basis_stride, (double2*)T, N, nvec, hcur, kmax, npart);
 }
 
 static void launch_norm2_parts(bool f32, const void* T, long N, int nrhs, double* partials,
@@ -1099,21 +1144,17 @@ void launch_norm2_part(bool f32, const void* T, long N, double* partials, hipStr
   launch_norm2_parts(f32, T, N, 1, partials, s);
 }
 
-void launch_arn_sub(const double* red_n, const double* red_tn, double2* H, int kmax, int j,
-                    double* scl, int* kstop, int* status, int nrhs, hipStream_t s) {
-  hipLaunchKernelGGL(k_arn_sub, dim3(cdiv_i(nrhs, 64)), dim3(64), 0, s, red_n, red_tn, H, kmax, j,
-                     scl, kstop, status, nrhs);
-}
-
-void launch_scale_copy(bool f32, const void* T, void* out, long N, const double* scl, int nrhs,
-                       hipStream_t s) {
+void launch_arn_next(bool f32, const void* T, void* out, long N, const double* npart,
+                     const double* tnpart, double2* H, int kmax, int j, int* kstop, int* status,
+                     int nrhs, hipStream_t s) {
+  const int nch = arn_nchunk(N);
   dim3 grid(chunks_for(N, 4096), nrhs);
   if (f32)
-    hipLaunchKernelGGL(k_scale_copy<float2>, grid, dim3(256), 0, s, (const float2*)T, (float2*)out,
-                       N, scl);
+    hipLaunchKernelGGL(k_arn_next<float2>, grid, dim3(256), 0, s, (const float2*)T, (float2*)out, N,
+                       npart, tnpart, nch, H, kmax, j, kstop, status);
   else
-    hipLaunchKernelGGL(k_scale_copy<double2>, grid, dim3(256), 0, s, (const double2*)T,
-                       (double2*)out, N, scl);
+    hipLaunchKernelGGL(k_arn_next<double2>, grid, dim3(256), 0, s, (const double2*)T,
+                       (double2*)out, N, npart, tnpart, nch, H, kmax, j, kstop, status);
 }
 
 int isign_tri_nwave(int nnode) { return cdiv_i(2L * nnode, 64); }

@@ -343,6 +343,70 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
+// Two values on their way down the tree of halves at once: lanes without bit OFF
+// return a + a(lane + OFF), the others b + b(lane - OFF), the sums that wave_sum
+// forms at this step.
+template <int OFF>
+__device__ __forceinline__ double lane_merge(double a, double b) {
+  static_assert(OFF == 32 || OFF == 16 || OFF == 8 || OFF == 4 || OFF == 2);
+  if constexpr (OFF >= 16) {
+    auto swap = [](int x, int y) {
+      if constexpr (OFF == 32) return __builtin_amdgcn_permlane32_swap(x, y, false, false);
+      else return __builtin_amdgcn_permlane16_swap(x, y, false, false);
+    };
+    const auto l = swap(__double2loint(a), __double2loint(b));
+    const auto h = swap(__double2hiint(a), __double2hiint(b));
+    return __hiloint2double(h[0], l[0]) + __hiloint2double(h[1], l[1]);
+  } else {
+    const bool up = threadIdx.x & OFF;
+    const double keep = up ? b : a, give = up ? a : b;
+    auto swap = [](int x) {  // lane ^ OFF
+      if constexpr (OFF == 8) return __builtin_amdgcn_update_dpp(0, x, 0x128, 0xf, 0xf, true);
+      else if constexpr (OFF == 2) return __builtin_amdgcn_update_dpp(0, x, 0x4e, 0xf, 0xf, true);
+      else
+        return __builtin_amdgcn_update_dpp(
+            0, __builtin_amdgcn_update_dpp(0, x, 0x141, 0xf, 0xf, true), 0x1b, 0xf, 0xf, true);
+    };
+    return keep + __hiloint2double(swap(__double2hiint(give)), swap(__double2loint(give)));
+  }
+}
+template <int NV, int OFF>
+__device__ __forceinline__ double wave_sums_from(double (&v)[NV]) {
+  if constexpr (NV == 1) {
+    double s = v[0];
+    if constexpr (OFF >= 8) s += lane_down<8>(s);
+    if constexpr (OFF >= 4) s += lane_down<4>(s);
+    if constexpr (OFF >= 2) s += lane_down<2>(s);
+    if constexpr (OFF >= 1) s += lane_down<1>(s);
+    return s;
+  } else {
+    double w[NV / 2];
+#pragma unroll
+    for (int j = 0; j < NV / 2; ++j) w[j] = lane_merge<OFF>(v[j], v[j + NV / 2]);
+    return wave_sums_from<NV / 2, OFF / 2>(w);
+  }
+}
+// Sums over the workgroup of NV (8, 16 or 32) values per thread, of value j in
+// thread j; the same sums as block_sum's, with NV + 5 - log2(NV) additions a
+// lane instead of 6 NV and a thread for each last one.  All threads call it; lds
+// holds NV doubles a wave.
+template <int NV>
+__device__ __forceinline__ double block_sums(double (&v)[NV], double* lds) {
+  static_assert(NV == 8 || NV == 16 || NV == 32);
+  constexpr int L = 64 / NV;  // lanes that end up with one value
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const double s = wave_sums_from<NV, 32>(v);
+  if (lane % L == 0) lds[wave * NV + lane / L] = s;
+  __syncthreads();
+  double a = 0.0;
+  if ((int)threadIdx.x < NV) {
+    a = lds[threadIdx.x];
+    for (int w = 1; w < (int)(blockDim.x >> 6); ++w) a += lds[w * NV + threadIdx.x];
+  }
+  __syncthreads();
+  return a;
+}
+
 // Sums `n` values per thread over the first nw waves of the workgroup (all its
 // threads call it); result valid in thread 0.  lds must hold nw * n doubles.
 template <int NV>

@@ -63,26 +63,32 @@ void launch_replay(bool f32, const void* T, void* ring, long ring_stride, long N
 void launch_overlap(const double2* b, double2* y, long N, int V, hipStream_t s);
 
 int arn_nchunk(long N);
+// partials of V_i^H T (i < nvec), [nrhs][nvec][arn_nchunk(N)]; npart (may be null):
+// those of |T|^2, [nrhs][arn_nchunk(N)]
 void launch_arn_dots(bool f32, const void* basis, long basis_stride, const void* T, long N,
-                     int nvec, int nrhs, double* partials, double* red, hipStream_t s);
+                     int nvec, int nrhs, double* partials, double* npart, hipStream_t s);
+// the dots themselves: red[nrhs][nvec]
+void launch_block_dots(bool f32, const void* basis, long basis_stride, const void* T, long N,
+                       int nvec, int nrhs, double* partials, double* red, hipStream_t s);
 // G = X^H Y (nx x ny, column-major) for column-major FP64 blocks with
 // leading dimension N: one dot launch per column of Y (tall-skinny products
 // that library GEMMs tile poorly); partials hold nx * arn_nchunk(N) * 2.
 void launch_gram(const double2* X, int nx, const double2* Y, int ny, long N, double* partials,
                  double2* G, hipStream_t s);
-void launch_arn_accum(const double* red, int nvec, int kmax, int j, bool first, double2* H,
-                      double2* hcur, int nrhs, hipStream_t s);
+void launch_arn_accum(const double* partials, long N, int nvec, int kmax, int j, bool first,
+                      double2* H, double2* hcur, int nrhs, hipStream_t s);
+// T -= sum_i hcur_i V_i; npart (may be null): partials of |T|^2 as above
 void launch_arn_axpy(bool f32, const void* basis, long basis_stride, void* T, long N, int nvec,
-                     const double2* hcur, int kmax, int nrhs, double* partials, double* red,
-                     hipStream_t s);
+                     const double2* hcur, int kmax, int nrhs, double* npart, hipStream_t s);
+// out = T / |T| and H[j+1][j] = |T| from the partials of |T|^2; tnpart: those of
+// the vector before its orthogonalisation (lucky breakdown)
+void launch_arn_next(bool f32, const void* T, void* out, long N, const double* npart,
+                     const double* tnpart, double2* H, int kmax, int j, int* kstop, int* status,
+                     int nrhs, hipStream_t s);
 // partials of |T|^2 of one source, arn_nchunk(N) of them
 void launch_norm2_part(bool f32, const void* T, long N, double* partials, hipStream_t s);
 void launch_norm2(bool f32, const void* T, long N, int nrhs, double* partials, double* red,
                   hipStream_t s);
-void launch_arn_sub(const double* red_n, const double* red_tn, double2* H, int kmax, int j,
-                    double* scl, int* kstop, int* status, int nrhs, hipStream_t s);
-void launch_scale_copy(bool f32, const void* T, void* out, long N, const double* scl, int nrhs,
-                       hipStream_t s);
 
 // Inner sign by the tau = e^u trapezoid rule.  The tridiagonal form runs its
 // shifted solves in launches of at most isign_wave_chunk(nrhs) waves of 64

@@ -138,3 +138,29 @@ def test_eigentriples_both_forms_of_the_inner_solves(dims, m, tol):
     assert float(rr.max()) <= 2 * tol and float(rl.max()) <= 2 * tol
     d.close()
     lat.close()
+
+
+@pytest.mark.parametrize("k", [1, 2, 8, 9, 16, 17, 32, 33, 49])
+def test_arnoldi_vector_groups(k):
+    """Arnoldi at sizes around the groups of 8 vectors of the dots and of 16 (two in
+    turn) of the subtraction, on a field whose last workgroup has a remainder (12 x
+    274 entries), two sources, against the oracle: sgn(H) e_1 is accepted at a
+    coarse/fine difference quad_err, which bounds the coarse rule's error, and
+    orthogonalised twice both bases agree to rounding, hence 2 quad_err + 1e-10."""
+    import paper_0810_4228_amd as ovs
+    from gpu_util import to_dev
+    from oracle import dirac
+    dims = (3, 2, 5, 7)
+    U = synth.random_links(dims, 0.5, seed=51)
+    A = dirac.csr_A(dims, U, MW, 0.3)
+    b = synth.gaussian_sources(dims, 2, seed=52)
+    lat = ovs.Lattice(dims, precision="f64")
+    lat.set_links(to_dev(U))
+    lat.set_params(MW, 0.3)
+    y, info, st = lat.sign_apply(to_dev(b), k, method="arnoldi")
+    for r in range(2):
+        e = rel(y.cpu().numpy()[r], krylov.arnoldi_apply(lambda v: A @ v, b[r], k))
+        say(f"arnoldi k={k} source {r}: {e:.1e}, quad_err {info[r]['quad_err']:.1e}")
+        assert info[r]["k_used"] == k
+        assert e <= 2 * info[r]["quad_err"] + 1e-10
+    lat.close()
