@@ -233,12 +233,12 @@ int max_nodes() {
   return nn;
 }
 
-// Scratch of the inner sign (sizes in ovs_krylov.h): mult, swp, part for
+// Scratch of the inner sign (sizes in ovs_krylov.h): minor, expo, part for
 // the tridiagonal form; ys, acc, and xtmp [nrhs][kmax], kv [nrhs] for the
 // refinement levels, of the Hessenberg form.
 struct InnerScratch {
-  double2* mult = nullptr;
-  unsigned long long* swp = nullptr;
+  double2* minor = nullptr;
+  int* expo = nullptr;
   double2* part = nullptr;
   double2* ys = nullptr;
   double2* acc = nullptr;
@@ -318,7 +318,7 @@ ovs_status inner_sign_tri(ovs_lattice_s* l, const double2* alpha, const double* 
       nw = std::max(nw, w);
     }
     launch_isign_tri(alpha, beta, gamma, kmax, task, kstop, status, nrhs, nw,
-                     isign_wave_chunk(nrhs), first, sc.mult, sc.swp, sc.part, x, kout, res, s);
+                     isign_wave_chunk(nrhs), first, sc.minor, sc.expo, sc.part, x, kout, res, s);
     OVS_HIP(hipGetLastError());
     if (then) {
       st = then();
@@ -1160,10 +1160,10 @@ static ovs_status sign_apply_impl(ovs_lattice l, ovs_deflation defl, int32_t n_d
     double2 *Bq, *bR, *bL, *yex, *Y;
     char *basis, *wbuf, *T, *S;
     double *part1, *part2, *dpart, *CD, *spart, *sums, *sumsb, *nb;
-    double2 *alpha, *gamma, *sw, *coef, *x, *mult, *part, *H, *hcur, *ys, *acc, *xtmp;
+    double2 *alpha, *gamma, *sw, *coef, *x, *minor, *part, *H, *hcur, *ys, *acc, *xtmp;
     double *beta, *sv, *tnorm2, *qerr, *red, *apart, *npart, *tnpart, *dnorm;
     int *kstop, *status, *rhs_map, *ints, *kused, *pidx, *kv;
-    unsigned long long* swp;
+    int* expo;
     double2* probes;
     unsigned* bar;
   } B{};
@@ -1212,8 +1212,8 @@ static ovs_status sign_apply_impl(ovs_lattice l, ovs_deflation defl, int32_t n_d
     }
     if (!arn) {
       const int wchunk = isign_wave_chunk(nr);
-      B.mult = a.take<double2>((size_t)nr * wchunk * K * 64);
-      B.swp = a.take<unsigned long long>((size_t)nr * wchunk * isign_swp_words(K) * 64);
+      B.minor = a.take<double2>((size_t)nr * wchunk * K * 64);
+      B.expo = a.take<int>((size_t)nr * wchunk * isign_expo_words(K) * 64);
       B.part = a.take<double2>((size_t)nr * nwave_max * 2 * K);
       B.dnorm = a.take<double>((size_t)nr * K);
       if (monitor) {
@@ -1462,7 +1462,7 @@ static ovs_status sign_apply_impl(ovs_lattice l, ovs_deflation defl, int32_t n_d
   std::vector<double> best_est(nr, HUGE_VAL);
   std::vector<int> since_best(nr, 0);
   std::vector<char> stalled(nr, 0);
-  InnerScratch isc{B.mult, B.swp, B.part, B.ys, B.acc, B.xtmp, B.kv};
+  InnerScratch isc{B.minor, B.expo, B.part, B.ys, B.acc, B.xtmp, B.kv};
   const std::vector<double> qtarget = quad_targets(tol, nr);
   std::vector<double> errh;
   std::vector<IsignResult> ires;
@@ -2196,8 +2196,8 @@ static ovs_status inner_sign_entry(ovs_lattice l, bool tri, int batch, int k, co
       al = a.take<double2>((size_t)batch * k);
       be = a.take<double>((size_t)batch * k);
       ga = a.take<double2>((size_t)batch * k);
-      sc.mult = a.take<double2>((size_t)batch * wchunk * k * 64);
-      sc.swp = a.take<unsigned long long>((size_t)batch * wchunk * isign_swp_words(k) * 64);
+      sc.minor = a.take<double2>((size_t)batch * wchunk * k * 64);
+      sc.expo = a.take<int>((size_t)batch * wchunk * isign_expo_words(k) * 64);
       sc.part = a.take<double2>((size_t)batch * nwave * 2 * k);
     } else {
       H = a.take<double2>((size_t)batch * k * k);

@@ -545,10 +545,7 @@ __global__ void __launch_bounds__(256) k_arn_next(const T2* __restrict__ T, T2* 
 // 1/(z-i tau)] d tau, tau = e^u, trapezoidal rule in u:
 //   x ~= (h/pi) sum_n e^{u_n} [ (T + i e^{u_n})^{-1} e_1 + (T - i e^{u_n})^{-1} e_1 ].
 // The nodes with even n form the rule with step 2h; their difference gives
-// the error estimate.  Each shifted solve (T + i sigma) y = e_1 eliminates the
-// subdiagonal from the bottom up by column operations with column pivoting:
-// M P E = R upper triangular, so y = P E e_1 / R_00 with P E stored as one
-// multiplier and one swap bit per column.
+// the error estimate.
 // ===========================================================================
 
 // One thread per (source r, shifted solve q): q = 2*node + (0: +tau, 1: -tau).
@@ -557,31 +554,37 @@ __global__ void __launch_bounds__(256) k_arn_next(const T2* __restrict__ T, T2* 
 // first rule, then those of the second.  Wave results are reduced over lanes:
 // part[r][wave][2][kmax] complex (fine rule, coarse rule), wave = wave0 +
 // blockIdx.x of nwave in all; waves beyond a source's nodes write nothing.  A
-// launch covers one chunk of waves; the multipliers of a chunk live in mult
-// [r][blockIdx.x][kmax][64] and swp, which the next chunk (ordered on the
-// stream) reuses.
+// launch covers one chunk of waves; the minors of a chunk live in minor
+// [r][blockIdx.x][kmax][64] and their exponents in expo, which the next chunk
+// (ordered on the stream) reuses.
 //
-// swp holds the swaps as bits: word w of a wave and lane is steps 64 w to
-// 64 w + 63 from the bottom, isign_swp_words(kmax) words.
+// (T + i sigma) y = e_1 by the trailing principal minors theta_j of T + i sigma
+// (rows and columns j to k-1; Usmani, Linear Algebra Appl. 212/213 (1994) 413):
+//   theta_j = a_j theta_{j+1} - gamma_j beta_j theta_{j+2},  theta_k = 1,
+//   y_j = (-1)^j beta_0 ... beta_{j-1} theta_{j+1} / theta_0.
+// A computed theta_j is the exact combination of the two before it for entries
+// changed by a few rounding errors each, and every a_j and gamma_j beta_j enters
+// one of them only: the computed minors are those of a matrix equal to T + i sigma
+// to rounding, entry by entry, also through zero or tiny minors, so no pivoting;
+// y_j adds one relative rounding error per factor.  The pair of minors is scaled
+// by a power of two every kMinors steps (exact), expo holding the exponents.
 //
-// Bound by the latency of one wave's serial chain, k elimination steps and k
-// rows back, whatever the number of waves.  A step is two dependent quotients
-// and a complex multiply-add: the pivot test compares squares (hypot only for
-// near ties and extreme values), both pivot cases share one quotient by
-// selects (the subdiagonal is real, so Smith's quotient by it is two plain
-// ones), and the coefficients of 64 steps sit in the lanes of the wave, loaded
-// a block ahead and read by readlane.  The rows back load their multipliers a
-// block of 16 ahead.  One source, k = 375 on average (the checks of an 8^4
-// solve): 217 us a launch with hypot, three divergent divisions and one
-// scalar load per step, 130 us so.
+// Bound by the latency and issue of one wave's serial chain, whatever the number
+// of waves: a step is two dependent fused multiply-adds, with the coefficients of
+// 64 steps in the lanes of the wave, loaded a block ahead and read by readlane.
+// The rows have no chain; their minors load a block of 16 ahead.  One source, k =
+// 375 on average (the checks of an 8^4 solve): 149 us a launch by elimination
+// with column pivoting (two dependent quotients a step), 65 us so; against 113-bit
+// arithmetic both are within 3e-15 for Lanczos matrices of 4^4 and 6^4 (k to 600).
+constexpr int kMinors = 8;
 __global__ void __launch_bounds__(64) k_isign_tri(const double2* __restrict__ alpha,
                                                   const double* __restrict__ beta,
                                                   const double2* __restrict__ gamma, int kmax,
                                                   const IsignTask* __restrict__ task,
                                                   const int* __restrict__ kstop,
                                                   int wave0, int nwave,
-                                                  double2* __restrict__ mult,
-                                                  unsigned long long* __restrict__ swp,
+                                                  double2* __restrict__ minor,
+                                                  int* __restrict__ expo,
                                                   double2* __restrict__ part) {
   const int r = blockIdx.y;
   const IsignTask tk = task[r];
@@ -599,108 +602,134 @@ __global__ void __launch_bounds__(64) k_isign_tri(const double2* __restrict__ al
   const double tau = exp(node * qn.h);
   const double sig = live ? ((q & 1) ? -tau : tau) : 1.0;
   const double wfine = live ? qn.h / M_PI * tau : 0.0;
-  const double wcoarse = (live && ((node & 1) == 0)) ? 2.0 * qn.h / M_PI * tau : 0.0;
   const double2* al = alpha + (long)r * kmax;
   const double* be = beta + (long)r * kmax;
   const double2* ga = gamma + (long)r * kmax;
-  const long mbase = ((long)(r * gridDim.x + blockIdx.x) * kmax) * 64 + lane;
-  unsigned long long* swap_w =
-      swp + (long)(r * gridDim.x + blockIdx.x) * isign_swp_words(kmax) * 64 + lane;
+  const long wbase = (long)(r * gridDim.x + blockIdx.x);
+  double2* th = minor + wbase * kmax * 64 + lane;             // theta_j at [j * 64]
+  int* ex = expo + wbase * isign_expo_words(kmax) * 64 + lane;  // by (k - 1 - j) / kMinors
   double2* part_r = part + ((long)r * nwave + wave) * 2 * kmax;
-  // elimination from the bottom: current column j holds (cu: row j-1, cd: row j)
-  Cx<double> cu = (k >= 2) ? c64(ga[k - 2]) : Cx<double>{0, 0};
-  Cx<double> cd = c64(al[k - 1]) + Cx<double>{0.0, sig};
-  // lane l of a block starting at column j0 holds the entries of column
-  // j0 - l (below column 1: clamped loads, never used)
+  // lane l of a block starting at row j0 holds the entries of row j0 - l (below
+  // row 0: clamped loads, never used): a_j without the shift and gamma_j beta_j
   struct Block {
     double2 a, g;
     double b;
   };
   auto load_block = [&](int j0) {
-    const int j = j0 - lane;
+    const int j = max(j0 - lane, 0);
     Block o;
-    o.a = al[max(j - 1, 0)];
-    o.b = be[max(j - 1, 0)];
-    o.g = ga[max(j - 2, 0)];
-    if (j < 2) o.g = make_double2(0.0, 0.0);
+    o.a = al[j];
+    o.b = be[j];
+    o.g = ga[j];
+    if (j >= k - 1) {  // theta_{k+1} = 0; the last row's couplings may be unset
+      o.g = make_double2(0.0, 0.0);
+      o.b = 0.0;
+    }
     return o;
   };
+  Cx<double> t1 = {1.0, 0.0}, t2 = {0.0, 0.0};  // theta_{j+1}, theta_{j+2} times 2^-e
+  int e = 0;
   Block nxt = load_block(k - 1);
-  for (int j0 = k - 1; j0 >= 1; j0 -= 64) {
+  for (int j0 = k - 1; j0 >= 0; j0 -= 64) {
     const Block cur = nxt;
     nxt = load_block(j0 - 64);
-    const int n = min(64, j0);
-    unsigned long long swaps = 0;
-#pragma unroll 2
-    for (int l = 0; l < n; ++l) {
-      const int j = j0 - l;
-      const Cx<double> du = {lane_value(cur.g.x, l), lane_value(cur.g.y, l)};
-      const Cx<double> dm = Cx<double>{lane_value(cur.a.x, l), lane_value(cur.a.y, l)} +
-                            Cx<double>{0.0, sig};
-      const double dd = lane_value(cur.b, l);
-      bool sw;
-      const Cx<double> m = pivot_quotient(dd, cd, sw);
-      // sw: column = (-m du, cu - m dm), else (du, dm - m cu)
-      const Cx<double> t = cmul(m, csel(sw, dm, cu));
-      const Cx<double> nu_ = -cmul(m, du);
-      cd = csel(sw, cu, dm) - t;
-      cu = csel(sw, nu_, du);
-      mult[mbase + (long)j * 64] = d2(m);
-      swaps |= (unsigned long long)sw << l;
+    const double cre = cur.b * cur.g.x, cim = cur.b * cur.g.y;
+    const int n = min(64, j0 + 1);
+    auto step = [&](int l) {
+      const double are = lane_value(cur.a.x, l), aim = lane_value(cur.a.y, l) + sig;
+      const double gr = lane_value(cre, l), gi = lane_value(cim, l);
+      const double ur = fma(gi, t2.im, -(gr * t2.re)), ui = -fma(gr, t2.im, gi * t2.re);
+      const Cx<double> t0 = {fma(are, t1.re, fma(-aim, t1.im, ur)),
+                             fma(are, t1.im, fma(aim, t1.re, ui))};
+      th[(long)(j0 - l) * 64] = d2(t0);
+      t2 = t1;
+      t1 = t0;
+    };
+    for (int l0 = 0; l0 < n; l0 += kMinors) {
+      if (l0 + kMinors <= n) {
+#pragma unroll
+        for (int l = 0; l < kMinors; ++l) step(l0 + l);
+      } else {
+        for (int l = l0; l < n; ++l) step(l);
+      }
+      ex[(long)((k - 1 - j0 + l0) / kMinors) * 64] = e;
+      const double top = fmax(fmax(fabs(t1.re), fabs(t1.im)), fmax(fabs(t2.re), fabs(t2.im)));
+      const int s = __builtin_amdgcn_frexp_exp(top);
+      t1 = {__builtin_amdgcn_ldexp(t1.re, -s), __builtin_amdgcn_ldexp(t1.im, -s)};
+      t2 = {__builtin_amdgcn_ldexp(t2.re, -s), __builtin_amdgcn_ldexp(t2.im, -s)};
+      e += s;
     }
-    swap_w[(long)((k - 1 - j0) >> 6) * 64] = swaps;
   }
-  const Cx<double> inv_r00 = cdiv(Cx<double>{1.0, 0.0}, cd);
-  // z = P E e_1 streamed out top-down; row j-1 is final after column j.  The
-  // weighted rows of the 64 lanes are buffered in LDS for kRows rows at a time
-  // and summed over the lanes in a fixed order, one (row, part) per lane.
-  constexpr int kRows = 16;
-  __shared__ double rows[kRows][4][65];  // [row][fine re, fine im, coarse re, coarse im][lane]
-  Cx<double> cur = inv_r00;
-  // a block's multipliers and swaps, loaded together and one block ahead of
-  // their use (rows from k on clamped to row k-1, never used)
+  const Cx<double> inv = scale(wfine, cdiv(Cx<double>{1.0, 0.0}, t1));  // weight / theta_0
+  const int e0 = e;
+  // The weighted rows of the 64 lanes are buffered in LDS for two groups of minors
+  // at a time and summed over the lanes of even nodes and of odd nodes (the coarse
+  // rule takes the even ones at twice the weight), in a fixed order, one (row,
+  // part, parity) per lane.  Row j takes theta_{j+1}: the blocks start ahead of
+  // row 0 where that aligns them with the groups.
+  constexpr int kRows = 2 * kMinors;
+  static_assert(kRows == 16);
+  __shared__ double rows[kRows][2][65];  // [row][re, im][lane]
+  // a block's minors and the exponents of its groups, loaded together and one
+  // block ahead of their use (clamped outside the matrix)
   double2 mb[kRows], mn[kRows];
-  unsigned long long sb[2], sn[2];  // words of the block's first and last row
-  auto word = [&](int j) { return max(k - 1 - j, 0) >> 6; };
+  int sb[2], sn[2];
+  double bb, bn;  // lane t: beta_{j-1} of row j = j0 + t
   auto load_rows = [&](int j0) {
 #pragma unroll
-    for (int t = 0; t < kRows; ++t) mn[t] = mult[mbase + (long)min(j0 + t, k - 1) * 64];
-    sn[0] = swap_w[(long)word(j0) * 64];
-    sn[1] = swap_w[(long)word(j0 + kRows - 1) * 64];
+    for (int t = 0; t < kRows; ++t) mn[t] = th[(long)min(max(j0 + t + 1, 0), k - 1) * 64];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) sn[u] = ex[(long)(max(k - 2 - j0 - u * kMinors, 0) / kMinors) * 64];
+    const int jb = j0 + (lane & (kRows - 1)) - 1;
+    bn = be[min(max(jb, 0), k - 1)];
+    if (jb < 0) bn = -1.0;
   };
-  if (k > 1) load_rows(1);
-  for (int j0 = 1; j0 <= k; j0 += kRows) {
-    const int nrow = min(kRows, k - j0 + 1);
+  const int parity = qn.n0 & 1;
+  double bm = 1.0;  // (-1)^j beta_0 ... beta_{j-1} = bm 2^bx
+  int bx = 0;
+  const int start = -((kMinors + 1 - k % kMinors) % kMinors);  // (k - 2 - start) % kMinors == kMinors - 1
+  load_rows(start);
+  for (int j0 = start; j0 < k; j0 += kRows) {
 #pragma unroll
     for (int t = 0; t < kRows; ++t) mb[t] = mn[t];
     sb[0] = sn[0];
     sb[1] = sn[1];
-    if (j0 + kRows <= k) load_rows(j0 + kRows);
-    // rows beyond k (the last block's tail) are formed from clamped entries and
-    // not read
+    bb = bn;
+    if (j0 + kRows < k) load_rows(j0 + kRows);
+    // rows before 0 and from k on are formed from clamped entries and not read
 #pragma unroll
-    for (int t = 0; t < kRows; ++t) {
-      const Cx<double> nw = -cmul(c64(mb[t]), cur);
-      const int j = j0 + t;
-      const unsigned long long w = word(j) == word(j0) ? sb[0] : sb[1];
-      const bool swapped = (w >> ((k - 1 - j) & 63)) & 1;
-      const bool take = swapped & (j < k);  // row k-1: the current value
-      const Cx<double> fin = csel(take, nw, cur);
-      cur = csel(swapped, cur, nw);
-      rows[t][0][lane] = wfine * fin.re;
-      rows[t][1][lane] = wfine * fin.im;
-      rows[t][2][lane] = wcoarse * fin.re;
-      rows[t][3][lane] = wcoarse * fin.im;
+    for (int u = 0; u < 2; ++u) {
+      const int s = __builtin_amdgcn_frexp_exp(bm);
+      bm = __builtin_amdgcn_ldexp(bm, -s);
+      bx += s;
+      const bool end = j0 + u * kMinors >= k - 1;  // row k - 1: theta_k = 1
+      const int eg = bx + (end ? 0 : sb[u]) - e0;
+      const Cx<double> ig = {__builtin_amdgcn_ldexp(inv.re, eg), __builtin_amdgcn_ldexp(inv.im, eg)};
+      if (end) mb[u * kMinors] = make_double2(1.0, 0.0);
+#pragma unroll
+      for (int v = 0; v < kMinors; ++v) {
+        const int t = u * kMinors + v;
+        bm = -(bm * lane_value(bb, t));
+        const Cx<double> y = cmul(c64(mb[t]), ig);
+        rows[t][0][lane] = bm * y.re;
+        rows[t][1][lane] = bm * y.im;
+      }
     }
     __syncthreads();
     {
-      const int t = lane & (kRows - 1), c = lane / kRows;  // 16 rows x 4 parts = 64 lanes
-      if (t < nrow) {
-        double acc = 0.0;
-#pragma unroll 16
-        for (int l = 0; l < 64; ++l) acc += rows[t][c][l];
-        double* out = reinterpret_cast<double*>(part_r + (c < 2 ? 0 : kmax) + (j0 - 1 + t));
-        out[c & 1] = acc;
+      const int t = lane & (kRows - 1), c = (lane >> 4) & 1, odd = lane >> 5;
+      const double* row = rows[t][c] + 2 * (odd ^ parity);
+      double acc = 0.0;
+#pragma unroll
+      for (int l = 0; l < 64; l += 4) {
+        acc += row[l];
+        acc += row[l + 1];
+      }
+      const double other = __shfl_xor(acc, 32);
+      const int j = j0 + t;
+      if (j >= 0 && j < k) {
+        double* out = reinterpret_cast<double*>(part_r + (odd ? kmax : 0) + j);
+        out[c] = odd ? 2.0 * other : acc + other;
       }
     }
     __syncthreads();
@@ -1161,11 +1190,11 @@ int isign_tri_nwave(int nnode) { return cdiv_i(2L * nnode, 64); }
 
 void launch_isign_tri(const double2* alpha, const double* beta, const double2* gamma, int kmax,
                       const IsignTask* task, const int* kstop, const int* status, int nrhs,
-                      int nwave, int chunk, bool first, double2* mult, unsigned long long* swp,
+                      int nwave, int chunk, bool first, double2* minor, int* expo,
                       double2* part, double2* x, int* kout, IsignResult* res, hipStream_t s) {
   for (int w0 = 0; w0 < nwave; w0 += chunk)
     hipLaunchKernelGGL(k_isign_tri, dim3(std::min(chunk, nwave - w0), nrhs), dim3(64), 0, s, alpha,
-                       beta, gamma, kmax, task, kstop, w0, nwave, mult, swp, part);
+                       beta, gamma, kmax, task, kstop, w0, nwave, minor, expo, part);
   hipLaunchKernelGGL(k_isign_final, dim3(nrhs), dim3(1024), 0, s, part, nwave, kmax, task, kstop,
                      status, (int)first, x, kout, res);
 }

@@ -92,8 +92,8 @@ void launch_norm2(bool f32, const void* T, long N, int nrhs, double* partials, d
 
 // Inner sign by the tau = e^u trapezoid rule.  The tridiagonal form runs its
 // shifted solves in launches of at most isign_wave_chunk(nrhs) waves of 64
-// solves per source (mult: [nrhs][chunk][kmax][64]; swp: [nrhs][chunk]
-// [isign_swp_words(kmax)][64]; part: [nrhs][all waves][2][kmax]); the Hessenberg
+// solves per source (minor: [nrhs][chunk][kmax][64]; expo: [nrhs][chunk]
+// [isign_expo_words(kmax)][64]; part: [nrhs][all waves][2][kmax]); the Hessenberg
 // form kIsignHessChunk solves per source (ys: [nrhs][kIsignHessChunk][kmax];
 // acc: [nrhs][2][kmax]).
 constexpr int kIsignHessChunk = 1024;
@@ -117,7 +117,7 @@ struct IsignResult {
   int k, kstop, status;
 };
 int isign_tri_nwave(int nnode);
-// A launch takes about k sequential elimination steps whatever its number of
+// A launch takes about k sequential steps of the minors whatever its number of
 // waves, until the waves of a compute unit's SIMDs share their issue slots: the
 // chunk holds every solve of the rules down to step 1/16 (43 waves), and for up
 // to five sources those of 1/32 (86) or all (171).  Not for more: a chunk takes
@@ -126,13 +126,13 @@ inline int isign_wave_chunk(int nrhs) {
   const int c = 512 / nrhs;
   return nrhs > 5 ? 48 : c > 172 ? 172 : c;
 }
-// 64-bit words that hold one swap bit for each of kmax elimination steps
-__host__ __device__ inline int isign_swp_words(int kmax) { return (kmax + 63) / 64; }
+// exponents of kmax minors, one for each eight
+__host__ __device__ inline int isign_expo_words(int kmax) { return (kmax + 7) / 8; }
 // task, res: [nrhs] (readable and writable by the device); nwave: the largest
 // number of waves of a source's rules together (the part stride).
 void launch_isign_tri(const double2* alpha, const double* beta, const double2* gamma, int kmax,
                       const IsignTask* task, const int* kstop, const int* status, int nrhs,
-                      int nwave, int chunk, bool first, double2* mult, unsigned long long* swp,
+                      int nwave, int chunk, bool first, double2* minor, int* expo,
                       double2* part, double2* x, int* kout, IsignResult* res, hipStream_t s);
 void launch_isign_hess(const double2* H, int kmax, const int* kvec, int nrhs, double h, int n0,
                        int nnode, double2* ys, double2* acc, double2* x, double* err,
