@@ -360,9 +360,9 @@ ovs_status compute_eigentriples(ovs_lattice_s* l, int m, double tol, int max_ite
   // microseconds of work per launch, so launch overhead would dominate the solve
   // (4^3 x 8, 8 triples: 712 ms with graphs of two steps, 600 with eight).  A step
   // is bound by its launches up to there: three where the stencil runs with one
-  // wave per hop (12.9 us a step on 4^3 x 8, 14.8 on 8^4, 63.6 on 16^4, against
+  // wave per hop (12.9 us a step on 4^3 x 8, 14.9 on 8^4, 59.2 on 16^4, against
   // 16.3, 17.8 and 64.3 in five), five on larger lattices, whose direction is
-  // read eight times by the stencil (16^3 x 24: 88.7 in three, 86.5 in five with
+  // read eight times by the stencil (16^3 x 24: 83.6 in three, 86.5 in five with
   // one thread per site).
   const bool one_wave_hops = default_tuning(false, g, 1).hops != 0;
   struct CgGraph {

@@ -37,22 +37,9 @@ __device__ __forceinline__ int neighbour(int s, const Geometry& g) {
 template <typename R, bool CANON> struct HopField;
 template <typename R> struct HopField<R, false> {
   typename Vec2<R>::T* f;
-  __device__ void head() const {}
-  struct Spinor {
-    Cx<R> v[12];
-  };
-  struct Pair {
-    Cx<R> a, b;
-  };
-  __device__ void load(int Vs, int s, Spinor& p) const { load_spinor_u(f, Vs, s, false, p.v); }
-  __device__ void form(const Spinor& p, Cx<R> (&o)[12]) const {
-#pragma unroll
-    for (int c = 0; c < 12; ++c) o[c] = p.v[c];
-  }
-  __device__ void load(int Vs, int s, int q, Pair& p) const { load_pair(Vs, s, q, p.a, p.b); }
-  __device__ void form(const Pair& p, int, int, int, bool, Cx<R>& a, Cx<R>& b) const {
-    a = p.a;
-    b = p.b;
+  static constexpr bool kFormed = false;
+  __device__ void load(int Vs, int s, bool g5, Cx<R> (&p)[12]) const {
+    load_spinor_u(f, Vs, s, g5, p);
   }
   __device__ void load_pair(int Vs, int s, int q, Cx<R>& a, Cx<R>& b) const {
     ld_pair(pair_at(f + (long)q * 2 * Vs, s), a, b);
@@ -64,28 +51,17 @@ template <typename R> struct HopField<R, false> {
 template <typename R> struct HopField<R, true> {
   double2* f;
   __device__ static Cx<R> conv(double2 v) { return {(R)v.x, (R)v.y}; }
-  __device__ void head() const {}
-  struct Spinor {
-    double2 v[12];
-  };
-  struct Pair {
-    double2 a, b;
-  };
-  __device__ void load(int, int s, Spinor& p) const {
+  static constexpr bool kFormed = false;
+  __device__ void load(int, int s, bool g5, Cx<R> (&p)[12]) const {
 #pragma unroll
-    for (int c = 0; c < 12; ++c) p.v[c] = f[12L * s + c];
+    for (int c = 0; c < 12; ++c) {
+      p[c] = conv(f[12L * s + c]);
+      if (g5 && c >= 6) p[c] = -p[c];
+    }
   }
-  __device__ void form(const Spinor& p, Cx<R> (&o)[12]) const {
-#pragma unroll
-    for (int c = 0; c < 12; ++c) o[c] = conv(p.v[c]);
-  }
-  __device__ void load(int, int s, int q, Pair& p) const {
-    p.a = f[12L * s + 2 * q];
-    p.b = f[12L * s + 2 * q + 1];
-  }
-  __device__ void form(const Pair& p, int, int, int, bool, Cx<R>& a, Cx<R>& b) const {
-    a = conv(p.a);
-    b = conv(p.b);
+  __device__ void load_pair(int, int s, int q, Cx<R>& a, Cx<R>& b) const {
+    a = conv(f[12L * s + 2 * q]);
+    b = conv(f[12L * s + 2 * q + 1]);
   }
   __device__ void store_pair(int, int s, int q, Cx<R> a, Cx<R> b) const {
     f[12L * s + 2 * q] = make_double2((double)a.re, (double)a.im);
@@ -98,6 +74,7 @@ template <typename R> struct HopField<R, true> {
 // beta = rr' / rr, rr' the sum of the nch <= 256 partials (of the residual's
 // norm, in the order of a 256-thread reduction); workgroup 0 stores rr'.
 struct HopDirection {
+  static constexpr bool kFormed = true;
   const double2 *r, *p;
   double2* next;
   const double *rr, *part;
@@ -156,6 +133,16 @@ __device__ __forceinline__ void hop_half(const Cx<R> (&u)[9], const Cx<R> (&psi)
   project<R, NU, FWD ? -1 : +1>(psi, h);
   link_mul<R, FWD>(u, h, uh);
 }
+template <typename R, int NU, bool FWD, typename In>
+__device__ __forceinline__ void hop_half_at(const typename Vec2<R>::T* __restrict__ links,
+                                            const In& in, const Geometry& g, int s, bool g5in,
+                                            Cx<R> (&uh)[6]) {
+  const int n = neighbour<NU, FWD>(s, g);
+  Cx<R> u[9], psi[12];
+  load_link_u(links, g.Vs, NU, FWD ? s : n, u);
+  in.load(g.Vs, n, g5in, psi);
+  hop_half<R, NU, FWD>(u, psi, uh);
+}
 
 // acc += the share of component C (3 spin + colour) in the expansion of the hop
 // (NU, S) with half spinor h[i * 64], as expand_acc adds it.
@@ -207,40 +194,36 @@ __device__ __forceinline__ void hops_body(const typename Vec2<R>::T* __restrict_
   __shared__ double prod[PART ? 12 * 3 * 64 : 1];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const bool live = site0 + lane < g.V;
-  const int s = live ? site0 + lane : g.V - 1;  // lanes past the end load the last site
+  const int s = site0 + lane;
+  const bool live = s < g.V;
   const int q = wave;  // the component pair formed after the barrier (waves 0 to 5)
   Cx<R> p0 = {R(0), R(0)}, p1 = p0, w0 = p0, w1 = p0;
-  // all loads, then what the input's head does meanwhile, then the arithmetic
-  int n;
-  switch (wave) {
-    case 0: n = neighbour<0, false>(s, g); break;
-    case 1: n = neighbour<0, true>(s, g); break;
-    case 2: n = neighbour<1, false>(s, g); break;
-    case 3: n = neighbour<1, true>(s, g); break;
-    case 4: n = neighbour<2, false>(s, g); break;
-    case 5: n = neighbour<2, true>(s, g); break;
-    case 6: n = neighbour<3, false>(s, g); break;
-    default: n = neighbour<3, true>(s, g); break;
-  }
-  Cx<R> u[9];
-  typename In::Spinor nb;
-  typename In::Pair own;
-  load_link_u(links, g.Vs, wave >> 1, (wave & 1) ? s : n, u);
-  in.load(g.Vs, n, nb);
-  if (q < 6) {
-    in.load(g.Vs, s, q, own);
-    if (PART && part) ld_pair(pair_at(w + (long)q * 2 * g.Vs, s), w0, w1);
-  }
-  in.head();
-  if (q < 6) in.form(own, g.Vs, s, q, live, p0, p1);
-  {
-    Cx<R> psi[12], uh[6];
-    in.form(nb, psi);
-    if (g5in) {
-#pragma unroll
-      for (int c = 6; c < 12; ++c) psi[c] = -psi[c];
+  Cx<R> uh[6];
+  if constexpr (In::kFormed) {
+    // all loads, the input's head meanwhile, then the arithmetic (lanes past the
+    // end load the last site); takes 161 registers against 96 with each wave's
+    // loads in its own case, so for the small grids of latency-bound launches only
+    const int sl = live ? s : g.V - 1;
+    int n;
+    switch (wave) {
+      case 0: n = neighbour<0, false>(sl, g); break;
+      case 1: n = neighbour<0, true>(sl, g); break;
+      case 2: n = neighbour<1, false>(sl, g); break;
+      case 3: n = neighbour<1, true>(sl, g); break;
+      case 4: n = neighbour<2, false>(sl, g); break;
+      case 5: n = neighbour<2, true>(sl, g); break;
+      case 6: n = neighbour<3, false>(sl, g); break;
+      default: n = neighbour<3, true>(sl, g); break;
     }
+    Cx<R> u[9], psi[12];
+    typename In::Spinor nb;
+    typename In::Pair own;
+    load_link_u(links, g.Vs, wave >> 1, (wave & 1) ? sl : n, u);
+    in.load(g.Vs, n, nb);
+    if (q < 6) in.load(g.Vs, sl, q, own);
+    in.head();
+    if (q < 6) in.form(own, g.Vs, sl, q, live, p0, p1);
+    in.form(nb, psi);
     switch (wave) {
       case 0: hop_half<R, 0, false>(u, psi, uh); break;
       case 1: hop_half<R, 0, true>(u, psi, uh); break;
@@ -251,6 +234,23 @@ __device__ __forceinline__ void hops_body(const typename Vec2<R>::T* __restrict_
       case 6: hop_half<R, 3, false>(u, psi, uh); break;
       default: hop_half<R, 3, true>(u, psi, uh); break;
     }
+  } else if (live) {
+    if (q < 6) {
+      in.load_pair(g.Vs, s, q, p0, p1);
+      if (PART && part) ld_pair(pair_at(w + (long)q * 2 * g.Vs, s), w0, w1);
+    }
+    switch (wave) {
+      case 0: hop_half_at<R, 0, false>(links, in, g, s, g5in, uh); break;
+      case 1: hop_half_at<R, 0, true>(links, in, g, s, g5in, uh); break;
+      case 2: hop_half_at<R, 1, false>(links, in, g, s, g5in, uh); break;
+      case 3: hop_half_at<R, 1, true>(links, in, g, s, g5in, uh); break;
+      case 4: hop_half_at<R, 2, false>(links, in, g, s, g5in, uh); break;
+      case 5: hop_half_at<R, 2, true>(links, in, g, s, g5in, uh); break;
+      case 6: hop_half_at<R, 3, false>(links, in, g, s, g5in, uh); break;
+      default: hop_half_at<R, 3, true>(links, in, g, s, g5in, uh); break;
+    }
+  }
+  if (live) {
 #pragma unroll
     for (int i = 0; i < 6; ++i) hops[(wave * 6 + i) * 64 + lane] = T2{uh[i].re, uh[i].im};
   }
@@ -288,9 +288,8 @@ __device__ __forceinline__ void hops_body(const typename Vec2<R>::T* __restrict_
         prod[(c * 3 + 1) * 64 + lane] = d.im;
         prod[(c * 3 + 2) * 64 + lane] = cnorm2(t64);
       };
-      const Cx<R> zero = {R(0), R(0)};
-      put(2 * q, a0, live ? w0 : zero);
-      put(2 * q + 1, a1, live ? w1 : zero);
+      put(2 * q, a0, w0);
+      put(2 * q + 1, a1, w1);
     }
   }
   if (PART && part) {
