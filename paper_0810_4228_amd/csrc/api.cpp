@@ -233,9 +233,9 @@ int max_nodes() {
   return nn;
 }
 
-// Scratch of the inner sign (sizes in ovs_krylov.h): minor, expo, part for
-// the tridiagonal form; ys, acc, and xtmp [nrhs][kmax], kv [nrhs] for the
-// refinement levels, of the Hessenberg form.
+// Scratch of the inner sign (sizes in ovs_krylov.h): minor, expo (of `chunk`
+// waves a launch), part for the tridiagonal form; ys, acc, and xtmp [nrhs][kmax],
+// kv [nrhs] for the refinement levels, of the Hessenberg form.
 struct InnerScratch {
   double2* minor = nullptr;
   int* expo = nullptr;
@@ -244,6 +244,7 @@ struct InnerScratch {
   double2* acc = nullptr;
   double2* xtmp = nullptr;
   int* kv = nullptr;
+  int chunk = 0;
 };
 
 // Quadrature target of each source (see kQuadAccept); tol may be NULL.
@@ -318,7 +319,7 @@ ovs_status inner_sign_tri(ovs_lattice_s* l, const double2* alpha, const double* 
       nw = std::max(nw, w);
     }
     launch_isign_tri(alpha, beta, gamma, kmax, task, kstop, status, nrhs, nw,
-                     isign_wave_chunk(nrhs), first, sc.minor, sc.expo, sc.part, x, kout, res, s);
+                     sc.chunk, first, sc.minor, sc.expo, sc.part, x, kout, res, s);
     OVS_HIP(hipGetLastError());
     if (then) {
       st = then();
@@ -1171,6 +1172,7 @@ static ovs_status sign_apply_impl(ovs_lattice l, ovs_deflation defl, int32_t n_d
   const bool debug = (l->debug_flags & OVS_DEBUG_CHECKS) != 0;  // progress alone checks nothing
   const bool monitor = debug && !arn && !two_pass;  // biorthogonality rows need the stored V
   const int P = (int)std::min<long>(kProbe, 12L * l->g.V);
+  int wchunk = kIsignWaveChunk;  // waves per launch of the inner sign, chosen below
   auto layout = [&](Arena& a) {
     B.Bq = a.take<double2>((size_t)nr * N);
     if (m > 0) {
@@ -1185,7 +1187,9 @@ static ovs_status sign_apply_impl(ovs_lattice l, ovs_deflation defl, int32_t n_d
     if (!arn) B.wbuf = a.take<char>(3ul * nr * N * es);
     B.T = a.take<char>((size_t)nr * N * es);
     if (!arn) B.S = a.take<char>((size_t)nr * N * es);
-    B.part1 = a.take<double>((size_t)nr * nwg_d * 12);  // sums of tiles or of their quarters
+    // the dual stencil's sums (of tiles or of their quarters, 96 bytes a tile at most)
+    // are read before the result takes the same memory (192 bytes a site)
+    B.part1 = reinterpret_cast<double*>(B.Y);
     B.part2 = a.take<double>((size_t)nr * nwg_u * 4);
     B.spart = a.take<double>((size_t)nr * nch_start * 3);
     B.sums = a.take<double>((size_t)nr * 3);
@@ -1211,7 +1215,6 @@ static ovs_status sign_apply_impl(ovs_lattice l, ovs_deflation defl, int32_t n_d
       B.probes = a.take<double2>((size_t)nr * K * P);
     }
     if (!arn) {
-      const int wchunk = isign_wave_chunk(nr);
       B.minor = a.take<double2>((size_t)nr * wchunk * K * 64);
       B.expo = a.take<int>((size_t)nr * wchunk * isign_expo_words(K) * 64);
       B.part = a.take<double2>((size_t)nr * nwave_max * 2 * K);
@@ -1233,18 +1236,31 @@ static ovs_status sign_apply_impl(ovs_lattice l, ovs_deflation defl, int32_t n_d
     }
   };
   {
-    Arena sizing{nullptr};
-    layout(sizing);
+    auto bytes_for = [&](int chunk) {
+      wchunk = chunk;
+      Arena sizing{nullptr};
+      layout(sizing);
+      return sizing.off + 4096;
+    };
+    // what a call needs: with the narrow chunk, so that no part of a batch (a half,
+    // the FP32 group) needs more than the batch; the wide one where there is room
+    const size_t need = bytes_for(kIsignWaveChunk);
     if (ws_bytes) {
-      *ws_bytes = sizing.off + 4096;
+      *ws_bytes = need;
       return OVS_OK;
     }
+    const size_t wide = arn ? need : bytes_for(isign_wave_chunk(nr));
     char* base;
     if (user_ws) {
-      if (user_ws_bytes < sizing.off + 4096) return OVS_ERR_ARG;
+      if (user_ws_bytes < need) return OVS_ERR_ARG;
+      if (user_ws_bytes < wide) wchunk = kIsignWaveChunk;
       base = (char*)(((uintptr_t)user_ws + 255) & ~uintptr_t(255));
     } else {
-      ovs_status st = ensure_ws(l, sizing.off + 4096);
+      ovs_status st = ensure_ws(l, wide);
+      if (st == OVS_ERR_ALLOC && wide > need) {
+        wchunk = kIsignWaveChunk;
+        st = ensure_ws(l, need);
+      }
       if (st != OVS_OK) return st;
       base = (char*)l->ws;
     }
@@ -1462,7 +1478,7 @@ static ovs_status sign_apply_impl(ovs_lattice l, ovs_deflation defl, int32_t n_d
   std::vector<double> best_est(nr, HUGE_VAL);
   std::vector<int> since_best(nr, 0);
   std::vector<char> stalled(nr, 0);
-  InnerScratch isc{B.minor, B.expo, B.part, B.ys, B.acc, B.xtmp, B.kv};
+  InnerScratch isc{B.minor, B.expo, B.part, B.ys, B.acc, B.xtmp, B.kv, wchunk};
   const std::vector<double> qtarget = quad_targets(tol, nr);
   std::vector<double> errh;
   std::vector<IsignResult> ires;
@@ -2187,17 +2203,15 @@ static ovs_status inner_sign_entry(ovs_lattice l, bool tri, int batch, int k, co
   StreamScope scope(l);
   hipStream_t s = l->stream;
   const int nwave = isign_tri_nwave(max_nodes());
-  const int wchunk = isign_wave_chunk(batch);
   const int nq = std::min(kIsignHessChunk, 2 * max_nodes());
-  Arena sizing{nullptr};
   auto lay = [&](Arena& a, double2*& al, double*& be, double2*& ga, double2*& H, InnerScratch& sc,
                  double2*& xd, double*& ed) {
     if (tri) {
       al = a.take<double2>((size_t)batch * k);
       be = a.take<double>((size_t)batch * k);
       ga = a.take<double2>((size_t)batch * k);
-      sc.minor = a.take<double2>((size_t)batch * wchunk * k * 64);
-      sc.expo = a.take<int>((size_t)batch * wchunk * isign_expo_words(k) * 64);
+      sc.minor = a.take<double2>((size_t)batch * sc.chunk * k * 64);
+      sc.expo = a.take<int>((size_t)batch * sc.chunk * isign_expo_words(k) * 64);
       sc.part = a.take<double2>((size_t)batch * nwave * 2 * k);
     } else {
       H = a.take<double2>((size_t)batch * k * k);
@@ -2212,8 +2226,14 @@ static ovs_status inner_sign_entry(ovs_lattice l, bool tri, int batch, int k, co
   double2 *al = nullptr, *ga = nullptr, *H = nullptr, *xd = nullptr;
   double *be = nullptr, *ed = nullptr;
   InnerScratch sc;
-  lay(sizing, al, be, ga, H, sc, xd, ed);
-  ovs_status st = ensure_ws(l, sizing.off + 4096);
+  auto reserve = [&](int chunk) {
+    sc.chunk = chunk;
+    Arena sizing{nullptr};
+    lay(sizing, al, be, ga, H, sc, xd, ed);
+    return ensure_ws(l, sizing.off + 4096);
+  };
+  ovs_status st = reserve(isign_wave_chunk(batch));
+  if (st == OVS_ERR_ALLOC) st = reserve(kIsignWaveChunk);
   if (st != OVS_OK) return st;
   Arena a{(char*)l->ws};
   lay(a, al, be, ga, H, sc, xd, ed);

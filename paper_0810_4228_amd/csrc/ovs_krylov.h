@@ -91,9 +91,9 @@ void launch_norm2(bool f32, const void* T, long N, int nrhs, double* partials, d
                   hipStream_t s);
 
 // Inner sign by the tau = e^u trapezoid rule.  The tridiagonal form runs its
-// shifted solves in launches of at most isign_wave_chunk(nrhs) waves of 64
-// solves per source (minor: [nrhs][chunk][kmax][64]; expo: [nrhs][chunk]
-// [isign_expo_words(kmax)][64]; part: [nrhs][all waves][2][kmax]); the Hessenberg
+// shifted solves in launches of at most `chunk` waves of 64 solves per source
+// (kIsignWaveChunk or isign_wave_chunk(nrhs); minor: [nrhs][chunk][kmax][64]; expo:
+// [nrhs][chunk][isign_expo_words(kmax)][64]; part: [nrhs][all waves][2][kmax]); the Hessenberg
 // form kIsignHessChunk solves per source (ys: [nrhs][kIsignHessChunk][kmax];
 // acc: [nrhs][2][kmax]).
 constexpr int kIsignHessChunk = 1024;
@@ -118,13 +118,19 @@ struct IsignResult {
 };
 int isign_tri_nwave(int nnode);
 // A launch takes about k sequential steps of the minors whatever its number of
-// waves, until the waves of a compute unit's SIMDs share their issue slots: the
-// chunk holds every solve of the rules down to step 1/16 (43 waves), and for up
-// to five sources those of 1/32 (86) or all (171).  Not for more: a chunk takes
-// 1 KiB a wave, source and Krylov step, as much as the basis of a small lattice.
+// waves, until the waves of a compute unit's SIMDs share their issue slots, and a
+// wave takes 1 KiB a source and Krylov step.  The narrow chunk holds every solve of
+// the rules down to step 1/16 (43 waves); it is what a call needs, and never more
+// for a part of a batch than for the batch.  Where there is room, up to five sources
+// take a wide one, with 512 KiB a step for the solves of 1/32 (86 waves) or 1/64 (171)
+// in one launch: 8^4 in FP64 to 1e-10, 1 / 2 / 5 sources 12.4 / 14.9 / 22.4 ms against
+// 13.7 / 17.1 / 24.3.  From six on 512 KiB would still gain (6: 25.3 against 27.0), but
+// the two halves of a batch of 12 would hold 1 MiB a step, 2.8 times the FP32 basis
+// of 4^4 (the narrow ones 1.6).
+constexpr int kIsignWaveChunk = 48;
 inline int isign_wave_chunk(int nrhs) {
   const int c = 512 / nrhs;
-  return nrhs > 5 ? 48 : c > 172 ? 172 : c;
+  return nrhs > 5 ? kIsignWaveChunk : c > 172 ? 172 : c;
 }
 // exponents of kmax minors, one for each eight
 __host__ __device__ inline int isign_expo_words(int kmax) { return (kmax + 7) / 8; }
