@@ -210,7 +210,8 @@ ovs_status ovs_get_tuning(ovs_lattice lat, int32_t nrhs, int32_t* rhs_block, int
 /* Full tuned configuration for nrhs sources, host int32 [8]:
  * {stencil shape = 1000*staged tile + 100*rhs block + 10*lanes per site +
  *  streaming stores (staged tile: the workgroup's own input spinors copied to
- *  LDS, lanes per site 1 and rhs block <= 4 in FP32, <= 2 in FP64),
+ *  LDS, lanes per site 1 and rhs block <= 4 in FP32, <= 2 in FP64; lanes per
+ *  site 0: one wave per hop, with rhs block 1, workgroup size 64 and the rest 0),
  *  stencil workgroup size, stencil LDS cap KiB, stencil block order,
  *  Lanczos dual-stencil shape = 100*rhs block + 10*variant + streaming stores
  *  (bit 0: the dual stencil's outputs, bit 1: the new Lanczos vectors of the
@@ -222,8 +223,11 @@ ovs_status ovs_get_tuning(ovs_lattice lat, int32_t nrhs, int32_t* rhs_block, int
  *  operator and one source per workgroup, marching along t through the XCD's
  *  time chunk with the time neighbours in registers and the plane in LDS, FP32
  *  storage, rhs block 1, Lx Ly = 256 and Lt a multiple of 8, block order 0 (sources of a
- *  column adjacent) or 1 (columns of a source adjacent)), its workgroup size
- *  (512 for variants 2 and 3, else 256), its LDS cap KiB, its block order}.  Block order: 0 = the source blocks of a tile adjacent; 1 =
+ *  column adjacent) or 1 (columns of a source adjacent); 7: one wave per hop, rhs
+ *  block 1, its outputs not streamed, no LDS cap, order 0), its workgroup size
+ *  (512 for variants 2, 3 and 7, else 256), its LDS cap KiB, its block order}.
+ *  Without a set configuration: the default that runs (of the operator pair, for
+ *  batches that run as two halves, the half's).  Block order: 0 = the source blocks of a tile adjacent; 1 =
  *  source block slowest; 2 to 7 = each XCD sweeps its chunk of time slices
  *  once per window of 1, 2, 3, 4, 6 or all source blocks (lattices whose Lx Ly
  *  is a multiple of the tile and Lt of 8; otherwise as 0). */

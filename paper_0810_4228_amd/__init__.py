@@ -287,6 +287,7 @@ class Lattice:
         _check(self._lib.ovs_set_tuning_ex(self._h, int(nrhs), arr), "ovs_set_tuning_ex")
 
     def get_tuning_ex(self, nrhs):
+        """The configuration of get_tuning_raw by name (lanes_per_site 0: one wave per hop)."""
         out = (ctypes.c_int32 * 8)()
         _check(self._lib.ovs_get_tuning_ex(self._h, int(nrhs), out), "ovs_get_tuning_ex")
         keys = ("rhs_block", "wg", "lds_kb", "order")
@@ -298,7 +299,7 @@ class Lattice:
         shape = du["rhs_block"]
         variants = {1: "one thread per site", 2: "lane pair", 3: "lane pair, LDS-staged tile",
                     4: "operator per workgroup", 5: "operator per workgroup, LDS-staged tile",
-                    6: "operator per workgroup, marching along t"}
+                    6: "operator per workgroup, marching along t", 7: "one wave per hop"}
         du.update(rhs_block=shape // 100, variant=variants.get((shape // 10) % 10, "?"),
                   streaming_store=shape % 2, update_streaming_store=(shape % 10) // 2)
         return {"stencil": st, "dual": du}

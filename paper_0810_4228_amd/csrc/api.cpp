@@ -92,10 +92,6 @@ void set_dual_tuning(ovs_lattice_s* l, int nrhs, const Tuning& t) {
   l->dual_tuning.push_back({nrhs, t});
 }
 
-void clear_tuning(std::vector<std::pair<int, Tuning>>& v, int nrhs) {
-  v.erase(std::remove_if(v.begin(), v.end(), [&](auto& p) { return p.first == nrhs; }), v.end());
-}
-
 // Occupancy caps tried by the autotuner: dynamic LDS per workgroup in KiB
 // (0 = none; 40, 53, 80, 160 allow 4, 3, 2, 1 workgroups per CU of 160 KiB).
 std::vector<int> lds_candidates(const ovs_lattice_s* l) {
@@ -750,13 +746,15 @@ ovs_status ovs_get_tuning(ovs_lattice l, int32_t nrhs, int32_t* rhs_block, int32
 
 ovs_status ovs_get_tuning_ex(ovs_lattice l, int32_t nrhs, int32_t out[8]) {
   if (!l || nrhs < 1 || !out) return OVS_ERR_ARG;
-  const Tuning t = get_tuning(l, nrhs), d = get_dual_tuning(l, nrhs);
-  out[0] = t.stage * 1000 + t.rhs_block * 100 + t.g * 10 + t.nt;
+  // (of a batch that runs as two halves, the operator pair's launch is a half's)
+  const Tuning t = get_tuning(l, nrhs);
+  const Tuning d = get_dual_tuning(l, nrhs, nrhs >= kSplitMin ? nrhs / 2 : nrhs);
+  out[0] = t.stage * 1000 + t.rhs_block * 100 + (t.hops ? 0 : t.g) * 10 + t.nt;
   out[1] = t.wg;
   out[2] = t.lds_kb;
   out[3] = t.order;
-  out[4] = d.rhs_block * 100 + d.g * 10 + d.nt;
-  out[5] = (d.g == 2 || d.g == 3) ? 512 : 256;
+  out[4] = d.rhs_block * 100 + (dual_pair_of(d) + 1) * 10 + d.nt;
+  out[5] = (d.hops || d.g == 2 || d.g == 3) ? 512 : 256;
   out[6] = d.lds_kb;
   out[7] = d.order;
   return OVS_OK;
@@ -778,23 +776,31 @@ ovs_status ovs_set_tuning_ex(ovs_lattice l, int32_t nrhs, const int32_t cfg[8]) 
   d.nt = cfg[4] % 10;
   d.lds_kb = cfg[6];
   d.order = cfg[7];
+  t.hops = t.g == 0;
+  d.hops = d.g == kDualHops + 1;
   const bool blk_ok = f32 ? (t.rhs_block == 1 || t.rhs_block == 2 || t.rhs_block == 3 ||
                              t.rhs_block == 4 || t.rhs_block == 6)
                           : (t.rhs_block >= 1 && t.rhs_block <= 3);
-  const bool g_ok = t.g == 1 || ((t.g == 2 || t.g == 4 || t.g == 8) && t.rhs_block == 1);
+  // one wave per hop has one form: 64 sites and one source a workgroup
+  const bool g_ok = (t.hops && t.rhs_block == 1 && t.wg == 64 && !t.stage && !t.nt && !t.lds_kb &&
+                     !t.order) ||
+                    t.g == 1 || ((t.g == 2 || t.g == 4 || t.g == 8) && t.rhs_block == 1);
   // the staged tile (B 12 256 values) fits for B <= 4 in FP32 and B <= 2 in FP64
   const bool stage_ok = t.stage == 0 || (t.stage == 1 && t.g == 1 && t.rhs_block <= (f32 ? 4 : 2));
   const bool wg_ok = t.wg == 64 || t.wg == 128 || t.wg == 256;
   // variant 6 marches along t: FP32 storage, one source per thread, xy planes
   // of 256 sites, Lt % 8 == 0
   const bool march_ok = f32 && l->g.lx * l->g.ly == 256 && l->g.lt % 8 == 0;
-  const bool d_ok = d.rhs_block >= 1 && d.rhs_block <= (f32 ? 4 : 2) && d.g >= 1 && d.g <= 6 &&
+  const bool d_ok = d.rhs_block >= 1 && d.rhs_block <= (f32 ? 4 : 2) && d.g >= 1 &&
+                    (d.g <= 6 || (d.hops && d.rhs_block == 1 && !(d.nt & 1) && !d.lds_kb && !d.order)) &&
                     (d.g != 3 || d.rhs_block <= (f32 ? 2 : 1)) &&
                     (d.g != 6 || (d.rhs_block == 1 && march_ok));
   if (!blk_ok || !g_ok || !stage_ok || !wg_ok || !d_ok || t.nt < 0 || t.nt > 1 || d.nt < 0 || d.nt > 3 ||
       t.lds_kb < 0 || t.lds_kb >= l->lds_max_kb || d.lds_kb < 0 || d.lds_kb >= l->lds_max_kb ||
       t.order < 0 || t.order > 7 || d.order < 0 || d.order > 7)
     return OVS_ERR_ARG;
+  if (t.hops) t.g = 1;
+  if (d.hops) d.g = 1;
   t.tuned = d.tuned = true;
   set_tuning(l, nrhs, t);
   set_dual_tuning(l, nrhs, d);
@@ -854,18 +860,15 @@ ovs_status ovs_autotune(ovs_lattice l, int32_t nrhs) {
             if (ms < best_ms) { best_ms = ms; best = t; }
           }
     }
-    best.tuned = true;
-    // a default that none of the candidates beats (one wave per hop is not among
-    // them) stays the batch's configuration
+    // one wave per hop, where it is the default, unless a candidate beats it
     double def_ms = 1e300;
     const Tuning def = default_tuning(f32, l->g, nrhs);
     if (timed_loop(l, OVS_OP_A, fi, fo, 2, def, &def_ms) != OVS_OK ||
         timed_loop(l, OVS_OP_A, fi, fo, 8, def, &def_ms) != OVS_OK)
       def_ms = 1e300;
-    if (st == OVS_OK) {
-      if (def.hops && def_ms <= best_ms) clear_tuning(l->tuning, nrhs);
-      else set_tuning(l, nrhs, best);
-    }
+    if (def.hops && def_ms <= best_ms) best = def;
+    best.tuned = true;
+    if (st == OVS_OK) set_tuning(l, nrhs, best);
     // dual-stencil source block for the Lanczos step
     if (st == OVS_OK) {
       const long N = 12L * l->g.Vs;
@@ -961,11 +964,9 @@ ovs_status ovs_autotune(ovs_lattice l, int32_t nrhs) {
         // after T and S and the other vectors have passed through the caches:
         // streaming stores measured ~1% faster over whole solves at 16^3 x 32
         dbest.nt |= 2;
+        if (dbest.g == kDualHops + 1) dbest = default_dual_tuning(f32, l->g, n1);
         dbest.tuned = true;
-        if (st == OVS_OK) {
-          if (dbest.g == kDualHops + 1) clear_tuning(l->dual_tuning, nrhs);  // the default
-          else set_dual_tuning(l, nrhs, dbest);
-        }
+        if (st == OVS_OK) set_dual_tuning(l, nrhs, dbest);
         if (s2) (void)hipStreamSynchronize(s2);
         if (fork) (void)hipEventDestroy(fork);
         if (join) (void)hipEventDestroy(join);

@@ -52,3 +52,70 @@ def test_workspace_size_grows_with_the_batch(prec, method, two_pass):
         say("workspace sizes", prec, dims, method, two_pass, n[0], n[4], n[5], n[-1])
         assert n == sorted(n)
         lat.close()
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("dims,nrhs,hops,dual_hops", [
+    ((2, 2, 2, 2), 1, True, True), ((4, 4, 6, 6), 3, True, True), ((8, 8, 8, 8), 12, True, True),
+    ((12, 12, 12, 12), 5, False, "f64"), ((16, 16, 16, 16), 4, False, False)])
+def test_tuning_saved_and_installed_again(prec, dims, nrhs, hops, dual_hops):
+    """get_tuning_raw without a set configuration reports the default that runs, one
+    wave per hop among them (lanes per site 0, variant 7; batches from 8 on: the
+    operator pair of a half), and set_tuning_raw installs it: get, set, get is the
+    identity and a solve equals the untuned one bit for bit."""
+    import torch
+    U = synth.random_links(dims, 0.5, seed=63)
+    lat, other = lattice(dims, prec, U, 0.3), lattice(dims, prec, U, 0.3)
+    raw = lat.get_tuning_raw(nrhs)
+    ex = lat.get_tuning_ex(nrhs)
+    say("tuning", prec, dims, nrhs, raw, ex)
+    assert (ex["stencil"]["lanes_per_site"] == 0) == hops
+    assert (ex["dual"]["variant"] == "one wave per hop") == (dual_hops in (True, prec))
+    other.set_tuning_raw(nrhs, raw)
+    assert other.get_tuning_raw(nrhs) == raw
+    b = to_dev(synth.gaussian_sources(dims, nrhs, seed=64))
+    k = 20
+    assert torch.equal(lat.apply("A", b), other.apply("A", b))
+    assert torch.equal(lat.sign_apply(b, k)[0], other.sign_apply(b, k)[0])
+    lat.close()
+    other.close()
+
+
+def test_tuning_of_one_wave_per_hop():
+    """What the autotuner chose on a small lattice installs on another handle; set
+    for a larger lattice one wave per hop gives the bits of the default forms (FP64
+    sums of the operator pair by quarters of a tile, in the same order); fields it
+    has no use for are refused."""
+    import torch
+    import paper_0810_4228_amd as ovs
+    U = synth.random_links((4, 4, 4, 4), 0.5, seed=65)
+    lat, other = lattice((4, 4, 4, 4), "f64", U, 0.2), lattice((4, 4, 4, 4), "f64", U, 0.2)
+    lat.autotune(2)
+    raw = lat.get_tuning_raw(2)
+    say("autotuned", raw)
+    other.set_tuning_raw(2, raw)
+    assert other.get_tuning_raw(2) == raw
+    good = [100, 64, 0, 0, 172, 512, 0, 0]
+    other.set_tuning_raw(2, good)
+    assert other.get_tuning_raw(2) == good
+    for at, value in ((0, 200), (0, 101), (0, 1100), (1, 256), (2, 40), (3, 1), (4, 272), (4, 171),
+                      (4, 180), (4, 102), (6, 40), (7, 2)):
+        bad = list(good)
+        bad[at] = value
+        with pytest.raises(ovs.OvsError) as e:
+            other.set_tuning_raw(2, bad)
+        assert e.value.status == ovs.OVS_ERR_ARG, bad
+        assert other.get_tuning_raw(2) == good
+    lat.close()
+    other.close()
+    for prec in ("f64", "f32"):
+        dims = (16, 16, 16, 16)
+        U = synth.random_links(dims, 0.5, seed=66)
+        b = to_dev(synth.gaussian_sources(dims, 3, seed=67))
+        lat, other = lattice(dims, prec, U, 0.2), lattice(dims, prec, U, 0.2)
+        other.set_tuning_raw(3, [100, 64, 0, 0, 170, 512, 0, 0])
+        for method in ({}, {"two_pass": True}, {"graph": True}, {"persistent": True}):
+            assert torch.equal(lat.sign_apply(b, 12, **method)[0], other.sign_apply(b, 12, **method)[0])
+        assert torch.equal(lat.apply("A", b), other.apply("A", b))
+        lat.close()
+        other.close()
