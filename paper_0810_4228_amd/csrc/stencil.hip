@@ -325,7 +325,9 @@ k_wilson(const typename Vec2<R>::T* __restrict__ links, const typename Vec2<R>::
           const int e = u * wg + (int)threadIdx.x;
           if (e < n) {
             const T2 v = plane[e / 12 * 13 + e % 12];
-            st64_nt(dst + e, Cx<double>{(double)v.x, (double)v.y});
+            const Cx<double> o = {(double)v.x, (double)v.y};
+            if (nt) st64_nt(dst + e, o);
+            else st64(dst + e, o);
           }
         }
       } else {
@@ -582,16 +584,25 @@ static hipError_t launch_canon(const void* links, const double2* x, double2* y, 
   if constexpr (f32) launch_pack_f32(x, (float2*)fin, nrhs, g, s);
   else launch_pack_f64(x, (double2*)fin, nrhs, g, s);
   if (!tn.hops && tn.stage && tn.rhs_block == 1 && tn.g == 1) {
-    // its own tile and order (16^3 x 32 x 12 FP32: 128 sites, order 4 217 us with
-    // the conversion, orders 0 and 7 236, 256 sites 222-228; x 4 FP64: 256 sites,
-    // order 0 119 us, 128 sites 122-126)
-    const int wg = f32 ? 128 : 256;
-    const TileMap tm = make_tile_map(g, wg, nrhs, f32 ? 4 : 0);
-    if (!lds_fits((const void*)k_wilson<R, 1, true, true>, 0)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_wilson<R, 1, true, true>), dim3(8 * tm.per_xcd), dim3(wg), 0, s,
-                       (const T2*)links, (const T2*)fin, (T2*)nullptr, g, HopR<R>::make(hop_c),
-                       nrhs, (int)g5in, (int)g5out, 0, tm, y);
-    return hipGetLastError();
+    // Tile, order, LDS cap and store of the configuration.  The default's are chosen
+    // for the resident stencil: here it streams its stores (FP32 16^4 x 12 98 us, 105
+    // to 130 without), and FP32 calls whose tensors pass the 256 MB cache take
+    // 128-site tiles in windows of three sources (16^3 x 32 x 12, 604 MB of tensors,
+    // 218 us against 228 with the default's 256-site tiles; 16^4 x 12, 302 MB, 105
+    // against 98, x 4 43 against 39; FP64 16^4 x 4 67 against 64).
+    const bool def = tn.wg == 256 && !tn.order && !tn.lds_kb && !tn.nt;
+    const bool window = def && f32 && (long)g.V * nrhs >= 1200000;
+    const int wg = window ? 128 : tn.wg;
+    const TileMap tm = make_tile_map(g, wg, nrhs, window ? 4 : tn.order);
+    static std::once_flag lds_set;
+    std::call_once(lds_set, [] { apply_lds_limit((const void*)k_wilson<R, 1, true, true>); });
+    if (lds_fits((const void*)k_wilson<R, 1, true, true>, tn.lds_kb)) {
+      hipLaunchKernelGGL((k_wilson<R, 1, true, true>), dim3(8 * tm.per_xcd), dim3(wg),
+                         tn.lds_kb * 1024, s, (const T2*)links, (const T2*)fin, (T2*)nullptr, g,
+                         HopR<R>::make(hop_c), nrhs, (int)g5in, (int)g5out, (int)(def || tn.nt), tm,
+                         y);
+      return hipGetLastError();
+    }
   }
   const hipError_t e = launch_wilson(f32, links, fin, fout, nrhs, g, hop_c, g5in, g5out, tn, s);
   if (e != hipSuccess) return e;

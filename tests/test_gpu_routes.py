@@ -119,3 +119,36 @@ def test_tuning_of_one_wave_per_hop():
         assert torch.equal(lat.apply("A", b), other.apply("A", b))
         lat.close()
         other.close()
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+def test_apply_obeys_a_set_configuration(prec):
+    """apply on tensors runs the configuration that is set, as resident fields do: an
+    LDS cap that fits serves both with the same bits, and one that does not fit
+    beside the staged tile (FP64 48 KiB, FP32 24 KiB of a CU's 160) is refused by both
+    as OVS_ERR_HIP."""
+    import torch
+    import paper_0810_4228_amd as ovs
+    dims = (4, 4, 6, 6)
+    lat = lattice(dims, prec, synth.random_links(dims, 0.6, seed=70), 0.3)
+    b = to_dev(synth.gaussian_sources(dims, 2, seed=71))
+    f, g = lat.field_create(2), lat.field_create(2)
+    f.import_(b)
+    base = lat.get_tuning_raw(2)
+    ref = lat.apply("A", b)
+    # caps that fit beside both forms, beside the resident form alone, beside neither
+    for cap in (40, 106, 110, 158) if prec == "f64" else (40, 132, 135, 158):
+        for wg in (64, 256):
+            lat.set_tuning_raw(2, [1110, wg, cap, 0] + base[4:])
+            if cap < 158:
+                f.apply("A", g)
+                assert torch.equal(g.export().reshape(b.shape), ref)
+                assert torch.equal(lat.apply("A", b), ref), (cap, wg)
+            else:
+                for call in (lambda: f.apply("A", g), lambda: lat.apply("A", b)):
+                    with pytest.raises(ovs.OvsError) as e:
+                        call()
+                    assert e.value.status == ovs.OVS_ERR_HIP
+    f.close()
+    g.close()
+    lat.close()
