@@ -3,7 +3,7 @@ route is open to the calls that the interface admits, with the same results (GPU
 import pytest
 
 import synth
-from gpu_util import say, to_dev
+from gpu_util import rel_rows, say, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -119,6 +119,55 @@ def test_tuning_of_one_wave_per_hop():
         assert torch.equal(lat.apply("A", b), other.apply("A", b))
         lat.close()
         other.close()
+
+
+def configurations(prec, nrhs):
+    """(shape, workgroup, order) of the stencil configurations the autotuner can pick."""
+    shapes = [(blk, 1, st) for blk in ((1, 2, 3, 4, 6) if prec == "f32" else (1, 2, 3))
+              for st in (0, 1) if st == 0 or blk <= (4 if prec == "f32" else 2)]
+    shapes += [(1, g, 0) for g in (2, 4, 8)]
+    for blk, g, st in shapes:
+        for wg in (64, 128, 256):
+            for order in range(8):
+                for nt in (0, 1):
+                    yield 1000 * st + 100 * blk + 10 * g + nt, wg, order
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("dims", [(4, 4, 6, 6), (16, 16, 2, 8), (8, 8, 4, 8)])
+def test_every_configuration_on_resident_fields(prec, dims):
+    """Every stencil configuration through import, apply and export, and through
+    apply on tensors: 1e-14 (FP64) and 1e-6 (FP32 storage) of the oracle for the
+    first of each shape, and the same bits by all others and by both routes.  A
+    ragged lattice, and planar ones for 256- and 64-site tiles with Lt = 8 (grouped
+    block orders), 7 sources (ragged source blocks and windows)."""
+    import torch
+    from oracle import dirac
+    U = synth.random_links(dims, 0.6, seed=68)
+    b = synth.gaussian_sources(dims, 7, seed=69)
+    lat = lattice(dims, prec, U, 0.3)
+    bt = to_dev(b)
+    f, g = lat.field_create(7), lat.field_create(7)
+    f.import_(bt)
+    base = lat.get_tuning_raw(7)
+    for op in ("A", "Dw_dag"):
+        m = dirac.csr_A(dims, U, MW, 0.3) if op == "A" else dirac.csr_dw(dims, U, MW, 0.3)
+        ref = ((m if op == "A" else m.conj().T.tocsr()) @ b.T).T
+        first, n = None, 0
+        for cfg in configurations(prec, 7):
+            lat.set_tuning_raw(7, [cfg[0], cfg[1], 0, cfg[2]] + base[4:])
+            f.apply(op, g)
+            y = g.export().reshape(bt.shape)
+            if first is None:
+                first = y
+                assert rel_rows(y.cpu().numpy(), ref) <= (1e-14 if prec == "f64" else 1e-6)
+            assert torch.equal(y, first), (op, cfg)
+            assert torch.equal(lat.apply(op, bt), first), (op, cfg)
+            n += 1
+        say("resident configurations", prec, dims, op, n)
+    f.close()
+    g.close()
+    lat.close()
 
 
 @pytest.mark.parametrize("prec", ["f64", "f32"])
