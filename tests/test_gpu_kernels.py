@@ -164,3 +164,36 @@ def test_arnoldi_vector_groups(k):
         assert info[r]["k_used"] == k
         assert e <= 2 * info[r]["quad_err"] + 1e-10
     lat.close()
+
+
+@pytest.mark.parametrize("k", [1, 3, 4, 5, 6, 7, 11, 12, 13, 14, 64, 67, 68, 69, 70, 72, 129])
+def test_inner_sign_tridiag_batch_of_steps(k):
+    """sgn(T) e_1 by trailing minors, at every residue of k mod 8 (the groups of
+    minors that share an exponent and the start of the row blocks), for a batch of
+    eight whose matrices end at quadrature steps from 1/4 to 1/64: entries of the
+    first row turned to angles d from the imaginary axis, where the difference of the
+    rules with steps h and 2 h is about 2 exp(-pi d / h).  The batch runs in several
+    launches that share their scratch, with rounds in which some matrices are done;
+    every row equals its batch of one (one launch a round) bit for bit.  The accepted
+    rule's error is of the order of the squared difference; what remains is rounding:
+    the weighted sums (some 7e-14), the minors and the oracle's eigenvectors (each
+    some k eps), over the distance d of the nodes from the spectrum: 1e-12 / d."""
+    import paper_0810_4228_amd as ovs
+    rng = np.random.default_rng(300 + k)
+    angle = np.array([1.5, 0.8, 0.4, 0.2, 0.1, 1.5, 0.2, 0.4])
+    n = len(angle)
+    diag = rng.choice([-1.0, 1.0], (n, k)) * (1 + 0.3 * rng.random((n, k))) \
+        + 0.05j * rng.standard_normal((n, k))
+    diag[:, 0] = np.exp(1j * (np.pi / 2 - angle))
+    sub = (0.05 + 0.05 * rng.random((n, k))).astype(complex)
+    sup = 0.03 * (rng.standard_normal((n, k)) + 1j * rng.standard_normal((n, k)))
+    lat = ovs.Lattice((2, 2, 2, 2))
+    x, err, st = lat.inner_sign_tridiag(diag, sub, sup, return_status=True)
+    assert st == 0
+    for r in range(n):
+        one, err1 = lat.inner_sign_tridiag(diag[r], sub[r], sup[r])
+        e = rel(x[r], sign.sign_e1(krylov.tridiag(diag[r], sub[r, :k - 1].real, sup[r, :k - 1])))
+        say(f"inner sign k={k} angle {angle[r]}: {e:.1e}, estimate {err[r]:.1e}")
+        assert np.array_equal(x[r], one[0]) and err[r] == err1[0]
+        assert e <= 10 * err[r] ** 2 + 1e-12 / angle[r]
+    lat.close()
