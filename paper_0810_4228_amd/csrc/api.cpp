@@ -107,6 +107,9 @@ std::vector<int> lds_candidates(const ovs_lattice_s* l) {
 // the growth of cached buffers hold this lock.
 static std::mutex g_capture_mu;
 
+// Memory that single kernels on the caller's stream may still use (the workspace,
+// fields, links) is freed by hipFree alone, which waits for the whole device: the
+// caller's stream may be gone by then, so it is not waited for by name.
 ovs_status ensure_ws(ovs_lattice_s* l, size_t bytes) {
   if (l->ws && l->ws_bytes >= bytes) return OVS_OK;
   std::lock_guard<std::mutex> lock(g_capture_mu);

@@ -201,3 +201,40 @@ def test_apply_obeys_a_set_configuration(prec):
     f.close()
     g.close()
     lat.close()
+
+
+def test_closing_behind_enqueued_calls():
+    """Operator calls only enqueue; a workspace that grows, a field or a lattice that
+    is closed behind them waits for them: results as with synchronisations between."""
+    import torch
+    import paper_0810_4228_amd as ovs
+    dims = (12, 12, 12, 24)
+    U = to_dev(synth.random_links(dims, 0.5, seed=72))
+    b = to_dev(synth.gaussian_sources(dims, 8, seed=73))
+    out = []
+    for wait in (True, False):
+        done = []
+        with torch.cuda.stream(torch.cuda.Stream()):
+            lat = ovs.Lattice(dims, precision="f32")
+            lat.set_links(U)
+            lat.set_params(MW, 0.2)
+            f, g = lat.field_create(8), lat.field_create(8)
+            f.import_(b)
+            for _ in range(20):
+                f.apply("A", g)
+                g.apply("A_dag", f)
+            done.append(f.export())
+            for n in (4, 6, 8):   # staged forms: the scratch fields grow
+                done.append(lat.apply("A", b[:n].contiguous()))
+                if wait:
+                    torch.cuda.synchronize()
+            for h in (f, g, lat):
+                h.close()
+                if wait:
+                    torch.cuda.synchronize()
+            scrap = torch.full((64 << 20,), 1.0, dtype=torch.float64, device="cuda")
+        torch.cuda.synchronize()
+        del scrap
+        out.append(done)
+    for x, y in zip(*out):
+        assert torch.isfinite(torch.view_as_real(x)).all() and torch.equal(x, y)
