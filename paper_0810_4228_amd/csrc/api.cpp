@@ -267,7 +267,7 @@ std::vector<double> quad_targets(const double* tol, int nrhs) {
 // return the step it was accepted at.  Without it every source starts at
 // kHStart.  Every round takes each unaccepted source at its own step and, where
 // both fit the scratch, the next finer one in the same launch: a launch takes
-// the time of one elimination however many solves it holds, and the device
+// the time of one sweep of minors however many solves it holds, and the device
 // picks the first step that meets the target.  A source's steps depend only on
 // its own differences, so its x, and with it the convergence checks that pass
 // their levels from one check to the next, do not depend on the rest of the

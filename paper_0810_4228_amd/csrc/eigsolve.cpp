@@ -412,7 +412,8 @@ ovs_status compute_eigentriples(ovs_lattice_s* l, int m, double tol, int max_ite
     if (hipMemsetAsync(cX, 0, sizeof(double2) * Np, s) != hipSuccess) return OVS_ERR_HIP;
     if (!apply(cY, cW, 1, hb)) return OVS_ERR_HIP;  // b = M^H y (kept in cW until the first step)
     if (!project_add(D, cW, cX)) return OVS_ERR_HIP;
-    // r = b - M^H M x; the first step's direction is r (beta = 0)
+    // r = b - M^H M x; the first step's direction is r + 0 p = r: cP holds y - M x by
+    // then, every entry new and finite where r is
     auto restart = [&]() -> bool {
       if (!apply(cX, cT, 1, hf)) return false;
       launch_resid(cP, cY, cT, one_d, 1, Np, s);  // y - M x

@@ -455,8 +455,8 @@ __device__ void gp_coef_rows(const GradScalars& s, int i, const TabOut& o) {
 // Every workgroup of source r forms the step's coefficient rows itself (the
 // same dot sums in the same order, kWG = kScalarWG threads, so the same
 // values as the separate scalar kernel) and keeps them in LDS; the first
-// workgroup of each source also writes the step's scalars and, with
-// global_tabs, the global tables.  That saves the scalar kernel's launch.
+// workgroup of each source also writes the step's scalars.  That saves the
+// scalar kernel's launch.
 // Every value a step reads is written by earlier launches and none is
 // written in this one, except the scalars of workgroup 0, which no other
 // workgroup of the launch reads.

@@ -11,7 +11,8 @@
 //
 // Bound by latency: one batch of loads instead of eight in a row, and an eighth
 // of the arithmetic per lane.  The price is that nothing is shared between the
-// operators or sources, and 49 KiB of LDS traffic per workgroup in FP64: larger
+// operators or sources, and 48 KiB of LDS in FP64 that take 144 KiB of traffic (six
+// entries of eight hops written, twelve components of eight hops read): larger
 // grids, whose other waves hide the latency, are faster with one thread per site.
 #pragma once
 
