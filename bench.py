@@ -47,12 +47,12 @@ SAVED_TUNING = os.path.join(ROOT, "paper_0810_4228_amd", "tuning_mi355x.json")
 # (profiles/*_hbm_counters.txt).  Reported only while the kernel source and
 # the autotuner's choice are the ones that were measured.
 TRAFFIC = {
-    "stencil": {"source_sha256_prefix": "a7a8e2649522da8a",
-                "tuning": {"rhs_block": 1, "wg": 128, "lds_kb": 0, "order": 7, "lanes_per_site": 1, "streaming_store": 1, "staged_tile": 1},
-                "bytes_per_launch": 1.9998 * 203933.94 * 1024 + 1.0000 * 147460.89 * 1024},
-    "dual": {"source_sha256_prefix": "a7a8e2649522da8a",
+    "stencil": {"source_sha256_prefix": "794f83d7a5d7e123",
+                "tuning": {"rhs_block": 1, "wg": 128, "lds_kb": 0, "order": 4, "lanes_per_site": 1, "streaming_store": 1, "staged_tile": 1},
+                "bytes_per_launch": 1.9998 * 268048.61 * 1024 + 1.0000 * 147462.31 * 1024},
+    "dual": {"source_sha256_prefix": "794f83d7a5d7e123",
              "tuning": {"rhs_block": 1, "wg": 256, "lds_kb": 53, "order": 4, "variant": "one thread per site", "streaming_store": 1, "update_streaming_store": 1},
-             "bytes_per_launch": 1.9998 * 453238.45 * 1024 + 1.0000 * 295162.41 * 1024},
+             "bytes_per_launch": 1.9998 * 453431.09 * 1024 + 1.0000 * 295164.72 * 1024},
 }
 
 
@@ -505,7 +505,7 @@ def main():
     ap.add_argument("--tuning", default=SAVED_TUNING,
                     help="JSON file with a saved kernel configuration: loaded if present, "
                          "written after autotuning otherwise (default: the configuration "
-                         "the autotuner chose on an MI355X, the one the committed counter "
+                         "of this workload on an MI355X, the one the committed counter "
                          "profiles were taken with)")
     ap.add_argument("--retune", action="store_true",
                     help="autotune even if the tuning file holds a configuration")

@@ -161,7 +161,8 @@ ovs_status ovs_set_debug(ovs_lattice lat, int32_t flags, int32_t breakdown_at);
 /* y = op x for nrhs sources (Section 1).  x, y: device complex128
  * [nrhs][V][4][3], must not alias.  OVS_OP_A is gamma5 Dw(mu), OVS_OP_A_DAG its
  * adjoint (= gamma5 Dw(-mu)), OVS_OP_DW_DAG = gamma5 Dw(-mu) gamma5.  In
- * OVS_F32_STORE mode the stencil runs in FP32 (inputs rounded to FP32). */
+ * OVS_F32_STORE mode the stencil runs in FP32 (inputs rounded to FP32).  A
+ * configuration set for nrhs (below) holds here as for resident fields. */
 ovs_status ovs_apply(ovs_lattice lat, ovs_op op, const void* x, void* y, int32_t nrhs);
 
 /* For callers that cannot allocate device memory (code under HIP graph
@@ -227,8 +228,8 @@ ovs_status ovs_get_tuning(ovs_lattice lat, int32_t nrhs, int32_t* rhs_block, int
  *  block 1, its outputs not streamed, no LDS cap, order 0), its workgroup size
  *  (512 for variants 2, 3 and 7, else 256), its LDS cap KiB, its block order}.
  *  Without a set configuration: the default that runs (of the operator pair, for
- *  batches that run as two halves, the half's).  Block order: 0 = the source blocks of a tile adjacent; 1 =
- *  source block slowest; 2 to 7 = each XCD sweeps its chunk of time slices
+ *  batches that run as two halves, the half's).  Block order: 0 = the source
+ *  blocks of a tile adjacent; 1 = source block slowest; 2 to 7 = each XCD sweeps its chunk of time slices
  *  once per window of 1, 2, 3, 4, 6 or all source blocks (lattices whose Lx Ly
  *  is a multiple of the tile and Lt of 8; otherwise as 0). */
 ovs_status ovs_get_tuning_ex(ovs_lattice lat, int32_t nrhs, int32_t out[8]);
@@ -271,7 +272,9 @@ ovs_status ovs_deflation_destroy(ovs_deflation d);
  * needs (its `workspace` argument): both halves of a batch that is split, with
  * convergence checks, and the one-pass basis for k_max vectors (at 16^3 x 32
  * with 12 sources and k_max = 1000, about 150 GB in FP32 storage;
- * OVS_FLAG_TWO_PASS keeps three vectors: 2.6 GB).  No device work, and links
+ * OVS_FLAG_TWO_PASS keeps three vectors: 2.6 GB).  Does not decrease with nrhs,
+ * so the size for a batch serves its parts; a larger workspace may let the inner
+ * sign of up to five sources run in fewer launches.  No device work, and links
  * need not be set; OVS_ERR_ARG as for ovs_sign_apply. */
 ovs_status ovs_workspace_size(ovs_lattice lat, ovs_deflation defl, int32_t n_defl, int32_t nrhs,
                               int32_t k_max, ovs_method method, int32_t flags, size_t* bytes);
